@@ -20,10 +20,6 @@ namespace lya {
 constexpr int kPdWaves = 4;
 constexpr int kPdNT = 64 * kPdWaves;
 
-__global__ void __launch_bounds__(64) k_p1d_reset(unsigned int* queue) {
-  if (threadIdx.x == 0) queue[0] = 0u;
-}
-
 __global__ void __launch_bounds__(kPdNT) k_p1d(P1dArgs a) {
   __shared__ float2 sbuf[kPdWaves][kHalfBuf];
   __shared__ float spw[kPdWaves][kHalfMax + 1];
@@ -155,7 +151,6 @@ __global__ void __launch_bounds__(256) k_p1d_reduce(int64_t n_sk, int nk, const 
 }
 
 hipError_t launch_p1d(const P1dArgs& a, double* psum, int64_t* pcount, hipStream_t st) {
-  LYA_TIMED("p1d_reset", st, hipLaunchKernelGGL(k_p1d_reset, dim3(1), dim3(64), 0, st, a.queue));
   const int64_t nchunks = (a.n_sk + a.chunk - 1) / a.chunk;
   int64_t blocks = static_cast<int64_t>(device_cus()) * 3;
   if (blocks * kPdWaves > nchunks) blocks = (nchunks + kPdWaves - 1) / kPdWaves;

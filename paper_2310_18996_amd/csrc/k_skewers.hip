@@ -33,16 +33,6 @@ namespace lya {
 constexpr int kSkWaves = 4;
 constexpr int kSkNT = 64 * kSkWaves;
 
-__global__ void __launch_bounds__(256) k_skewer_reset(unsigned int* queue, unsigned long long* bsum,
-                                                      unsigned long long* bcnt) {
-  const int t = threadIdx.x;
-  if (t == 0) queue[0] = 0u;
-  if (t < kMaxZBins) {
-    bsum[t] = 0ull;
-    bcnt[t] = 0ull;
-  }
-}
-
 __global__ void __launch_bounds__(256) k_skewer_finalize(int n_bins, const unsigned long long* bsum,
                                                          const unsigned long long* bcnt, double* fsum,
                                                          int64_t* cnt) {
@@ -532,10 +522,8 @@ void launch_skewer_kernel(const SkewerArgs& a, int u, dim3 grid, hipStream_t st)
 }
 
 hipError_t launch_skewers(const SkewerArgs& a, hipStream_t st) {
-  LYA_TIMED("skewer_reset", st,
-            hipLaunchKernelGGL(k_skewer_reset, dim3(1), dim3(256), 0, st, a.queue, a.bin_sum, a.bin_cnt));
-  const int64_t nchunks = (a.n_sk + a.chunk - 1) / a.chunk;
   int64_t blocks = static_cast<int64_t>(device_cus()) * (a.blocks_per_cu > 0 ? a.blocks_per_cu : 4);
+  const int64_t nchunks = (a.n_sk + a.chunk - 1) / a.chunk;
   if (blocks * kSkWaves > nchunks) blocks = (nchunks + kSkWaves - 1) / kSkWaves;
   if (blocks < 1) blocks = 1;
   const int u = a.unroll == 1 || a.unroll == 4 ? a.unroll : 2;

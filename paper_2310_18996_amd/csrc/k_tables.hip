@@ -139,32 +139,127 @@ __global__ void __launch_bounds__(256) k_xi_weights(const double* amp, PkParams 
   f[j] = w * h / 3.0 * P * exp(-(k * s) * (k * s)) * k;
 }
 
-// ---- pixel redshift table: z at chi = i * h_chi, i = 0..n-1 ----
+// ---- pixel redshift table: z at chi = i * kZTabH ----
 __device__ __forceinline__ double inv_e(double z, double om) {
   const double zp = 1.0 + z;
-  return 1.0 / sqrt(om * zp * zp * zp + (1.0 - om));
+  return rsqrt(om * zp * zp * zp + (1.0 - om));
 }
 
-__device__ double chi_of_z(double z, double om) {
-  // composite Simpson, 128 intervals on [0, z]: relative error ~1e-9 for z < 5
+// Sum over the 16 lanes of a group (one DPP row), the same bits in every
+// lane, so that the lanes take the same branches: the empty asm keeps the
+// compiler from fusing v's last product into a lane's own first addition.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const uint64_t u = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(u), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), CTRL, 0xf, 0xf, false);
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<uint32_t>(lo));
+}
+__device__ __forceinline__ double group_sum(double v) {
+  asm volatile("" : "+v"(v));
+  v += dpp_f64<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  v += dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  v += dpp_f64<0x141>(v);  // row_half_mirror
+  v += dpp_f64<0x140>(v);  // row_mirror
+  return v;
+}
+
+// chi(z) by composite Simpson, 128 intervals on [0, z] (relative error ~1e-9
+// for z < 5), the nodes dealt out over a group of 16 lanes: lane l takes the
+// nodes l + 1 + 16 t, all of one parity (lane 15's last one is the end node).
+__device__ __forceinline__ double chi_of_z_group(double z, double om, int l) {
   constexpr int m = 128;
-  const double h = z / m;
-  double s = inv_e(0.0, om) + inv_e(z, om);
-  for (int i = 1; i < m; ++i) s += ((i & 1) ? 4.0 : 2.0) * inv_e(h * i, om);
-  return kCOverH0 * h / 3.0 * s;
+  const double h = z / m, w = (l & 1) ? 2.0 : 4.0;
+  double s = 0.0;
+#pragma unroll
+  for (int t = 0; t < m / 16; ++t) {
+    const int i = l + 1 + 16 * t;
+    s += (i == m ? 1.0 : w) * inv_e(h * i, om);
+  }
+  return kCOverH0 * h / 3.0 * (group_sum(s) + inv_e(0.0, om));
 }
 
-__global__ void __launch_bounds__(256) k_zchi_table(double om, double h_chi, int n, float* ztab) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const double chi = h_chi * i;
+// Positive nodes and weights of the 16-point Gauss-Legendre rule on [-1, 1].
+__constant__ double kGlX[8] = {0.09501250983763744, 0.2816035507792589,  0.45801677765722737, 0.6178762444026438,
+                               0.755404408355003,   0.8656312023878318,  0.9445750230732326,  0.9894009349916499};
+__constant__ double kGlW[8] = {0.1894506104550685,  0.18260341504492358, 0.16915651939500254, 0.14959598881657674,
+                               0.12462897125553388, 0.09515851168249279, 0.062253523938647894, 0.027152459411754096};
+
+// z(chi) by Newton on the Simpson chi(z), from z = chi H0/c, until a step is
+// below 1e-11 (at most 20 steps), by a group of 16 lanes per node.  A thread
+// per node with 129 square roots and divisions in each of its 5-20 steps was
+// one serial chain of 0.23 ms on 79 blocks, whatever the size of the call.
+// Split over 16 lanes, and with the first steps taken on the 16-point
+// Gauss-Legendre chi(z) (one node per lane: it agrees with the Simpson rule
+// to ~1e-9 for z < 5, so one or two Simpson steps remain), the table takes
+// 0.018 ms.  Where the quick start has not settled below z = 60, or the
+// Simpson steps from it do not (towards and beyond the horizon, where no z has
+// that distance), the steps start again from z = chi H0/c; a NaN stays one.
+__device__ __forceinline__ double z_of_chi_group(double chi, double om, int l) {
+  const double x0 = (l & 1) ? kGlX[l >> 1] : -kGlX[l >> 1], w0 = kGlW[l >> 1];
+  auto slope = [om](double z) { return sqrt(om * (1 + z) * (1 + z) * (1 + z) + 1 - om) / kCOverH0; };
   double z = chi / kCOverH0;
-  for (int it = 0; it < 20; ++it) {
-    const double dz = (chi_of_z(z, om) - chi) * sqrt(om * (1 + z) * (1 + z) * (1 + z) + 1 - om) / kCOverH0;
+  bool quick = false;
+  for (int it = 0; it < 10 && !quick && z < 60.0; ++it) {
+    const double half = 0.5 * z;
+    const double dz = (kCOverH0 * half * group_sum(w0 * inv_e(half * (x0 + 1.0), om)) - chi) * slope(z);
     z -= dz;
-    if (fabs(dz) < 1e-11) break;
+    quick = fabs(dz) < 1e-6;
   }
-  ztab[i] = static_cast<float>(z);
+  quick = quick && z >= 0.0 && z < 60.0;
+  for (int start = quick ? 0 : 1; start < 2; ++start) {
+    if (start == 1) z = chi / kCOverH0;
+    const int most = start == 0 ? 6 : 20;
+    for (int it = 0; it < most; ++it) {
+      const double dz = (chi_of_z_group(z, om, l) - chi) * slope(z);
+      z -= dz;
+      if (fabs(dz) < 1e-11 || z != z) return z;
+    }
+  }
+  return z;
+}
+
+// What a call needs before its main kernel, in one launch (each of these was
+// a launch of 4-5 us of its own): the z(chi) table (ztab), the 2048 twiddles
+// (tw), and the work-queue counter and bin sums cleared (queue, bsum, bcnt;
+// ordinary stores, no memset node).  Null pointers are left out.  The table's
+// blocks come first and in decreasing chi (the far nodes take the most steps).
+constexpr int kPrepNT = 256;
+constexpr int kPrepZBlocks = (kZTabN * 16 + kPrepNT - 1) / kPrepNT;
+constexpr int kPrepTwBlocks = kTw2048 / kPrepNT;
+
+__global__ void __launch_bounds__(kPrepNT) k_prep(PrepArgs a) {
+  const int nz = a.ztab ? kPrepZBlocks : 0, nt = a.tw ? kPrepTwBlocks : 0;
+  int b = blockIdx.x;
+  const int t = threadIdx.x;
+  if (b < nz) {
+    // the lanes of a group share their node, so a group leaves as a whole
+    const int i = kZTabN - 1 - (b * (kPrepNT / 16) + (t >> 4));
+    if (i < 0) return;
+    const double z = z_of_chi_group(kZTabH * i, a.omega_m, t & 15);
+    if ((t & 15) == 0) a.ztab[i] = static_cast<float>(z);
+    return;
+  }
+  b -= nz;
+  if (b < nt) {
+    const int k = b * kPrepNT + t;
+    double sn, cs;
+    sincospi(2.0 * k / kTw2048, &sn, &cs);
+    a.tw[k] = make_float2(static_cast<float>(cs), static_cast<float>(sn));
+    return;
+  }
+  if (t == 0 && a.queue) a.queue[0] = 0u;
+  if (t < kMaxZBins && a.bsum) {
+    a.bsum[t] = 0ull;
+    a.bcnt[t] = 0ull;
+  }
+}
+
+hipError_t launch_prep(const PrepArgs& a, hipStream_t st) {
+  const int blocks = (a.ztab ? kPrepZBlocks : 0) + (a.tw ? kPrepTwBlocks : 0) + (a.queue || a.bsum ? 1 : 0);
+  if (blocks == 0) return hipSuccess;
+  LYA_TIMED("prep", st, hipLaunchKernelGGL(k_prep, dim3(blocks), dim3(kPrepNT), 0, st, a));
+  return hipGetLastError();
 }
 
 // ---- launchers ----
@@ -193,9 +288,10 @@ hipError_t launch_xi_weights(const PkParams& p, double s, double h, int m, doubl
 }
 
 hipError_t launch_zchi_table(double omega_m, float* ztab, hipStream_t st) {
-  LYA_TIMED("zchi_table", st,
-            hipLaunchKernelGGL(k_zchi_table, dim3((kZTabN + 255) / 256), dim3(256), 0, st, omega_m, kZTabH, kZTabN, ztab));
-  return hipGetLastError();
+  PrepArgs a{};
+  a.omega_m = omega_m;
+  a.ztab = ztab;
+  return launch_prep(a, st);
 }
 
 __global__ void __launch_bounds__(256) k_twiddles(float2* tw, int ntw) {

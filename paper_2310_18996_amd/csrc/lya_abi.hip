@@ -297,15 +297,15 @@ int run_skewers(lya::SkewerArgs& a, const lya_cosmo* cosmo, const lya_zbins* zb,
     }
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
-  hipError_t e = hipSuccess;
-  if (a.do_flux) {
-    e = lya::launch_zchi_table(cosmo->omega_m, const_cast<float*>(a.ztab), st);
-    if (e != hipSuccess) return hip_fail(e, "redshift table");
-  }
-  if (a.field || a.field_bf16 || a.ds_in_apply) {
-    e = lya::launch_twiddles(const_cast<float2*>(a.tw2048), lya::kTw2048, st);
-    if (e != hipSuccess) return hip_fail(e, "twiddles");
-  }
+  lya::PrepArgs pa{};
+  pa.omega_m = cosmo ? cosmo->omega_m : 0.0;
+  pa.ztab = a.do_flux ? const_cast<float*>(a.ztab) : nullptr;
+  pa.tw = (a.field || a.field_bf16 || a.ds_in_apply) ? const_cast<float2*>(a.tw2048) : nullptr;
+  pa.queue = a.queue;
+  pa.bsum = a.bin_sum;
+  pa.bcnt = a.bin_cnt;
+  hipError_t e = lya::launch_prep(pa, st);
+  if (e != hipSuccess) return hip_fail(e, "skewer tables");
   e = lya::launch_skewers(a, st);
   if (e != hipSuccess) return hip_fail(e, "skewer kernel");
   return LYA_OK;
@@ -428,7 +428,10 @@ int lya_p1d(const lya_skewers* sk, const lya_cosmo* cosmo, const float* flux, co
   a.queue = reinterpret_cast<unsigned int*>(w + c.queue);
   a.chunk = 4;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  hipError_t e = lya::launch_twiddles(const_cast<float2*>(a.tw2048), lya::kTw2048, st);
+  lya::PrepArgs pa{};
+  pa.tw = const_cast<float2*>(a.tw2048);
+  pa.queue = a.queue;
+  hipError_t e = lya::launch_prep(pa, st);
   if (e != hipSuccess) return hip_fail(e, "twiddles");
   e = lya::launch_p1d(a, psum, pcount, st);
   if (e != hipSuccess) return hip_fail(e, "1D power kernel");

@@ -76,6 +76,18 @@ int device_cus();
 double growth_lcdm(double z, double om);
 
 hipError_t launch_pk_table(const PkParams& p, int n, double dx, TableWork& w, hipStream_t st);
+// One launch for what precedes a call's main kernel: z(chi) table, the
+// kTw2048 twiddles, cleared work-queue counter and kMaxZBins bin sums (null
+// pointers are left out).
+struct PrepArgs {
+  double omega_m;
+  float* ztab;
+  float2* tw;
+  unsigned int* queue;
+  unsigned long long* bsum;
+  unsigned long long* bcnt;
+};
+hipError_t launch_prep(const PrepArgs& a, hipStream_t st);
 hipError_t launch_zchi_table(double omega_m, float* ztab, hipStream_t st);
 // Simpson-weighted integrand of xi_m (k_j = j h, j = 0..m): sigma8
 // normalisation first for the analytic form (partial: kSigmaBlocks, amp: 1).

@@ -188,8 +188,10 @@ hipError_t launch_box_moments(const float2* box, int n, double* part, double* ou
 // ---- per-distance table: {z, c_1, c_2, c_3} at chi = i kZTabH ----
 __device__ __forceinline__ double bias_qso(double z) { return 3.7 * pow((1.0 + z) / 3.33, 1.7); }
 
-__global__ void __launch_bounds__(256) k_qso_coef(const float* __restrict__ ztab, QsoCoef c, float4* __restrict__ tab) {
+__global__ void __launch_bounds__(256) k_qso_coef(const float* __restrict__ ztab, QsoCoef c, float4* __restrict__ tab,
+                                                  unsigned long long* count) {
   const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i == 0) *count = 0ull;  // of the draw that follows
   if (i >= kZTabN) return;
   const double z = ztab[i];
   double cf[3] = {1.0, 0.0, 0.0};
@@ -375,12 +377,10 @@ __global__ void __launch_bounds__(kQsoBlock) k_qso_draw(QsoDrawArgs a) {
   }
 }
 
-__global__ void k_zero_u64(unsigned long long* p) { *p = 0ull; }
-
 hipError_t launch_qso_draw(const QsoCoef& c, const QsoDrawArgs& a, const float* ztab, float4* tab, hipStream_t st) {
   LYA_TIMED("qso_coef", st,
-            hipLaunchKernelGGL(k_qso_coef, dim3((kZTabN + 255) / 256), dim3(256), 0, st, ztab, c, tab));
-  LYA_TIMED("qso_zero", st, hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(1), 0, st, a.count));
+            hipLaunchKernelGGL(k_qso_coef, dim3((kZTabN + 255) / 256), dim3(256), 0, st, ztab, c, tab,
+                               a.count));
   // kQsoBlock threads x kQsoVpt voxels per block: n^3 / (kQsoBlock kQsoVpt) blocks, a
   // whole number for every supported n (n >= 32), so every wave is full, as
   // the wave-wide ballots need
