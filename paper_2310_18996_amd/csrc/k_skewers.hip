@@ -25,6 +25,8 @@
 // One persistent launch; each wavefront pulls chunks of skewers from an
 // atomic queue and owns a skewer at a time (its small-scale FFT lives in the
 // wave's slice of LDS, so no block-wide barrier is needed per skewer).
+#include <algorithm>
+
 #include "lya_internal.h"
 #include "lya_wavefft.h"
 
@@ -521,12 +523,20 @@ void launch_skewer_kernel(const SkewerArgs& a, int u, dim3 grid, hipStream_t st)
   }
 }
 
-hipError_t launch_skewers(const SkewerArgs& a, hipStream_t st) {
+hipError_t launch_skewers(SkewerArgs a, hipStream_t st) {
   int64_t blocks = static_cast<int64_t>(device_cus()) * (a.blocks_per_cu > 0 ? a.blocks_per_cu : 4);
+  // no more skewers per pull than leave every wave of the grid one: 500
+  // skewers of 256 pixels in pulls of 4 ran on 125 waves, four in a row each
+  // (39.5 us; one per wave 18.6 us); from 4 skewers per wave up the tuned pull stays
+  a.chunk = static_cast<int>(std::min<int64_t>(a.chunk, std::max<int64_t>(1, a.n_sk / (blocks * kSkWaves))));
   const int64_t nchunks = (a.n_sk + a.chunk - 1) / a.chunk;
   if (blocks * kSkWaves > nchunks) blocks = (nchunks + kSkWaves - 1) / kSkWaves;
   if (blocks < 1) blocks = 1;
-  const int u = a.unroll == 1 || a.unroll == 4 ? a.unroll : 2;
+  // with at most a skewer per wave the pass is one skewer's latency: the gathers of
+  // four steps of 64 pixels go out together instead of step by step (18.6 ->
+  // 17.4 us for 500 skewers of 256 pixels; every unroll gives the same bits)
+  const bool few = a.n_sk <= blocks * kSkWaves;
+  const int u = few ? 4 : a.unroll == 1 || a.unroll == 4 ? a.unroll : 2;
   const dim3 grid(static_cast<unsigned>(blocks));
   if (a.field_bf16)
     launch_skewer_kernel<true>(a, u, grid, st);

@@ -174,7 +174,7 @@ struct SkewerArgs {
   int unroll;         // pixels per lane per step: 1, 2 or 4 (other values: 2)
 };
 
-hipError_t launch_skewers(const SkewerArgs& a, hipStream_t st);
+hipError_t launch_skewers(SkewerArgs a, hipStream_t st);
 
 // 1D flux power spectrum.
 constexpr int kMaxKBins = 64;
