@@ -123,20 +123,24 @@ __global__ void __launch_bounds__(256) k_amp_table(const double* amp, PkParams p
 // Integrand of the matter correlation function of the smoothed spectrum
 // (section "Quasar generation"): xi(r) = 1/(2 pi^2 r) int_0^kmax P(k)
 // exp(-k^2 s^2) k sin(k r) dk, composite Simpson on k_j = j h, j = 0..m
-// (m even).  f_j holds the Simpson weight times P(k_j) exp(-k_j^2 s^2) k_j;
-// k = 0 carries nothing.
-__global__ void __launch_bounds__(256) k_xi_weights(const double* amp, PkParams p, double s, double h, int m,
-                                                    double* f) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j > m) return;
-  if (j == 0) {
-    f[0] = 0.0;
-    return;
-  }
-  const double k = h * j;
-  const double P = p.k_tab ? pk_tabulated(k, p) : amp[0] * pk_shape(k, p);
-  const double w = (j == m) ? 1.0 : ((j & 1) ? 4.0 : 2.0);
-  f[j] = w * h / 3.0 * P * exp(-(k * s) * (k * s)) * k;
+// (m even).  f_j is the Simpson weight times P(k_j) exp(-k_j^2 s^2) k_j (k = 0
+// carries nothing), written as the sums and differences of the node pairs that
+// k_sine_sum takes (nodes beyond m are 0).
+__global__ void __launch_bounds__(256) k_xi_weights(const double* amp, PkParams p, double s, double h, int m, int na,
+                                                    double* sd) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  const int a = t / kSineB, b = t % kSineB;
+  if (a >= na) return;
+  auto f = [&](int j) {
+    if (j == 0 || j > m) return 0.0;
+    const double k = h * j;
+    const double P = p.k_tab ? pk_tabulated(k, p) : amp[0] * pk_shape(k, p);
+    const double w = (j == m) ? 1.0 : ((j & 1) ? 4.0 : 2.0);
+    return w * h / 3.0 * P * exp(-(k * s) * (k * s)) * k;
+  };
+  const double fp = f(a * kSineJ + kSineB + b), fm = f(a * kSineJ + kSineB - 1 - b);
+  sd[static_cast<size_t>(a) * kSineJ + b] = fp + fm;
+  sd[static_cast<size_t>(a) * kSineJ + kSineB + b] = fp - fm;
 }
 
 // ---- pixel redshift table: z at chi = i * kZTabH ----
@@ -282,8 +286,10 @@ hipError_t launch_xi_weights(const PkParams& p, double s, double h, int m, doubl
               hipLaunchKernelGGL(k_pk_finalize, dim3(1), dim3(256), 0, st, p, partial, kSigmaBlocks, amp,
                                  static_cast<float2*>(nullptr), 0));
   }
+  const int na = sine_shape(m + 1, 1).na;
   LYA_TIMED("xi_weights", st,
-            hipLaunchKernelGGL(k_xi_weights, dim3((m + 256) / 256), dim3(256), 0, st, amp, p, s, h, m, f));
+            hipLaunchKernelGGL(k_xi_weights, dim3((na * kSineB + 255) / 256), dim3(256), 0, st, amp, p, s, h, m, na,
+                               f));
   return hipGetLastError();
 }
 

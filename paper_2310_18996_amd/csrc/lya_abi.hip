@@ -143,7 +143,7 @@ int64_t xi_nodes(double smooth, double rmax) {
 }
 
 struct LnCarve {
-  size_t partial, amp, f, xi, g, total;
+  size_t partial, amp, f, xi, g, part, total;
 };
 
 LnCarve carve_lognormal(int64_t m, int32_t n_r) {
@@ -151,9 +151,10 @@ LnCarve carve_lognormal(int64_t m, int32_t n_r) {
   size_t o = 0;
   c.partial = o; o += align256(sizeof(double) * lya::kSigmaBlocks);
   c.amp = o;     o += align256(sizeof(double));
-  c.f = o;       o += align256(sizeof(double) * static_cast<size_t>(m + 1));
+  c.f = o;       o += align256(sizeof(double) * lya::kSineJ * static_cast<size_t>(lya::sine_shape(m + 1, 1).na));
   c.xi = o;      o += align256(sizeof(double) * static_cast<size_t>(n_r));
-  c.g = o;       o += align256(sizeof(double) * static_cast<size_t>(n_r));
+  c.g = o;       o += align256(sizeof(double) * lya::kSineJ * static_cast<size_t>(lya::sine_shape(n_r, 1).na));
+  c.part = o;    o += align256(sizeof(double) * lya::kSineParts);
   c.total = o;
   return c;
 }
@@ -712,6 +713,7 @@ int lya_lognormal_pk(const lya_pk* pk, double z_box, double z_ref, const lya_cos
   a.xi = xi ? xi : reinterpret_cast<double*>(w + c.xi);
   a.f = reinterpret_cast<double*>(w + c.f);
   a.g = reinterpret_cast<double*>(w + c.g);
+  a.part = reinterpret_cast<double*>(w + c.part);
   a.partial = reinterpret_cast<double*>(w + c.partial);
   a.amp = reinterpret_cast<double*>(w + c.amp);
   hipError_t e = lya::launch_lognormal(pk_params(pk), a, static_cast<hipStream_t>(stream));

@@ -89,8 +89,9 @@ struct PrepArgs {
 };
 hipError_t launch_prep(const PrepArgs& a, hipStream_t st);
 hipError_t launch_zchi_table(double omega_m, float* ztab, hipStream_t st);
-// Simpson-weighted integrand of xi_m (k_j = j h, j = 0..m): sigma8
-// normalisation first for the analytic form (partial: kSigmaBlocks, amp: 1).
+// Simpson-weighted integrand of xi_m (k_j = j h, j = 0..m) in the groups of
+// k_sine_sum: sigma8 normalisation first for the analytic form (partial:
+// kSigmaBlocks, amp: 1).
 hipError_t launch_xi_weights(const PkParams& p, double s, double h, int m, double* partial, double* amp,
                              double* f, hipStream_t st);
 hipError_t launch_twiddles(float2* tw, int ntw, hipStream_t st);
@@ -269,6 +270,17 @@ hipError_t tune_eval_ds(const DsSource& src, char* w, const DsDraw* d, int G, do
                         hipStream_t st);
 
 // Lognormal quasar field (lya_qso.hip).
+// Groups of kSineJ nodes of the transforms' sums (see k_sine_sum), and how a
+// sum of n_nodes nodes at nx points is cut: na groups in segs segments, each
+// writing a partial sum per point (segs nx <= kSineParts, or one segment, which
+// writes the sums themselves).
+constexpr int kSineB = 16, kSineJ = 2 * kSineB;
+constexpr int kSineWaves = 4096;             // waves of a sum, about (four per SIMD)
+constexpr int kSineParts = 64 * kSineWaves;
+struct SineShape {
+  int na, per_seg, segs;
+};
+SineShape sine_shape(int n_nodes, int nx);
 struct LognormalArgs {
   double smooth;   // Gaussian smoothing length of the matter spectrum, Mpc/h
   double h;        // k spacing of the xi quadrature; nodes j = 0..m (m even)
@@ -280,8 +292,9 @@ struct LognormalArgs {
   const double* k;   // device [n_k]
   double* pq;        // device [n_k]
   double* xi;        // device [n_r]
-  double* f;         // workspace [m + 1]
-  double* g;         // workspace [n_r]
+  double* f;         // workspace [sine_shape(m + 1, .).na][kSineJ]: k weights in groups
+  double* g;         // workspace [sine_shape(n_r, .).na][kSineJ]: r weights in groups
+  double* part;      // workspace [kSineParts]
   double* partial;   // workspace [kSigmaBlocks]
   double* amp;       // workspace [1]
 };

@@ -26,102 +26,163 @@ __device__ double block_sum256(double v, double* red) {
   return threadIdx.x == 0 ? red[0] + red[1] + red[2] + red[3] : 0.0;
 }
 
-// Nodes a thread takes between exact sines: the rest come from rotating by
-// the angle of 256 nodes (rounding grows by about an ulp per rotation).
-constexpr int kRotSteps = 32;
-
 }  // namespace
 
-// xi_m at r_b = b dr (one block per r): sum_j f_j sin(k_j r) / (2 pi^2 r),
-// f from launch_xi_weights; r = 0 takes the limit sum_j f_j k_j / (2 pi^2).
-__global__ void __launch_bounds__(256) k_xi_r(const double* __restrict__ f, int m, double h, double dr,
-                                              double* __restrict__ xi) {
-  __shared__ double red[4];
-  const int b = blockIdx.x;
-  const double r = dr * b;
-  double acc = 0.0;
-  if (b == 0) {
-    for (int j = threadIdx.x; j <= m; j += 256) acc += f[j] * (h * j);
-  } else {
-    double sd, cd;
-    sincos(256.0 * h * r, &sd, &cd);
-    for (int j0 = threadIdx.x; j0 <= m; j0 += 256 * kRotSteps) {
-      double sn, cs;
-      sincos(h * j0 * r, &sn, &cs);
-      const int jend = min(j0 + 256 * kRotSteps, m + 1);
-      for (int j = j0; j < jend; j += 256) {
-        acc += f[j] * sn;
-        const double t = sn * cd + cs * sd;
-        cs = cs * cd - sn * sd;
-        sn = t;
-      }
-    }
-  }
-  const double tot = block_sum256(acc, red);
-  if (threadIdx.x == 0) xi[b] = (b == 0 ? tot : tot / r) / (2.0 * M_PI * M_PI);
-}
+// Both transforms are sums over uniform nodes, T(x) = sum_j f_j sin(j h x):
+// xi_m(r) over k_j = j h, P_q(k) over r_i = i dr.  The nodes go in groups of
+// kSineJ = 2 kSineB around a half-integer centre c: with beta = (b + 1/2) h x,
+//   f+ sin(phi + beta) + f- sin(phi - beta)
+//     = sin phi cos beta (f+ + f-) + cos phi sin beta (f+ - f-),  phi = c h x,
+// so a pair of nodes costs two FMAs once cos beta and sin beta, the same in
+// every group, sit in registers (one lane per x), and the sums and differences
+// f+ +- f- (the same for every lane) come as scalar operands: one FP64 FMA per
+// node and x, where a rotation per node takes five.  sin phi and cos phi turn
+// by J h x per group, from an exact sincos every kSineSync groups.  Bound by
+// FP64 FMA issue (4.4e9 nodes x r values, 0.11 ms of FMAs at 40001 r and 1.1e5
+// k nodes): 2.18 -> 0.29 ms.  x = 0 (or below) takes the limit sum_j f_j (j h):
+// sin y -> y / x, cos -> 1.
+// Group a of sd: kSineB sums f+ + f-, then kSineB differences f+ - f-, with
+// f+ = f[J a + B + b], f- = f[J a + B - 1 - b].
+constexpr int kSineSync = 32;
 
-// g_i = Simpson weight (dr/3) ln(1 + b2 xi_i) r_i on r_i = i dr (n_r odd).
-__global__ void __launch_bounds__(256) k_lognormal_g(const double* __restrict__ xi, int n_r, double dr, double b2,
-                                                     double* __restrict__ g) {
+__global__ void __launch_bounds__(256) k_sine_sum(const double* __restrict__ sd, int na, int per_seg, double h,
+                                                  const double* __restrict__ xv, double dx, int nx,
+                                                  double* __restrict__ part) {
+  constexpr int B = kSineB, J = kSineJ;
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n_r) return;
-  const double w = (i == 0 || i == n_r - 1) ? 1.0 : ((i & 1) ? 4.0 : 2.0);
-  g[i] = w * dr / 3.0 * log1p(b2 * xi[i]) * (dr * i);
-}
-
-// P_q(k) = 4 pi / k sum_i g_i sin(k r_i), one block per k; k = 0: 4 pi sum g_i r_i.
-__global__ void __launch_bounds__(256) k_lognormal_pq(const double* __restrict__ g, int n_r, double dr,
-                                                      const double* __restrict__ kv, double* __restrict__ pq) {
-  __shared__ double red[4];
-  const double k = kv[blockIdx.x];
-  double acc = 0.0;
-  if (k <= 0.0) {
-    for (int i = threadIdx.x; i < n_r; i += 256) acc += g[i] * (dr * i);
-  } else {
-    double sd, cd;
-    sincos(256.0 * dr * k, &sd, &cd);
-    for (int i0 = threadIdx.x; i0 < n_r; i0 += 256 * kRotSteps) {
-      double sn, cs;
-      sincos(dr * i0 * k, &sn, &cs);
-      const int iend = min(i0 + 256 * kRotSteps, n_r);
-      for (int i = i0; i < iend; i += 256) {
-        acc += g[i] * sn;
-        const double t = sn * cd + cs * sd;
-        cs = cs * cd - sn * sd;
-        sn = t;
+  const double x = i >= nx ? 0.0 : xv ? xv[i] : dx * i;
+  const bool lim = !(x > 0.0);
+  // a turn by (h x), an exact start at h x / 2 and B - 1 turns; limit: sin -> the
+  // angle over x, cos -> 1, which the turns keep
+  double cb[B], sb[B], st, ct, sr, cr;
+  sincos(0.5 * h * x, &sb[0], &cb[0]);
+  sincos(h * x, &st, &ct);
+  sincos(J * h * x, &sr, &cr);
+  if (lim) {
+    sb[0] = 0.5 * h;
+    st = h;
+    sr = J * h;
+    cb[0] = ct = cr = 1.0;
+  }
+  const double st0 = lim ? 0.0 : st, sr0 = lim ? 0.0 : sr;  // no sin sin term in the limit
+#pragma unroll
+  for (int b = 1; b < B; ++b) {
+    sb[b] = fma(sb[b - 1], ct, cb[b - 1] * st);
+    cb[b] = fma(cb[b - 1], ct, -(sb[b - 1] * st0));
+  }
+  const int a0 = blockIdx.y * per_seg, a1 = min(a0 + per_seg, na);
+  double tot = 0.0;
+  for (int as = a0; as < a1; as += kSineSync) {
+    const double kc = h * (static_cast<double>(J) * as + (B - 0.5));
+    double sp, cp;
+    sincos(kc * x, &sp, &cp);
+    if (lim) {
+      sp = kc;
+      cp = 1.0;
+    }
+    const int ae = min(as + kSineSync, a1);
+    for (int a = as; a < ae; ++a) {
+      const double* __restrict__ f = sd + static_cast<size_t>(a) * J;
+      double u0 = 0.0, u1 = 0.0, v0 = 0.0, v1 = 0.0;
+#pragma unroll
+      for (int b = 0; b < B; b += 2) {
+        u0 = fma(f[b], cb[b], u0);
+        u1 = fma(f[b + 1], cb[b + 1], u1);
+        v0 = fma(f[B + b], sb[b], v0);
+        v1 = fma(f[B + b + 1], sb[b + 1], v1);
       }
+      tot = fma(sp, u0 + u1, fma(cp, v0 + v1, tot));
+      const double t = fma(sp, cr, cp * sr);
+      cp = fma(cp, cr, -(sp * sr0));
+      sp = t;
     }
   }
-  const double tot = block_sum256(acc, red);
-  if (threadIdx.x == 0) pq[blockIdx.x] = 4.0 * M_PI * (k <= 0.0 ? tot : tot / k);
+  if (i < nx) part[static_cast<size_t>(blockIdx.y) * nx + i] = tot;
 }
 
-// Values below 1e-12 of the largest are raised to that floor (one block), so
-// that the result can serve as a tabulated spectrum (ln P interpolation).
-__global__ void __launch_bounds__(256) k_lognormal_floor(double* pq, int n_k) {
-  __shared__ double red[4];
+// Segments of the groups (blockIdx.y): enough for about kSineWaves waves in
+// all (four per SIMD), at least eight groups each.
+SineShape sine_shape(int n_nodes, int nx) {
+  constexpr int kMaxSegs = 64;
+  SineShape s{};
+  s.na = (n_nodes + kSineJ - 1) / kSineJ;
+  const int waves = (nx + 255) / 256 * 4;
+  int segs = std::max(1, std::min(kMaxSegs, kSineWaves / std::max(1, waves)));
+  segs = std::min(segs, (s.na + 7) / 8);
+  s.per_seg = (s.na + segs - 1) / segs;
+  s.segs = (s.na + s.per_seg - 1) / s.per_seg;
+  return s;
+}
+
+__device__ __forceinline__ double sine_total(const double* part, int segs, int nx, int i) {
+  double s = 0.0;
+  for (int k = 0; k < segs; ++k) s += part[static_cast<size_t>(k) * nx + i];
+  return s;
+}
+
+// xi_i = (the sum at r_i = i dr) / (2 pi^2 r_i), then g_i = Simpson weight
+// (dr/3) ln(1 + b2 xi_i) r_i (n_r odd) in the groups of k_sine_sum.  part may
+// be xi itself (one segment): a thread writes only the values it has read.
+__global__ void __launch_bounds__(256) k_lognormal_g(const double* part, int segs, int n_r, double dr, double b2,
+                                                     double* xi, double* __restrict__ sd, int na) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  const int a = t / kSineB, b = t % kSineB;
+  if (a >= na) return;
+  auto g = [&](int i) {
+    if (i >= n_r) return 0.0;
+    const double r = dr * i, tot = sine_total(part, segs, n_r, i);
+    const double x = (i == 0 ? tot : tot / r) / (2.0 * M_PI * M_PI);
+    xi[i] = x;
+    const double w = (i == 0 || i == n_r - 1) ? 1.0 : ((i & 1) ? 4.0 : 2.0);
+    return w * dr / 3.0 * log1p(b2 * x) * r;
+  };
+  const double fp = g(a * kSineJ + kSineB + b), fm = g(a * kSineJ + kSineB - 1 - b);
+  sd[static_cast<size_t>(a) * kSineJ + b] = fp + fm;
+  sd[static_cast<size_t>(a) * kSineJ + kSineB + b] = fp - fm;
+}
+
+// P_q(k) = 4 pi / k times the sum over r (k = 0: 4 pi times the limit), then
+// values below 1e-12 of the largest raised to that floor, so that the result
+// can serve as a tabulated spectrum (ln P interpolation).  One block; part may
+// be pq itself (one segment).
+__global__ void __launch_bounds__(1024) k_lognormal_pq(const double* part, int segs, int n_k,
+                                                       const double* __restrict__ kv, double* pq) {
+  __shared__ double red[16];
   double mx = 0.0;
-  for (int i = threadIdx.x; i < n_k; i += 256) mx = fmax(mx, pq[i]);
+  for (int i = threadIdx.x; i < n_k; i += 1024) {
+    const double k = kv[i], tot = sine_total(part, segs, n_k, i);
+    const double v = 4.0 * M_PI * (k <= 0.0 ? tot : tot / k);
+    pq[i] = v;
+    mx = fmax(mx, v);
+  }
   for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_down(mx, o, 64));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
   __syncthreads();
-  const double fl = 1e-12 * fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  mx = 0.0;
+  for (int w = 0; w < 16; ++w) mx = fmax(mx, red[w]);
+  const double fl = 1e-12 * mx;
   if (fl <= 0.0) return;
-  for (int i = threadIdx.x; i < n_k; i += 256) pq[i] = fmax(pq[i], fl);
+  for (int i = threadIdx.x; i < n_k; i += 1024) pq[i] = fmax(pq[i], fl);  // each thread its own values
 }
 
 hipError_t launch_lognormal(const PkParams& p, const LognormalArgs& a, hipStream_t st) {
   hipError_t e = launch_xi_weights(p, a.smooth, a.h, a.m, a.partial, a.amp, a.f, st);
   if (e != hipSuccess) return e;
-  LYA_TIMED("xi_r", st, hipLaunchKernelGGL(k_xi_r, dim3(a.n_r), dim3(256), 0, st, a.f, a.m, a.h, a.dr, a.xi));
+  const SineShape sx = sine_shape(a.m + 1, a.n_r), sk = sine_shape(a.n_r, a.n_k);
+  double* px = sx.segs == 1 ? a.xi : a.part;  // the caller's array where one segment holds the sums
+  double* pk = sk.segs == 1 ? a.pq : a.part;
+  LYA_TIMED("xi_r", st,
+            hipLaunchKernelGGL(k_sine_sum, dim3((a.n_r + 255) / 256, sx.segs), dim3(256), 0, st, a.f, sx.na,
+                               sx.per_seg, a.h, static_cast<const double*>(nullptr), a.dr, a.n_r, px));
   LYA_TIMED("lognormal_g", st,
-            hipLaunchKernelGGL(k_lognormal_g, dim3((a.n_r + 255) / 256), dim3(256), 0, st, a.xi, a.n_r, a.dr, a.b2,
-                               a.g));
+            hipLaunchKernelGGL(k_lognormal_g, dim3((sk.na * kSineB + 255) / 256), dim3(256), 0, st, px, sx.segs,
+                               a.n_r, a.dr, a.b2, a.xi, a.g, sk.na));
   if (a.n_k > 0) {
+    LYA_TIMED("lognormal_sum", st,
+              hipLaunchKernelGGL(k_sine_sum, dim3((a.n_k + 255) / 256, sk.segs), dim3(256), 0, st, a.g, sk.na,
+                                 sk.per_seg, a.dr, a.k, 0.0, a.n_k, pk));
     LYA_TIMED("lognormal_pq", st,
-              hipLaunchKernelGGL(k_lognormal_pq, dim3(a.n_k), dim3(256), 0, st, a.g, a.n_r, a.dr, a.k, a.pq));
-    LYA_TIMED("lognormal_floor", st, hipLaunchKernelGGL(k_lognormal_floor, dim3(1), dim3(256), 0, st, a.pq, a.n_k));
+              hipLaunchKernelGGL(k_lognormal_pq, dim3(1), dim3(1024), 0, st, pk, sk.segs, a.n_k, a.k, a.pq));
   }
   return hipGetLastError();
 }
