@@ -67,14 +67,13 @@ __device__ __forceinline__ float gelu_grad(float x) {
 __global__ void __launch_bounds__(256) k_emu_init(float* params, float* m, float* v, int n_out, uint64_t seed) {
   const Offs o = param_offsets(n_out);
   const size_t np = n_params(n_out);
-  const int fin[4] = {kIn, kHid, kHid, kHid};
   for (size_t i = blockIdx.x * 256ull + threadIdx.x; i < np; i += static_cast<size_t>(gridDim.x) * 256) {
-    int l = 3;
-    while (l > 0 && i < o.W[l]) --l;
+    const int l = i < o.W[1] ? 0 : i < o.W[2] ? 1 : i < o.W[3] ? 2 : 3;
     float val = 0.0f;
-    if (i < o.b[l]) {  // weight of layer l: He normal, std sqrt(2 / fan_in)
+    if (i < (l == 0 ? o.b[0] : l == 1 ? o.b[1] : l == 2 ? o.b[2] : o.b[3])) {
+      // weight of layer l: He normal, std sqrt(2 / fan_in)
       const float2 z = normal_pair(seed, 3u, static_cast<uint64_t>(i) << 1);
-      val = z.x * sqrtf(2.0f / fin[l]);
+      val = z.x * sqrtf(2.0f / (l == 0 ? kIn : kHid));
     }
     params[i] = val;
     m[i] = 0.0f;
@@ -210,128 +209,16 @@ __global__ void __launch_bounds__(256) k_gemm_f32_ks(int M, int N, int K, const 
   }
 }
 
-typedef short v4i16 __attribute__((ext_vector_type(4)));
-typedef float v4f32 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ unsigned short to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return static_cast<unsigned short>(u >> 16);
-}
-
-// 64x64 output tile per block of 4 waves (2x2, 32x32 each = 2x2 MFMA 16x16
-// tiles); K in tiles of 64 staged through LDS in bfloat16, the next tile's
-// global loads issued before the current tile's MFMAs.  MFMA 16x16x16 operand
-// layout: lane l supplies A rows (l % 16), k = 4 (l / 16) .. +3, and B columns
-// (l % 16), k = 4 (l / 16) .. +3; result element r of lane l is row
-// 4 (l / 16) + r, column l % 16.
-constexpr int kGemmBK = 64;
-
 template <bool TA, bool TB>
-__global__ void __launch_bounds__(256) k_gemm_bf16(int M, int N, int K, const float* __restrict__ A, int lda,
-                                                   const float* __restrict__ B, int ldb, float* C, int ldc,
-                                                   const float* bias, int epi, float* aux, int ldaux) {
-  __shared__ unsigned short As[64][kGemmBK + 8];
-  __shared__ unsigned short Bs[kGemmBK][64 + 8];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int wm = (wv >> 1) * 32, wn = (wv & 1) * 32;
-  v4f32 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = v4f32{0.f, 0.f, 0.f, 0.f};
-  // element e of this thread in a 64 x 64 tile: consecutive threads read
-  // consecutive addresses of the operand's own layout
-  auto a_coord = [&](int e, int& mm, int& kk) {
-    const int idx = tid + 256 * e;
-    mm = TA ? idx % 64 : idx / 64;
-    kk = TA ? idx / 64 : idx % 64;
-  };
-  auto b_coord = [&](int e, int& kk, int& nn) {
-    const int idx = tid + 256 * e;
-    kk = TB ? idx % 64 : idx / 64;
-    nn = TB ? idx / 64 : idx % 64;
-  };
-  float ra[16], rb[16];
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      int mm, kk;
-      a_coord(e, mm, kk);
-      const int m = m0 + mm, k = k0 + kk;
-      ra[e] = (m < M && k < K) ? (TA ? A[static_cast<size_t>(k) * lda + m] : A[static_cast<size_t>(m) * lda + k])
-                               : 0.0f;
-      int kb, nn;
-      b_coord(e, kb, nn);
-      const int kg = k0 + kb, n = n0 + nn;
-      rb[e] = (n < N && kg < K) ? (TB ? B[static_cast<size_t>(n) * ldb + kg] : B[static_cast<size_t>(kg) * ldb + n])
-                                : 0.0f;
-    }
-  };
-  gload(0);
-  for (int k0 = 0; k0 < K; k0 += kGemmBK) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      int mm, kk, kb, nn;
-      a_coord(e, mm, kk);
-      b_coord(e, kb, nn);
-      As[mm][kk] = to_bf16(ra[e]);
-      Bs[kb][nn] = to_bf16(rb[e]);
-    }
-    __syncthreads();
-    if (k0 + kGemmBK < K) gload(k0 + kGemmBK);
-#pragma unroll
-    for (int ks = 0; ks < kGemmBK; ks += 16) {
-      const int kb = ks + 4 * (lane >> 4);
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        v4i16 af;
-        const int r = wm + 16 * i + (lane & 15);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) af[q] = static_cast<short>(As[r][kb + q]);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          v4i16 bfr;
-          const int cidx = wn + 16 * j + (lane & 15);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) bfr[q] = static_cast<short>(Bs[kb + q][cidx]);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af, bfr, acc[i][j], 0, 0, 0);
-        }
-      }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + 16 * i + 4 * (lane >> 4) + r;
-        const int n = n0 + wn + 16 * j + (lane & 15);
-        if (m < M && n < N) {
-          float dummy;
-          C[static_cast<size_t>(m) * ldc + n] = epilogue(epi, acc[i][j][r], m, n, bias, aux, ldaux, dummy);
-        }
-      }
-}
-
-template <bool TA, bool TB>
-hipError_t gemm(bool bf16, int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc,
+hipError_t gemm(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc,
                 const float* bias, int epi, float* aux, int ldaux, hipStream_t st) {
-  if (bf16) {
-    hipLaunchKernelGGL((k_gemm_bf16<TA, TB>), dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, st, M, N, K, A, lda,
-                       B, ldb, C, ldc, bias, epi, aux, ldaux);
+  const int64_t tot = static_cast<int64_t>(M) * N;
+  if (tot <= 65536 && K >= 64) {
+    hipLaunchKernelGGL((k_gemm_f32_ks<TA, TB>), dim3(static_cast<unsigned>((tot + 15) / 16)), dim3(256), 0, st, M, N,
+                       K, A, lda, B, ldb, C, ldc, bias, epi, aux, ldaux);
   } else {
-    const int64_t tot = static_cast<int64_t>(M) * N;
-    if (tot <= 65536 && K >= 64) {
-      hipLaunchKernelGGL((k_gemm_f32_ks<TA, TB>), dim3(static_cast<unsigned>((tot + 15) / 16)), dim3(256), 0, st, M,
-                         N, K, A, lda, B, ldb, C, ldc, bias, epi, aux, ldaux);
-    } else {
-      hipLaunchKernelGGL((k_gemm_f32<TA, TB>), dim3(static_cast<unsigned>((tot + 255) / 256)), dim3(256), 0, st, M,
-                         N, K, A, lda, B, ldb, C, ldc, bias, epi, aux, ldaux);
-    }
+    hipLaunchKernelGGL((k_gemm_f32<TA, TB>), dim3(static_cast<unsigned>((tot + 255) / 256)), dim3(256), 0, st, M, N,
+                       K, A, lda, B, ldb, C, ldc, bias, epi, aux, ldaux);
   }
   return hipGetLastError();
 }
@@ -399,16 +286,440 @@ __global__ void __launch_bounds__(1024) k_colsum(const float* __restrict__ d, in
   if (g == 0 && n < N) db[n] = sp[0][c];
 }
 
-__global__ void __launch_bounds__(256) k_adam(float* p, float* m, float* v, const float* __restrict__ g, size_t np,
-                                              float lr, float b1, float b2, float eps, float bc1, float bc2) {
-  for (size_t i = blockIdx.x * 256ull + threadIdx.x; i < np; i += static_cast<size_t>(gridDim.x) * 256) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
+struct AdamArgs {
+  float *p, *m, *v;
+  float lr, b1, b2, eps, bc1, bc2;
+};
+__device__ __forceinline__ float adam_update(const AdamArgs& a, size_t i, float gi) {
+  const float mi = a.b1 * a.m[i] + (1.0f - a.b1) * gi;
+  const float vi = a.b2 * a.v[i] + (1.0f - a.b2) * gi * gi;
+  a.m[i] = mi;
+  a.v[i] = vi;
+  return a.p[i] -= a.lr * (mi / a.bc1) / (sqrtf(vi / a.bc2) + a.eps);
+}
+
+__global__ void __launch_bounds__(256) k_adam(AdamArgs a, const float* __restrict__ g, size_t np) {
+  for (size_t i = blockIdx.x * 256ull + threadIdx.x; i < np; i += static_cast<size_t>(gridDim.x) * 256)
+    adam_update(a, i, g[i]);
+}
+
+// ---------------------------------------------------------------- bfloat16 training batch in two launches
+// The batch used to take 17 launches (a product, an epilogue or a column sum
+// each, 4-16 us apiece, on 16-64 blocks), a training step 180 us at batch 512
+// for 0.4 GFLOP; now 32 us, bound by the chain of six dependent layers in
+// k_emu_rows.
+// No row of the batch needs another until the weight gradients, so
+// k_emu_rows takes 16 rows through the forward pass, the loss and the backward
+// pass to the inputs of every layer, and k_emu_grads then forms all weight and
+// bias gradients (and, in training, Adam's update of each parameter, which only
+// it touches).  The products, their order of summation and their roundings are
+// those of a chain of 16-deep MFMA steps per output, so the gradients do not
+// depend on how rows and tiles are dealt out.
+typedef short v4i16 __attribute__((ext_vector_type(4)));
+typedef float v4f32 __attribute__((ext_vector_type(4)));
+typedef __bf16 v2bf16 __attribute__((ext_vector_type(2)));
+typedef float v2f32 __attribute__((ext_vector_type(2)));
+
+// round to nearest even (v_cvt_pk_bf16_f32)
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f32{a, b}, v2bf16));
+}
+__device__ __forceinline__ v4i16 bf16x4(float a, float b, float c, float d) {
+  return __builtin_bit_cast(v4i16, make_uint2(pack_bf16(a, b), pack_bf16(c, d)));
+}
+
+constexpr int kRowPad = 16;            // the batch is padded to whole MFMA steps of rows
+constexpr int kRowNT = 512;            // a wave per 32 hidden units
+constexpr int kRowLd = kHid + 8;       // LDS row of bfloat16 activations
+
+// The weights of layers 2-4 as bfloat16 MFMA B operands, forward and
+// transposed: four values (k = 16 s + 4 (lane / 16) + q) of column lane % 16 of
+// tile t at [t][s][lane], so a wave reads an operand as 512 contiguous bytes
+// and 64 registers hold the next product's.  Built by k_emu_pack for a call,
+// kept up to date by Adam's update within a training call.
+constexpr int kPackTile = 16 * 64;                        // uint2 of a 16-step tile
+constexpr int kPackHid = 16 * kPackTile;                  // a hidden layer's
+constexpr int kPackOut = (kMaxOut / 16) * kPackTile;      // the output layer's
+constexpr int kPackTotal = 4 * kPackHid + 2 * kPackOut;
+// start of layer l (1-3), forward or transposed (arithmetic: a table indexed by
+// l would go to scratch)
+__host__ __device__ constexpr int pack_f(int l) { return (l - 1) * 2 * kPackHid; }
+__host__ __device__ constexpr int pack_b(int l) { return pack_f(l) + (l < 3 ? kPackHid : kPackOut); }
+// place of W[m][n] of layer l in shorts
+__device__ __forceinline__ int pack_fwd(int l, int m, int n) {
+  return 4 * (pack_f(l) + ((n >> 4) * 16 + (m >> 4)) * 64 + ((m >> 2) & 3) * 16 + (n & 15)) + (m & 3);
+}
+__device__ __forceinline__ int pack_bwd(int l, int m, int n) {
+  return 4 * (pack_b(l) + ((m >> 4) * (l < 3 ? 16 : kMaxOut / 16) + (n >> 4)) * 64 + ((n >> 2) & 3) * 16 + (m & 15)) +
+         (n & 3);
+}
+
+__global__ void __launch_bounds__(256) k_emu_pack(const float* __restrict__ params, int n_out, uint2* __restrict__ pk) {
+  const Offs o = param_offsets(n_out);
+  const int i = blockIdx.x * 256 + threadIdx.x;  // kPackTotal is a multiple of 256, and so is every part
+  const int l = i < pack_f(2) ? 1 : i < pack_f(3) ? 2 : 3;
+  const bool fwd = i < pack_b(l);
+  const int e = i - (fwd ? pack_f(l) : pack_b(l)), lane = e & 63, steps = l == 3 && !fwd ? kMaxOut / 16 : 16;
+  const int s = (e >> 6) & (steps - 1), t = (e >> 6) / steps, N = l < 3 ? kHid : n_out;
+  const float* __restrict__ W = params + (l == 1 ? o.W[1] : l == 2 ? o.W[2] : o.W[3]);
+  const int kk = 16 * s + 4 * (lane >> 4), c = 16 * t + (lane & 15);
+  float v[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int m = fwd ? kk + q : c, n = fwd ? c : kk + q;
+    v[q] = n < N ? W[m * N + n] : 0.0f;
   }
+  pk[i] = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+}
+
+struct RowArgs {
+  const EmuHeader* h;
+  const float* params;
+  const uint2* pk;         // packed weights
+  int n_out, B, Bp;        // Bp: B rounded up to whole blocks
+  const float *x0, *tgt;   // standardised batch, or (null):
+  const float *x, *y;      // raw rows (first + i) mod n
+  int64_t n, first;
+  float* x0s;              // the standardised inputs [B][4] of raw rows
+  unsigned short* hT[3];   // hidden activations, bfloat16, [unit][Bp]
+  unsigned short* dT[4];   // dZ2, dZ3 (entries 1, 2) and dY (3), bfloat16, [unit][Bp]
+  float* d[4];             // dZ1..dZ3, dY, FP32 [B][units]
+  double* lpart;           // squared misfit per block
+};
+
+// MFMA 16x16x16 operands: lane l supplies A row l % 16 and B column l % 16 at
+// k = 4 (l / 16) .. + 3; result element r of lane l is row 4 (l / 16) + r,
+// column l % 16.  A block takes 4 R rows of the batch, R = 1, 2 or 4: row
+// R g + r is the product's row 4 g + r, r < R, and the products' other rows are
+// not used (a row depends on its own A row alone).  Fewer rows a block leave
+// matrix work idle but spread the erfc and exp of the activations over more
+// CUs, and those cost more: at batch 512 R = 4 (32 blocks) takes 22.9 us,
+// R = 1 (128 blocks) 18.8 us; see row_shape for the rule.  Wave w of a block owns the hidden units 32 w .. 32 w + 31
+// (two column tiles) of every layer, so pre-activations stay in its registers
+// until the backward pass needs them.  The weights of the next product are
+// read before the barrier that the current one ends with.
+template <int R>
+__global__ void __launch_bounds__(kRowNT) k_emu_rows(RowArgs a) {
+  constexpr int kRowT = 4 * R;
+  __shared__ unsigned short sact[2][kRowT][kRowLd];
+  __shared__ float sx[kRowT][kIn], st[kRowT][kMaxOut], smask[kMaxOut];
+  __shared__ double sl[4];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6, c = lane & 15, kq = 4 * (lane >> 4), rq = R * (lane >> 4);
+  const int ar = R * (c >> 2) + ((c & 3) < R ? c & 3 : R - 1);  // the batch row of this lane's A row
+  const int n_out = a.n_out, row0 = blockIdx.x * kRowT;
+  const Offs o = param_offsets(n_out);
+  const float* __restrict__ P = a.params;
+  const int col = 32 * wv + c;   // and col + 16
+  uint2 w[2][16];   // B operands of this wave's two tiles
+  auto load = [&](size_t at) {
+    const uint2* __restrict__ f = a.pk + at + 2 * wv * 16 * 64 + lane;
+#pragma unroll
+    for (int s = 0; s < 16; ++s)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) w[j][s] = f[(j * 16 + s) * 64];
+  };
+  v4f32 acc[2];
+  auto product = [&](const unsigned short (*act)[kRowLd]) {
+    acc[0] = acc[1] = v4f32{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      const v4i16 af = __builtin_bit_cast(v4i16, *reinterpret_cast<const uint2*>(&act[ar][16 * s + kq]));
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af, __builtin_bit_cast(v4i16, w[j][s]), acc[j], 0, 0, 0);
+    }
+  };
+  // this lane's R rows of unit u: bfloat16 into LDS (act) and [unit][Bp] (gT)
+  auto put = [&](const float* v, int u, unsigned short (*act)[kRowLd], unsigned short* gT) {
+    unsigned short b[4];
+#pragma unroll
+    for (int r = 0; r < R; r += 2) {
+      const uint32_t p2 = pack_bf16(v[r], v[r + 1 < R ? r + 1 : r]);
+      b[r] = static_cast<unsigned short>(p2);
+      b[r + 1] = static_cast<unsigned short>(p2 >> 16);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) act[rq + r][u] = b[r];
+    if (gT) {
+      unsigned short* g = gT + static_cast<size_t>(u) * a.Bp + row0 + rq;
+      if constexpr (R == 4) *reinterpret_cast<uint2*>(g) = make_uint2(b[0] | b[1] << 16, b[2] | b[3] << 16);
+      else if constexpr (R == 2) *reinterpret_cast<uint32_t*>(g) = b[0] | b[1] << 16;
+      else *g = b[0];
+    }
+  };
+  load(pack_f(1));
+  // the rows' inputs and targets (rows past the batch: 0)
+  if (t < kRowT * kIn) {
+    const int i = t / kIn, k = t % kIn, row = row0 + i;
+    float v = 0.0f;
+    if (row < a.B) {
+      if (a.x0) {
+        v = a.x0[row * kIn + k];
+      } else {
+        v = scale_input(a.h, k, a.x[((a.first + row) % a.n) * kIn + k]);
+        a.x0s[row * kIn + k] = v;
+      }
+    }
+    sx[i][k] = v;
+  }
+  if (t < kMaxOut) smask[t] = a.h->out_mask[t];
+#pragma unroll
+  for (int e = t; e < kRowT * kMaxOut; e += kRowNT) {
+    const int i = e / kMaxOut, k = e % kMaxOut, row = row0 + i;
+    float v = 0.0f;
+    if (row < a.B && k < n_out) {
+      if (a.x0) {
+        v = a.tgt[static_cast<size_t>(row) * n_out + k];
+      } else {
+        v = a.y[((a.first + row) % a.n) * n_out + k];
+        if (k >= a.h->log_from) v = logf(v);
+        v = (v - a.h->out_mean[k]) / a.h->out_std[k];
+        v = (a.h->out_mask[k] > 0.0f && isfinite(v)) ? v : 0.0f;
+      }
+    }
+    st[i][k] = v;
+  }
+  __syncthreads();
+  float z[3][2][R], v[2][R];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {  // layer 1 (FP32)
+    const int u = col + 16 * j;
+    const float b = P[o.b[0] + u];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      float s1 = 0.0f;
+#pragma unroll
+      for (int k = 0; k < kIn; ++k) s1 = fmaf(sx[rq + r][k], P[o.W[0] + k * kHid + u], s1);
+      z[0][j][r] = s1 + b;
+      v[j][r] = gelu(z[0][j][r]);
+    }
+    put(v[j], u, sact[0], a.hT[0]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int l = 1; l < 3; ++l) {
+    product(sact[(l - 1) & 1]);
+    if (l == 1) load(pack_f(2));
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const float b = P[o.b[l] + col + 16 * j];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        z[l][j][r] = acc[j][r] + b;
+        v[j][r] = gelu(z[l][j][r]);
+      }
+      put(v[j], col + 16 * j, sact[l & 1], a.hT[l]);
+    }
+    __syncthreads();
+  }
+  load(pack_b(2));
+  // output layer (waves 0-3, 16 columns each) and loss: h3 in sact[0]
+  if (wv < 4) {
+    const int u = 16 * wv + c;
+    v4f32 y = {0.f, 0.f, 0.f, 0.f};
+    if (16 * wv < n_out) {
+      const uint2* __restrict__ f = a.pk + pack_f(3) + wv * 16 * 64 + lane;
+      uint2 wo[16];
+#pragma unroll
+      for (int s = 0; s < 16; ++s) wo[s] = f[s * 64];
+#pragma unroll
+      for (int s = 0; s < 16; ++s) {
+        const v4i16 af = __builtin_bit_cast(v4i16, *reinterpret_cast<const uint2*>(&sact[0][ar][16 * s + kq]));
+        y = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af, __builtin_bit_cast(v4i16, wo[s]), y, 0, 0, 0);
+      }
+    }
+    float neff = 0.0f;
+    for (int k = 0; k < n_out; ++k) neff += smask[k];
+    const float scale = 2.0f / (static_cast<float>(a.B) * (neff > 0.0f ? neff : 1.0f));
+    const float b = u < n_out ? P[o.b[3] + u] : 0.0f;
+    double lsum = 0.0;
+    float dy[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int row = row0 + rq + r;
+      dy[r] = 0.0f;
+      if (u < n_out && row < a.B) {
+        const float yv = y[r] + b;
+        const float d = (yv - st[rq + r][u]) * smask[u];
+        dy[r] = scale * d;
+        lsum += static_cast<double>(d) * d;
+        a.d[3][static_cast<size_t>(row) * n_out + u] = dy[r];
+      }
+    }
+    // sact[1] still holds h2, which no wave reads any more
+    put(dy, u, sact[1], u < n_out ? a.dT[3] : nullptr);
+    for (int k = 32; k >= 1; k >>= 1) lsum += __shfl_xor(lsum, k);
+    if (lane == 0) sl[wv] = lsum;
+  }
+  __syncthreads();
+  if (t == 0) a.lpart[blockIdx.x] = sl[0] + sl[1] + sl[2] + sl[3];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {  // dZ3 = (dY W4^T) gelu'(Z3)
+    v4f32 e = {0.f, 0.f, 0.f, 0.f};
+    const uint2* __restrict__ f = a.pk + pack_b(3) + (2 * wv + j) * (kMaxOut / 16) * 64 + lane;
+#pragma unroll
+    for (int s = 0; s < kMaxOut / 16; ++s) {
+      if (16 * s >= n_out) break;
+      const v4i16 af = __builtin_bit_cast(v4i16, *reinterpret_cast<const uint2*>(&sact[1][ar][16 * s + kq]));
+      e = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af, __builtin_bit_cast(v4i16, f[s * 64]), e, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[j][r] = e[r] * gelu_grad(z[2][j][r]);
+    put(v[j], col + 16 * j, sact[0], a.dT[2]);
+  }
+#pragma unroll
+  for (int l = 2; l >= 0; --l) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (row0 + rq + r < a.B) a.d[l][static_cast<size_t>(row0 + rq + r) * kHid + col + 16 * j] = v[j][r];
+    if (l == 0) break;
+    __syncthreads();
+    product(sact[l & 1]);
+    if (l == 2) load(pack_b(1));
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[j][r] = acc[j][r] * gelu_grad(z[l - 1][j][r]);
+      if (l == 2) put(v[j], col + 16 * j, sact[1], a.dT[1]);
+    }
+  }
+}
+
+struct GradArgs {
+  const EmuHeader* h;
+  int n_out, B, Bp, nparts;
+  const float* x0;
+  const unsigned short* hT[3];
+  const unsigned short* dT[4];
+  const float* d[4];
+  const double* lpart;
+  float* grad;   // gradients out, or
+  AdamArgs adam; // (ADAM) the parameters updated in place
+  unsigned short* pk;  // (ADAM) the packed weights, kept up to date
+  float* loss;   // or null
+};
+
+// Grid of k_emu_grads: 16x16 tiles of the weight gradients of layers 2, 3, 4 (a
+// wave each), then 16 columns a block of the bias gradients (with layer 1's
+// weights), then one block for the loss.
+struct GradGrid {
+  int tiles4, tile_blocks, cols4, blocks;
+};
+__host__ __device__ inline GradGrid grad_grid(int n_out) {
+  GradGrid g;
+  g.tiles4 = 16 * ((n_out + 15) / 16);
+  g.tile_blocks = (512 + g.tiles4) / 4;
+  g.cols4 = (n_out + 15) / 16;
+  g.blocks = g.tile_blocks + 3 * (kHid / 16) + g.cols4 + 1;
+  return g;
+}
+
+template <bool ADAM>
+__global__ void __launch_bounds__(256) k_emu_grads(GradArgs a) {
+  __shared__ float sp[5][16][17];
+  __shared__ double sl[256];
+  const int t = threadIdx.x, lane = t & 63, n_out = a.n_out;
+  const Offs o = param_offsets(n_out);
+  const GradGrid gg = grad_grid(n_out);
+  auto give = [&](size_t i, float g) {
+    if constexpr (ADAM) return adam_update(a.adam, i, g);
+    else return a.grad[i] = g;
+  };
+  int b = blockIdx.x;
+  if (b < gg.tile_blocks) {
+    // dW = H^T dZ over the batch, 16 rows per MFMA step in order; both operands
+    // lie [unit][row], four consecutive rows per lane
+    const int tile = 4 * b + (t >> 6), c = lane & 15, kq = 4 * (lane >> 4);
+    const int l = tile < 256 ? 1 : tile < 512 ? 2 : 3, u = tile & 255;
+    const int mt = l < 3 ? u >> 4 : u % 16, nt = l < 3 ? u & 15 : u / 16;
+    const int N = l < 3 ? kHid : n_out, n = 16 * nt + c;
+    // (arrays of the argument indexed by constants: by l they would go to scratch)
+    const unsigned short* __restrict__ A =
+        (l == 1 ? a.hT[0] : l == 2 ? a.hT[1] : a.hT[2]) + static_cast<size_t>(16 * mt + c) * a.Bp + kq;
+    const unsigned short* __restrict__ D =
+        (l == 1 ? a.dT[1] : l == 2 ? a.dT[2] : a.dT[3]) + static_cast<size_t>(n < N ? n : 0) * a.Bp + kq;
+    const size_t wo = l == 1 ? o.W[1] : l == 2 ? o.W[2] : o.W[3];
+    v4f32 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 16
+    for (int k = 0; k < a.Bp; k += 16) {
+      const uint2 av = *reinterpret_cast<const uint2*>(A + k);
+      const uint2 dv = *reinterpret_cast<const uint2*>(D + k);
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(v4i16, av), __builtin_bit_cast(v4i16, dv),
+                                                      acc, 0, 0, 0);
+    }
+    if (n < N) {
+      float p[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) p[r] = give(wo + static_cast<size_t>(16 * mt + kq + r) * N + n, acc[r]);
+      if constexpr (ADAM) {
+        const uint2 u = make_uint2(pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]));
+        const int m = 16 * mt + kq;
+        *reinterpret_cast<uint2*>(a.pk + pack_fwd(l, m, n)) = u;
+        a.pk[pack_bwd(l, m, n)] = static_cast<unsigned short>(u.x);
+        a.pk[pack_bwd(l, m + 1, n)] = static_cast<unsigned short>(u.x >> 16);
+        a.pk[pack_bwd(l, m + 2, n)] = static_cast<unsigned short>(u.y);
+        a.pk[pack_bwd(l, m + 3, n)] = static_cast<unsigned short>(u.y >> 16);
+      }
+    }
+    return;
+  }
+  b -= gg.tile_blocks;
+  const int nb = kHid / 16;
+  if (b < 3 * nb + gg.cols4) {
+    // column sums: sixteen row groups (rows g, g + 16, ...) in order, then the
+    // groups in a fixed tree; layer 1's weights alike (below 64 rows in one chain)
+    const int l = b < 3 * nb ? b / nb : 3, N = l < 3 ? kHid : n_out;
+    const int c = t & 15, g = t >> 4, n = 16 * (l < 3 ? b % nb : b - 3 * nb) + c;
+    const float* __restrict__ d = l == 0 ? a.d[0] : l == 1 ? a.d[1] : l == 2 ? a.d[2] : a.d[3];
+    const size_t bo = l == 0 ? o.b[0] : l == 1 ? o.b[1] : l == 2 ? o.b[2] : o.b[3];
+    float s[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+    if (n < N) {
+      if (l == 0) {
+#pragma unroll 8
+        for (int m = g; m < a.B; m += 16) {
+          const float dv = d[static_cast<size_t>(m) * kHid + n];
+          s[4] += dv;
+#pragma unroll
+          for (int i = 0; i < kIn; ++i) s[i] = fmaf(a.x0[m * kIn + i], dv, s[i]);
+        }
+        if (a.B < 64 && g < kIn) {
+          float acc = 0.0f;
+          for (int m = 0; m < a.B; ++m) acc = fmaf(a.x0[m * kIn + g], d[static_cast<size_t>(m) * kHid + n], acc);
+          give(o.W[0] + static_cast<size_t>(g) * kHid + n, acc);
+        }
+      } else {
+#pragma unroll 16
+        for (int m = g; m < a.B; m += 16) s[4] += d[static_cast<size_t>(m) * N + n];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 5; ++i) sp[i][g][c] = s[i];
+    __syncthreads();
+    for (int w = 8; w > 0; w >>= 1) {
+      if (g < w)
+#pragma unroll
+        for (int i = 0; i < 5; ++i) sp[i][g][c] += sp[i][g + w][c];
+      __syncthreads();
+    }
+    if (g == 0 && n < N) {
+      give(bo + n, sp[4][0][c]);
+      if (l == 0 && a.B >= 64)
+#pragma unroll
+        for (int i = 0; i < kIn; ++i) give(o.W[0] + static_cast<size_t>(i) * kHid + n, sp[i][0][c]);
+    }
+    return;
+  }
+  double l = 0.0;
+  for (int i = t; i < a.nparts; i += 256) l += a.lpart[i];
+  sl[t] = l;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (t < w) sl[t] += sl[t + w];
+    __syncthreads();
+  }
+  if (t == 0 && a.loss) a.loss[0] = static_cast<float>(sl[0] / (static_cast<double>(a.B) * emu_neff(a.h)));
 }
 
 // ---------------------------------------------------------------- small-batch FP32 forward (prediction)
@@ -491,19 +802,64 @@ static TrainBufs carve_train(char* w, int B, int n_out) {
   return t;
 }
 
-// Forward and backward of one batch (x0, tgt already standardised); gradients
+// Buffers of the bfloat16 path in the same workspace.
+struct Bf16Bufs {
+  float *x0s, *d[4];
+  unsigned short *hT[3], *dT[4];
+  double* lpart;
+  uint2* pk;
+  int Bp;
+  size_t total;
+};
+
+static Bf16Bufs carve_bf16(char* w, int B, int n_out) {
+  Bf16Bufs t{};
+  t.Bp = (B + kRowPad - 1) / kRowPad * kRowPad;
+  size_t o = 0;
+  auto take = [&](size_t bytes) {
+    char* p = w ? w + o : nullptr;
+    o += al(bytes);
+    return p;
+  };
+  t.lpart = reinterpret_cast<double*>(take(sizeof(double) * (t.Bp / 4)));
+  t.pk = reinterpret_cast<uint2*>(take(sizeof(uint2) * kPackTotal));
+  t.x0s = reinterpret_cast<float*>(take(sizeof(float) * kIn * B));
+  for (int l = 0; l < 4; ++l) {
+    const size_t units = l < 3 ? kHid : n_out;
+    t.d[l] = reinterpret_cast<float*>(take(sizeof(float) * units * B));
+    if (l > 0) t.dT[l] = reinterpret_cast<unsigned short*>(take(sizeof(unsigned short) * units * t.Bp));
+    if (l < 3) t.hT[l] = reinterpret_cast<unsigned short*>(take(sizeof(unsigned short) * units * t.Bp));
+  }
+  t.total = o;
+  return t;
+}
+
+// Rows per block of k_emu_rows (4 R): as few as leave no more blocks than CUs
+// (a training step with R = 1, 2, 4: batch 1024 42, 44, 47 us; 2048 67, 61, 64
+// us; 4096 122, 110, 95 us).
+static int row_shape(int B) {
+  const int blocks = (B + 3) / 4, cus = device_cus();
+  return blocks <= cus ? 1 : blocks <= 2 * cus ? 2 : 4;
+}
+
+static size_t train_bytes(int B, int n_out) {
+  const size_t a = carve_train(nullptr, B, n_out).total, b = carve_bf16(nullptr, B, n_out).total;
+  return a > b ? a : b;
+}
+
+// FP32 forward and backward of one batch (x0, tgt already standardised); gradients
 // into t.grad, loss into t.loss.
-static hipError_t emu_fwd_bwd(const EmuHeader* h_dev, const float* params, int n_out, int B, bool bf16,
+static hipError_t emu_fwd_bwd(const EmuHeader* h_dev, const float* params, int n_out, int B,
                               const TrainBufs& t, hipStream_t st) {
   const Offs o = param_offsets(n_out);
   hipError_t e;
   // forward
-  if ((e = gemm<false, false>(false, B, kHid, kIn, t.x0, kIn, params + o.W[0], kHid, t.hh[0], kHid, params + o.b[0],
+  if ((e = gemm<false, false>(B, kHid, kIn, t.x0, kIn, params + o.W[0], kHid, t.hh[0], kHid, params + o.b[0],
                               EPI_BIAS_GELU, t.z[0], kHid, st)) != hipSuccess) return e;
   for (int l = 1; l < 3; ++l)
-    if ((e = gemm<false, false>(bf16, B, kHid, kHid, t.hh[l - 1], kHid, params + o.W[l], kHid, t.hh[l], kHid,
+    if ((e = gemm<false, false>(B, kHid, kHid, t.hh[l - 1], kHid, params + o.W[l], kHid, t.hh[l], kHid,
                                 params + o.b[l], EPI_BIAS_GELU, t.z[l], kHid, st)) != hipSuccess) return e;
-  if ((e = gemm<false, false>(bf16, B, n_out, kHid, t.hh[2], kHid, params + o.W[3], n_out, t.y, n_out,
+  if ((e = gemm<false, false>(B, n_out, kHid, t.hh[2], kHid, params + o.W[3], n_out, t.y, n_out,
                               params + o.b[3], EPI_BIAS, nullptr, 0, st)) != hipSuccess) return e;
   {
     const int nparts = (B * n_out + 255) / 256;
@@ -511,22 +867,86 @@ static hipError_t emu_fwd_bwd(const EmuHeader* h_dev, const float* params, int n
     hipLaunchKernelGGL(k_emu_loss, dim3(1), dim3(256), 0, st, t.lpart, nparts, B, h_dev, t.loss);
   }
   // backward: output layer
-  if ((e = gemm<true, false>(bf16, kHid, n_out, B, t.hh[2], kHid, t.dy, n_out, t.grad + o.W[3], n_out, nullptr,
+  if ((e = gemm<true, false>(kHid, n_out, B, t.hh[2], kHid, t.dy, n_out, t.grad + o.W[3], n_out, nullptr,
                              EPI_STORE, nullptr, 0, st)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_colsum, dim3((n_out + 63) / 64), dim3(1024), 0, st, t.dy, B, n_out, t.grad + o.b[3]);
   // dZ3 = (dY W4^T) * gelu'(Z3)
-  if ((e = gemm<false, true>(bf16, B, kHid, n_out, t.dy, n_out, params + o.W[3], n_out, t.dz[2], kHid, nullptr,
+  if ((e = gemm<false, true>(B, kHid, n_out, t.dy, n_out, params + o.W[3], n_out, t.dz[2], kHid, nullptr,
                              EPI_GELU_GRAD, t.z[2], kHid, st)) != hipSuccess) return e;
   for (int l = 2; l >= 1; --l) {
-    if ((e = gemm<true, false>(bf16, kHid, kHid, B, t.hh[l - 1], kHid, t.dz[l], kHid, t.grad + o.W[l], kHid, nullptr,
+    if ((e = gemm<true, false>(kHid, kHid, B, t.hh[l - 1], kHid, t.dz[l], kHid, t.grad + o.W[l], kHid, nullptr,
                                EPI_STORE, nullptr, 0, st)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_colsum, dim3(kHid / 64), dim3(1024), 0, st, t.dz[l], B, kHid, t.grad + o.b[l]);
-    if ((e = gemm<false, true>(bf16, B, kHid, kHid, t.dz[l], kHid, params + o.W[l], kHid, t.dz[l - 1], kHid, nullptr,
+    if ((e = gemm<false, true>(B, kHid, kHid, t.dz[l], kHid, params + o.W[l], kHid, t.dz[l - 1], kHid, nullptr,
                                EPI_GELU_GRAD, t.z[l - 1], kHid, st)) != hipSuccess) return e;
   }
-  if ((e = gemm<true, false>(false, kIn, kHid, B, t.x0, kIn, t.dz[0], kHid, t.grad + o.W[0], kHid, nullptr,
+  if ((e = gemm<true, false>(kIn, kHid, B, t.x0, kIn, t.dz[0], kHid, t.grad + o.W[0], kHid, nullptr,
                              EPI_STORE, nullptr, 0, st)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_colsum, dim3(kHid / 64), dim3(1024), 0, st, t.dz[0], B, kHid, t.grad + o.b[0]);
+  return hipGetLastError();
+}
+
+// The packed weights of the bfloat16 path, from the parameters.
+static hipError_t emu_pack(const float* params, int n_out, int B, char* w, hipStream_t st) {
+  hipLaunchKernelGGL(k_emu_pack, dim3(kPackTotal / 256), dim3(256), 0, st, params, n_out,
+                     carve_bf16(w, B, n_out).pk);
+  return hipGetLastError();
+}
+
+// The same in bfloat16 MFMA products (k_emu_rows, k_emu_grads): the batch is
+// (x0, tgt), or with x0 null the raw rows (first + i) mod n of (x, y).  Adam's
+// update of the parameters where adam is given, else gradients into grad.
+static hipError_t emu_batch_bf16(const EmuHeader* h_dev, const float* params, int n_out, int B, char* w,
+                                 const float* x0, const float* tgt, const float* x, const float* y, int64_t n,
+                                 int64_t first, float* grad, const AdamArgs* adam, float* loss, hipStream_t st) {
+  const Bf16Bufs t = carve_bf16(w, B, n_out);
+  RowArgs r{};
+  r.h = h_dev;
+  r.params = params;
+  r.pk = t.pk;
+  r.n_out = n_out;
+  r.B = B;
+  r.Bp = t.Bp;
+  r.x0 = x0;
+  r.tgt = tgt;
+  r.x = x;
+  r.y = y;
+  r.n = n;
+  r.first = first;
+  r.x0s = t.x0s;
+  r.lpart = t.lpart;
+  GradArgs g{};
+  g.h = h_dev;
+  g.n_out = n_out;
+  g.B = B;
+  g.Bp = t.Bp;
+  const int R = row_shape(B);
+  const dim3 rows(t.Bp / (4 * R));
+  g.nparts = t.Bp / (4 * R);
+  g.x0 = x0 ? x0 : t.x0s;
+  g.lpart = t.lpart;
+  g.grad = grad;
+  g.pk = reinterpret_cast<unsigned short*>(t.pk);
+  if (adam) g.adam = *adam;
+  g.loss = loss;
+  for (int l = 0; l < 4; ++l) {
+    if (l < 3) g.hT[l] = r.hT[l] = t.hT[l];
+    g.dT[l] = r.dT[l] = t.dT[l];
+    g.d[l] = r.d[l] = t.d[l];
+  }
+  if (R == 1)
+    hipLaunchKernelGGL(k_emu_rows<1>, rows, dim3(kRowNT), 0, st, r);
+  else if (R == 2)
+    hipLaunchKernelGGL(k_emu_rows<2>, rows, dim3(kRowNT), 0, st, r);
+  else
+    hipLaunchKernelGGL(k_emu_rows<4>, rows, dim3(kRowNT), 0, st, r);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const dim3 grid(grad_grid(n_out).blocks);
+  if (adam)
+    hipLaunchKernelGGL(k_emu_grads<true>, grid, dim3(256), 0, st, g);
+  else
+    hipLaunchKernelGGL(k_emu_grads<false>, grid, dim3(256), 0, st, g);
   return hipGetLastError();
 }
 
@@ -904,7 +1324,7 @@ int lya_emulator_init(void* emu, int32_t n_out, int32_t log_from, uint64_t seed,
 
 size_t lya_emulator_train_workspace_size(int32_t batch, int32_t n_out) {
   if (batch < 1 || n_out < 1 || n_out > lya::kMaxOut) return 0;
-  return lya::carve_train(nullptr, batch, n_out).total;
+  return lya::train_bytes(batch, n_out);
 }
 
 int lya_emulator_set_scaling(void* emu, const float* y, int64_t n, void* stream) {
@@ -929,13 +1349,20 @@ int lya_emulator_loss_grad(const void* emu, const float* x0, const float* t, int
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return efail(LYA_EHIP, hipGetErrorString(e));
   lya::TrainBufs tb = lya::carve_train(static_cast<char*>(work), batch, h.n_out);
-  if (!work || work_bytes < tb.total) return efail(LYA_EWORKSPACE, "workspace too small for the emulator batch");
+  if (!work || work_bytes < lya::train_bytes(batch, h.n_out))
+    return efail(LYA_EWORKSPACE, "workspace too small for the emulator batch");
+  if (use_bf16) {
+    e = lya::emu_pack(lya::emu_params(emu), h.n_out, batch, static_cast<char*>(work), st);
+    if (e == hipSuccess)
+      e = lya::emu_batch_bf16(static_cast<const lya::EmuHeader*>(emu), lya::emu_params(emu), h.n_out, batch,
+                              static_cast<char*>(work), x0, t, nullptr, nullptr, 0, 0, grad, nullptr, loss, st);
+    return e == hipSuccess ? LYA_OK : efail(LYA_EHIP, hipGetErrorString(e));
+  }
   const size_t np = lya::n_params(h.n_out);
   e = hipMemcpyAsync(tb.x0, x0, sizeof(float) * batch * lya::kIn, hipMemcpyDeviceToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync(tb.tgt, t, sizeof(float) * batch * h.n_out, hipMemcpyDeviceToDevice, st);
   if (e == hipSuccess)
-    e = lya::emu_fwd_bwd(static_cast<const lya::EmuHeader*>(emu), lya::emu_params(emu), h.n_out, batch, use_bf16 != 0,
-                         tb, st);
+    e = lya::emu_fwd_bwd(static_cast<const lya::EmuHeader*>(emu), lya::emu_params(emu), h.n_out, batch, tb, st);
   if (e == hipSuccess) e = hipMemcpyAsync(grad, tb.grad, sizeof(float) * np, hipMemcpyDeviceToDevice, st);
   if (e == hipSuccess && loss) e = hipMemcpyAsync(loss, tb.loss, sizeof(float), hipMemcpyDeviceToDevice, st);
   return e == hipSuccess ? LYA_OK : efail(LYA_EHIP, hipGetErrorString(e));
@@ -951,26 +1378,39 @@ int lya_emulator_train(void* emu, const float* x, const float* y, int64_t n, int
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return efail(LYA_EHIP, hipGetErrorString(e));
   lya::TrainBufs tb = lya::carve_train(static_cast<char*>(work), batch, h.n_out);
-  if (!work || work_bytes < tb.total) return efail(LYA_EWORKSPACE, "workspace too small for the emulator batch");
+  if (!work || work_bytes < lya::train_bytes(batch, h.n_out))
+    return efail(LYA_EWORKSPACE, "workspace too small for the emulator batch");
   const size_t np = lya::n_params(h.n_out);
   float* p = lya::emu_params(emu);
   const size_t stride = lya::al(np * sizeof(float)) / sizeof(float);
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
   int step = h.step;
-  for (int s = 0; s < steps; ++s) {
-    hipLaunchKernelGGL(lya::k_emu_gather, dim3(64), dim3(256), 0, st, x, y, n, static_cast<int64_t>(step), batch,
-                       static_cast<const lya::EmuHeader*>(emu), tb.x0, tb.tgt);
-    e = lya::emu_fwd_bwd(static_cast<const lya::EmuHeader*>(emu), p, h.n_out, batch, use_bf16 != 0, tb, st);
+  if (use_bf16 && steps > 0) {
+    e = lya::emu_pack(p, h.n_out, batch, static_cast<char*>(work), st);
     if (e != hipSuccess) return efail(LYA_EHIP, hipGetErrorString(e));
-    ++step;
-    const float bc1 = 1.0f - powf(b1, static_cast<float>(step));
-    const float bc2 = 1.0f - powf(b2, static_cast<float>(step));
-    hipLaunchKernelGGL(lya::k_adam, dim3(512), dim3(256), 0, st, p, p + stride, p + 2 * stride, tb.grad, np,
-                       static_cast<float>(lr), b1, b2, eps, bc1, bc2);
-    if (loss_hist) {
-      e = hipMemcpyAsync(loss_hist + s, tb.loss, sizeof(float), hipMemcpyDeviceToDevice, st);
+  }
+  for (int s = 0; s < steps; ++s) {
+    const float bc1 = 1.0f - powf(b1, static_cast<float>(step + 1));
+    const float bc2 = 1.0f - powf(b2, static_cast<float>(step + 1));
+    const lya::AdamArgs adam{p, p + stride, p + 2 * stride, static_cast<float>(lr), b1, b2, eps, bc1, bc2};
+    const lya::EmuHeader* hd = static_cast<const lya::EmuHeader*>(emu);
+    if (use_bf16) {
+      e = lya::emu_batch_bf16(hd, p, h.n_out, batch, static_cast<char*>(work), nullptr, nullptr, x, y, n,
+                              static_cast<int64_t>(step) * batch, nullptr, &adam, loss_hist ? loss_hist + s : nullptr,
+                              st);
       if (e != hipSuccess) return efail(LYA_EHIP, hipGetErrorString(e));
+    } else {
+      hipLaunchKernelGGL(lya::k_emu_gather, dim3(64), dim3(256), 0, st, x, y, n, static_cast<int64_t>(step), batch, hd,
+                         tb.x0, tb.tgt);
+      e = lya::emu_fwd_bwd(hd, p, h.n_out, batch, tb, st);
+      if (e != hipSuccess) return efail(LYA_EHIP, hipGetErrorString(e));
+      hipLaunchKernelGGL(lya::k_adam, dim3(512), dim3(256), 0, st, adam, tb.grad, np);
+      if (loss_hist) {
+        e = hipMemcpyAsync(loss_hist + s, tb.loss, sizeof(float), hipMemcpyDeviceToDevice, st);
+        if (e != hipSuccess) return efail(LYA_EHIP, hipGetErrorString(e));
+      }
     }
+    ++step;
   }
   e = hipMemcpyAsync(reinterpret_cast<char*>(emu) + offsetof(lya::EmuHeader, step), &step, sizeof(step),
                      hipMemcpyHostToDevice, st);
