@@ -67,31 +67,38 @@ enum { kSkTri = 0, kSkWide = 1, kSkGauss = 2 };
 // point c (standard deviation one voxel, section "Gaussian fields along lines
 // of sight"): the weights separate into 7 per axis, exp(-(o - t)^2/2) with
 // t = u - c in [-1/2, 1/2), and the average divides by their product sum.
-// Each z run of 7 voxels is contiguous in memory.
+// The general form, straight from the box: for lines with steps of a third of a
+// cell or more (gauss_geo), whose neighbouring pixels share little; x and y
+// weights where they are needed.
 template <bool B16>
 __device__ __forceinline__ void gauss7_at(const SkewerArgs& a, int64_t px, int64_t py, int64_t pz, int N, size_t NN,
                                           float& d, float& e) {
-  float g[3][7], s[3];
-  int c[3];
   const int64_t p3[3] = {px, py, pz};
+  float t[3];
+  int c[3];
 #pragma unroll
   for (int ax = 0; ax < 3; ++ax) {
     const uint32_t fr = static_cast<uint32_t>(p3[ax]);
     const int up = static_cast<int>(fr >> 31);
     c[ax] = static_cast<int>(((p3[ax] >> 32) + up) & (N - 1));
-    const float t = static_cast<float>(fr) * 2.3283064365386963e-10f - static_cast<float>(up);
-    s[ax] = 0.0f;
+    t[ax] = static_cast<float>(fr) * 2.3283064365386963e-10f - static_cast<float>(up);
+  }
+  auto weight = [](int o, float tt) {
+    const float dd = static_cast<float>(o - 3) - tt;
+    return __expf(-0.5f * dd * dd);
+  };
+  float gz[7], sz = 0.0f, sx = 0.0f, sy = 0.0f;
 #pragma unroll
-    for (int o = 0; o < 7; ++o) {
-      const float dd = static_cast<float>(o - 3) - t;
-      g[ax][o] = __expf(-0.5f * dd * dd);
-      s[ax] += g[ax][o];
-    }
+  for (int o = 0; o < 7; ++o) {
+    gz[o] = weight(o, t[2]);
+    sz += gz[o];
   }
   float ax_ = 0.0f, ay_ = 0.0f;
+#pragma unroll 1
   for (int i = 0; i < 7; ++i) {
     const size_t rx = static_cast<size_t>((c[0] + i - 3) & (N - 1)) * NN;
     float bx = 0.0f, by = 0.0f;
+    sy = 0.0f;
 #pragma unroll
     for (int jy = 0; jy < 7; ++jy) {
       const size_t row = rx + static_cast<size_t>((c[1] + jy - 3) & (N - 1)) * N;
@@ -99,99 +106,243 @@ __device__ __forceinline__ void gauss7_at(const SkewerArgs& a, int64_t px, int64
 #pragma unroll
       for (int k = 0; k < 7; ++k) {
         const float2 f = ld_field<B16>(a, row + ((c[2] + k - 3) & (N - 1)));
-        rx_ += g[2][k] * f.x;
-        ry_ += g[2][k] * f.y;
+        rx_ += gz[k] * f.x;
+        ry_ += gz[k] * f.y;
       }
-      bx += g[1][jy] * rx_;
-      by += g[1][jy] * ry_;
+      const float w = weight(jy, t[1]);
+      sy += w;
+      bx += w * rx_;
+      by += w * ry_;
     }
-    ax_ += g[0][i] * bx;
-    ay_ += g[0][i] * by;
+    const float w = weight(i, t[0]);
+    sx += w;
+    ax_ += w * bx;
+    ay_ += w * by;
   }
-  const float inv = 1.0f / (s[0] * s[1] * s[2]);
+  const float inv = 1.0f / (sx * sy * sz);
   d = ax_ * inv;
   e = ay_ * inv;
 }
 
-// Staged form for 64 consecutive pixels of one skewer (one per lane, valid
-// lanes only): their 7^3 neighbourhoods lie in a bounding box of cells that
-// the wave loads into its LDS slice once (z runs contiguous), then each lane
-// sums its 343 voxels from LDS.  Returns false (nothing done) when the box
-// holds more than kGaussCap cells; the caller then gathers from global memory.
-constexpr int kGaussCap = 1024;
-__device__ __forceinline__ int wave_min(int v) {
-#pragma unroll
-  for (int w = 32; w >= 1; w >>= 1) v = min(v, __shfl_xor(v, w));
-  return v;
+// The Gaussian-kernel average of 64 consecutive pixels on the matrix cores.
+// The lanes of a quad hold four neighbouring pixels (steps below a third of a
+// cell per axis, so their nearest grid points differ by at most one), which
+// share a window of 8 cells in y and z: each pixel's 7 weights go into 8 slots,
+// the unused one 0.  For a plane x, one MFMA 4x4x1 (16 blocks: one per quad)
+// adds, for one z slot, the products of the quad's four z weights with four
+// columns: the two components of two neighbouring y rows; eight of them give
+// the z sums of all four pixels over two rows, which the y and x weights then
+// add up.  A voxel is so read from LDS once per quad and not once per pixel, as
+// single words, and the z sums' 686 multiply-adds per pixel (one fused
+// multiply-add each: K = 1) run at twice the rate of the vector unit.
+// The wave's cells lie in LDS as z runs of 16 (or 32) words, the components
+// apart: at half a run's shift of eight banks, the four columns of all quads
+// read different banks.  Almost always they are 8 planes of 8-12 rows at most,
+// and their loads go to registers while the previous 64 pixels are summed (at
+// two waves per SIMD nothing else hides them), with a plane's address in
+// scalar registers.
+// 35M pixels of 50,000 lines in a 512^3 box: 3.11 ms when each pixel read its
+// 343 voxels from LDS, 1.91 ms now (1.59 ms without delta_S; the same from a 64^3
+// box: bound by vector issue and the latencies two waves per SIMD leave open.
+// Reading a plane ahead took 2.26 against 2.07 ms under the profiler: spills).
+constexpr int kGaussRows = 84;                            // z runs of 16 in a wave's slice (42 of 32)
+constexpr int kGaussEta = 16 * kGaussRows + 8;            // start of the second component
+constexpr int kGaussWords = kGaussEta + 16 * kGaussRows;
+constexpr int kGaussPre = 24;                             // 8 planes x 3 groups of 4 rows
+struct GaussGeo {
+  int m1, m2;        // the quad's window start in y and z, relative to the wave's first cell
+  int sh1, sh2;      // the pixel's shift within it, 0 or 1
+  int c0;            // the pixel's nearest plane x, relative to the wave's first
+  float t[3];        // offset from the pixel's nearest grid point, [-1/2, 1/2)
+  int lo[3];         // the wave's first cell, to be taken modulo N (uniform, as the rest)
+  int nx, ny, zs;    // planes and y rows of the wave; z runs of 2^zs cells
+  bool fast;         // the cells fit the registers and the slice together
+};
+
+template <int CTRL>
+__device__ __forceinline__ int dpp_i32(int v) {
+  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
 }
-__device__ __forceinline__ int wave_max(int v) {
-#pragma unroll
-  for (int w = 32; w >= 1; w >>= 1) v = max(v, __shfl_xor(v, w));
-  return v;
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v) {
+  return __int_as_float(dpp_i32<CTRL>(__float_as_int(v)));
 }
-template <bool B16>
-__device__ __forceinline__ bool gauss7_staged(const SkewerArgs& a, int64_t px, int64_t py, int64_t pz, bool valid,
-                                              int64_t base_x, int64_t base_y, int64_t base_z, int N, size_t NN,
-                                              float2* lds, int lane, float& d, float& e) {
-  const int64_t p3[3] = {px, py, pz};
-  const int64_t b3[3] = {base_x, base_y, base_z};
-  int c[3], lo[3], sz[3];
-  float g[3][7], s[3];
+
+// Pixels j1 .. j1 + 63 of a line of np (those past the end repeat the last
+// one); st: steps below a third of a cell.
+__device__ __forceinline__ GaussGeo gauss_geo(const int64_t (&o)[3], const int32_t (&st)[3], int j1, int np, int lane) {
+  GaussGeo g;
+  const int last = min(63, np - 1 - j1), dj = min(lane, last);
+  int c[3], span[3];
 #pragma unroll
   for (int ax = 0; ax < 3; ++ax) {
-    const uint32_t fr = static_cast<uint32_t>(p3[ax]);
-    const int up = static_cast<int>(fr >> 31);
-    // nearest grid point relative to the chunk's base cell (small integers)
-    c[ax] = static_cast<int>((p3[ax] >> 32) - b3[ax]) + up;
-    const float t = static_cast<float>(fr) * 2.3283064365386963e-10f - static_cast<float>(up);
-    s[ax] = 0.0f;
+    // nearest grid points (floor(u + 1/2)) of the first and the last pixel:
+    // along a straight line the others lie between them
+    constexpr int64_t kHalf = int64_t(1) << 31;
+    const int64_t pf = o[ax] + static_cast<int64_t>(j1) * st[ax] + kHalf, pl = pf + static_cast<int64_t>(last) * st[ax];
+    const int64_t cf = pf >> 32, cl = pl >> 32;
+    const int64_t lo = cf < cl ? cf : cl;
+    span[ax] = static_cast<int>(cf < cl ? cl - cf : cf - cl);   // <= 21
+    g.lo[ax] = static_cast<int>(lo - 3);
+    const int64_t p = (pf - (lo << 32)) + static_cast<int64_t>(dj) * st[ax];
+    c[ax] = static_cast<int>(p >> 32);
+    // p's fraction is that of u + 1/2: t = u - c = fraction - 1/2
+    const uint32_t fr = static_cast<uint32_t>(p) ^ 0x80000000u;
+    g.t[ax] = static_cast<float>(fr) * 2.3283064365386963e-10f - static_cast<float>(fr >> 31);
+  }
+  auto quad_min = [](int v) {
+    v = min(v, dpp_i32<0xB1>(v));    // quad_perm [1, 0, 3, 2]
+    return min(v, dpp_i32<0x4E>(v));  // quad_perm [2, 3, 0, 1]
+  };
+  g.c0 = c[0] + 3;
+  g.m1 = quad_min(c[1]);
+  g.sh1 = c[1] - g.m1;
+  g.m2 = quad_min(c[2]);
+  g.sh2 = c[2] - g.m2;
+  g.nx = span[0] + 7;
+  g.ny = span[1] + 8;
+  g.zs = span[2] + 8 <= 16 ? 4 : 5;
+  g.fast = g.zs == 4 && g.nx <= 8 && g.ny <= 12 && g.nx * g.ny <= kGaussRows;
+  return g;
+}
+
+template <bool B16>
+struct GaussCell {
+  typedef float2 type;
+};
+template <>
+struct GaussCell<true> {
+  typedef uint32_t type;
+};
+__device__ __forceinline__ float2 gauss_cell(float2 v) { return v; }
+__device__ __forceinline__ float2 gauss_cell(uint32_t v) { return unpack_bf16x2(v); }
+
+// All cells of a fast geometry into registers: row group r (4 rows x 16 z, a
+// lane each) of plane p in pre[3 p + r].  Every address is in the box (the cell
+// indices are taken modulo N), also those of rows past the last.
+template <bool B16, int P0, int P1, int RG>
+__device__ __forceinline__ void gauss_load_planes(const typename GaussCell<B16>::type* fb, const GaussGeo& g,
+                                                  uint32_t msk, size_t NN, const uint32_t (&off)[3],
+                                                  typename GaussCell<B16>::type (&pre)[kGaussPre]) {
 #pragma unroll
-    for (int o = 0; o < 7; ++o) {
-      const float dd = static_cast<float>(o - 3) - t;
-      g[ax][o] = __expf(-0.5f * dd * dd);
-      s[ax] += g[ax][o];
+  for (int p = P0; p < P1; ++p) {
+    const auto* plane = fb + static_cast<size_t>(static_cast<uint32_t>(g.lo[0] + p) & msk) * NN;
+#pragma unroll
+    for (int r = 0; r < RG; ++r) pre[3 * p + r] = plane[off[r]];
+  }
+}
+template <bool B16>
+__device__ __forceinline__ void gauss_load(const typename GaussCell<B16>::type* fb, const GaussGeo& g, int N, size_t NN,
+                                           int lane, typename GaussCell<B16>::type (&pre)[kGaussPre]) {
+  const uint32_t msk = static_cast<uint32_t>(N - 1);
+  const uint32_t z = static_cast<uint32_t>(g.lo[2] + (lane & 15)) & msk;
+  uint32_t off[3];
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+    off[r] = (static_cast<uint32_t>(g.lo[1] + (lane >> 4) + 4 * r) & msk) * static_cast<uint32_t>(N) + z;
+  if (g.ny <= 8) {
+    gauss_load_planes<B16, 0, 7, 2>(fb, g, msk, NN, off, pre);
+    if (g.nx > 7) gauss_load_planes<B16, 7, 8, 2>(fb, g, msk, NN, off, pre);
+  } else {
+    gauss_load_planes<B16, 0, 7, 3>(fb, g, msk, NN, off, pre);
+    if (g.nx > 7) gauss_load_planes<B16, 7, 8, 3>(fb, g, msk, NN, off, pre);
+  }
+}
+
+// and on into the slice
+template <typename C>
+__device__ __forceinline__ void gauss_store(const GaussGeo& g, const C (&pre)[kGaussPre], float* lds, int lane) {
+  const bool third = (lane >> 4) + 8 < g.ny;
+  float* at = lds + lane;
+#pragma unroll
+  for (int p = 0; p < 8; ++p) {
+    if (p == 7 && g.nx <= 7) break;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const float2 v = gauss_cell(pre[3 * p + r]);
+      at[64 * r] = v.x;
+      at[kGaussEta + 64 * r] = v.y;
     }
-    lo[ax] = wave_min(valid ? c[ax] : INT_MAX) - 3;
-    sz[ax] = wave_max(valid ? c[ax] : INT_MIN) + 4 - lo[ax];
-  }
-  const int vol = sz[0] * sz[1] * sz[2];
-  if (vol > kGaussCap || sz[0] > 64 || sz[1] > 64 || sz[2] > 64) return false;
-  const int sxy = sz[1] * sz[2];
-  for (int v = lane; v < vol; v += 64) {
-    const int vx = v / sxy, r = v - vx * sxy, vy = r / sz[2], vz = r - vy * sz[2];
-    const int gx = static_cast<int>((base_x + lo[0] + vx) & (N - 1));
-    const int gy = static_cast<int>((base_y + lo[1] + vy) & (N - 1));
-    const int gz = static_cast<int>((base_z + lo[2] + vz) & (N - 1));
-    lds[v] = ld_field<B16>(a, gx * NN + static_cast<size_t>(gy) * N + gz);
-  }
-  wave_sync();
-  float ax_ = 0.0f, ay_ = 0.0f;
-  if (valid) {
-    const int o0 = ((c[0] - 3 - lo[0]) * sz[1] + (c[1] - 3 - lo[1])) * sz[2] + (c[2] - 3 - lo[2]);
-    for (int i = 0; i < 7; ++i) {
-      float bx = 0.0f, by = 0.0f;
-#pragma unroll
-      for (int jy = 0; jy < 7; ++jy) {
-        const float2* row = lds + o0 + i * sxy + jy * sz[2];
-        float rx_ = 0.0f, ry_ = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 7; ++k) {
-          const float2 f = row[k];
-          rx_ += g[2][k] * f.x;
-          ry_ += g[2][k] * f.y;
-        }
-        bx += g[1][jy] * rx_;
-        by += g[1][jy] * ry_;
+    if (g.ny > 8) {
+      const float2 v = gauss_cell(pre[3 * p + 2]);
+      if (third) {
+        at[128] = v.x;
+        at[kGaussEta + 128] = v.y;
       }
-      ax_ += g[0][i] * bx;
-      ay_ += g[0][i] * by;
+    }
+    at += 16 * g.ny;
+  }
+}
+
+// Planes x0 .. x0 + planes - 1 of any geometry straight into the slice.
+template <bool B16>
+__device__ __forceinline__ void gauss_stage(const typename GaussCell<B16>::type* fb, const GaussGeo& g, int x0,
+                                            int planes, int N, size_t NN, int lane, float* lds) {
+  const uint32_t msk = static_cast<uint32_t>(N - 1);
+  const uint32_t z = static_cast<uint32_t>(g.lo[2] + (lane & ((1 << g.zs) - 1))) & msk;
+  const int dy = 64 >> g.zs, cells = (planes * g.ny) << g.zs;
+  int x = g.lo[0] + x0, y = lane >> g.zs;   // dy <= 4 < ny
+#pragma unroll 4
+  for (int i = lane; i < cells; i += 64) {
+    const float2 v = gauss_cell(fb[static_cast<size_t>(static_cast<uint32_t>(x) & msk) * NN +
+                                   (static_cast<uint32_t>(g.lo[1] + y) & msk) * static_cast<uint32_t>(N) + z]);
+    lds[i] = v.x;
+    lds[kGaussEta + i] = v.y;
+    y += dy;
+    const bool wrap = y >= g.ny;
+    y -= wrap ? g.ny : 0;
+    x += wrap ? 1 : 0;
+  }
+}
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// Adds planes x0 .. x0 + planes - 1 to the quad's sums acc[pixel] (this lane's
+// column: component lane & 1 of every second row) and the x weights to sx.
+__device__ __forceinline__ void gauss_planes_add(const GaussGeo& g, int x0, int planes, const float (&wz)[8],
+                                                 const float (&wy)[4][4], const float* lds, int lane, float (&acc)[4],
+                                                 float& sx) {
+  const float* row = lds + ((lane & 1) ? kGaussEta : 0) + ((g.m1 + ((lane >> 1) & 1)) << g.zs) + g.m2;
+  const int two_rows = 2 << g.zs, plane = g.ny << g.zs;
+#pragma unroll 1
+  for (int x = x0; x < x0 + planes; ++x, row += plane) {
+    const int o = x - g.c0;
+    const float dd = static_cast<float>(o) - g.t[0];
+    const float w = o >= -3 && o <= 3 ? __expf(-0.5f * dd * dd) : 0.0f;
+    sx += w;
+    const float wx[4] = {dpp_f32<0x00>(w), dpp_f32<0x55>(w), dpp_f32<0xAA>(w), dpp_f32<0xFF>(w)};
+    float f[4][8];
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) f[jj][k] = row[jj * two_rows + k];
+    v4f D[4];
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) D[jj] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) D[jj] = __builtin_amdgcn_mfma_f32_4x4x1f32(wz[k], f[jj][k], D[jj], 0, 0, 0);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const float ty = fmaf(wy[3][p], D[3][p], fmaf(wy[2][p], D[2][p], fmaf(wy[1][p], D[1][p], wy[0][p] * D[0][p])));
+      acc[p] = fmaf(wx[p], ty, acc[p]);
     }
   }
-  wave_sync();  // the slice is reloaded for the next 64 pixels
-  const float inv = 1.0f / (s[0] * s[1] * s[2]);
-  d = ax_ * inv;
-  e = ay_ * inv;
-  return true;
+}
+
+// The pixel's weights of one axis in its quad's window slots; returns their sum.
+__device__ __forceinline__ float gauss_slots(float t, int sh, float (&w)[8]) {
+  float g[7], s = 0.0f;
+#pragma unroll
+  for (int o = 0; o < 7; ++o) {
+    const float dd = static_cast<float>(o - 3) - t;
+    g[o] = __expf(-0.5f * dd * dd);
+    s += g[o];
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k) w[k] = sh ? (k > 0 ? g[k - 1] : 0.0f) : (k < 7 ? g[k] : 0.0f);
+  return s;
 }
 
 __device__ __forceinline__ float trilerp(float tx, float ty, float tz, float c000, float c001, float c010, float c011,
@@ -205,10 +356,11 @@ __device__ __forceinline__ float trilerp(float tx, float ty, float tz, float c00
   return c0 + tx * (c1 - c0);
 }
 
+// (the Gaussian mode's LDS leaves two waves per SIMD)
 template <int U, int MODE, bool B16>
-__global__ void __launch_bounds__(kSkNT) k_skewers(SkewerArgs a) {
+__global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : 1) k_skewers(SkewerArgs a) {
   __shared__ float2 sbuf[kSkWaves][kHalfBuf];
-  __shared__ float2 sgauss[MODE == kSkGauss ? kSkWaves : 1][MODE == kSkGauss ? kGaussCap : 1];
+  __shared__ float sgauss[MODE == kSkGauss ? kSkWaves : 1][MODE == kSkGauss ? kGaussWords : 1];
   __shared__ int sjb[kSkWaves][kMaxZBins + 1];
   __shared__ unsigned long long s_sum[kMaxZBins], s_cnt[kMaxZBins];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -250,7 +402,9 @@ __global__ void __launch_bounds__(kSkNT) k_skewers(SkewerArgs a) {
         continue;
       }
       // twiddles from global memory: a copy in LDS would cost this kernel its fourth block per CU
-      if (with_ds) small_scale_wave(a, a.ps_amp, a.ps_kcut, a.id_base + q, ns, buf, a.tw2048, lane);
+      int dl_lane = lane;
+      if constexpr (MODE == kSkGauss) asm volatile("" : "+v"(dl_lane));
+      if (with_ds) small_scale_wave(a, a.ps_amp, a.ps_kcut, a.id_base + q, ns, buf, a.tw2048, dl_lane);
       // bin boundaries: jb[b] = first pixel with chi_j < edges[b] (chi_j decreases with j)
       if (want_bins) {
         bin_bounds(a.chi_edges, a.n_bins, chi0, a.dchi, np, jb, lane);
@@ -308,6 +462,24 @@ __global__ void __launch_bounds__(kSkNT) k_skewers(SkewerArgs a) {
       int bin = a.n_bins - 1;
       int cur = -1;
       unsigned long long acc = 0ull, cnt = 0ull;
+      // Gaussian mode: the geometry of the next 64 pixels, and their cells on the way
+      [[maybe_unused]] GaussGeo geo;
+      [[maybe_unused]] typename GaussCell<B16>::type pre[MODE == kSkGauss ? kGaussPre : 1];
+      [[maybe_unused]] const int64_t o3[3] = {ox, oy, oz};
+      [[maybe_unused]] const int32_t s3[3] = {static_cast<int32_t>(sx), static_cast<int32_t>(sy),
+                                              static_cast<int32_t>(sz)};
+      [[maybe_unused]] const typename GaussCell<B16>::type* fb = nullptr;
+      [[maybe_unused]] bool shared = false;   // quads share their window (steps below a third of a cell)
+      if constexpr (MODE == kSkGauss) {
+        if constexpr (B16) fb = a.field_bf16;
+        else fb = a.field;
+        constexpr int64_t kThird = (int64_t(1) << 32) / 3;
+        shared = sx < kThird && sx > -kThird && sy < kThird && sy > -kThird && sz < kThird && sz > -kThird;
+        if (shared && np > 0) {
+          geo = gauss_geo(o3, s3, 0, np, lane);
+          if (geo.fast) gauss_load<B16>(fb, geo, N, NN, lane, pre);
+        }
+      }
       // the Gaussian mode runs every lane through every 64-pixel chunk (its
       // wave reductions need all lanes); lanes past the end are not stored
       for (int it = (MODE == kSkGauss ? 0 : lane); it < np; it += 64 * U) {
@@ -317,15 +489,59 @@ __global__ void __launch_bounds__(kSkNT) k_skewers(SkewerArgs a) {
           float dl[U], el[U];
           if constexpr (MODE == kSkGauss) {
             static_assert(U == 1, "one pixel per lane");
-            const int j = j0;
-            const bool valid = j < np;
-            const int jj = valid ? j : j0 - lane;  // the chunk's first pixel (always valid)
-            const int64_t px = ox + jj * sx, py = oy + jj * sy, pz = oz + jj * sz;
-            // base cell: the chunk's first pixel, the same for every lane
-            const int j1 = j0 - lane;
-            const int64_t bx = (ox + j1 * sx) >> 32, by = (oy + j1 * sy) >> 32, bz = (oz + j1 * sz) >> 32;
-            if (!gauss7_staged<B16>(a, px, py, pz, valid, bx, by, bz, N, NN, sgauss[wv], lane, dl[0], el[0]))
-              gauss7_at<B16>(a, px, py, pz, N, NN, dl[0], el[0]);
+            bool done = false;   // uniform
+            if (shared) {
+              const GaussGeo g = geo;
+              float* lds = sgauss[wv];
+              // planes in the slice together
+              const int most = g.fast ? g.nx : min(g.nx, ((16 * kGaussRows) >> g.zs) / g.ny);
+              if (g.fast) gauss_store(g, pre, lds, lane);
+              else gauss_stage<B16>(fb, g, 0, most, N, NN, lane, lds);
+              wave_sync();
+              if (it + 64 < np) {  // the next pixels' cells
+                geo = gauss_geo(o3, s3, it + 64, np, lane);
+                if (geo.fast) gauss_load<B16>(fb, geo, N, NN, lane, pre);
+              }
+              float w[8], wz[8], wy[4][4], acc[4] = {0.0f, 0.0f, 0.0f, 0.0f}, wsum = 0.0f;
+              const float ws = gauss_slots(g.t[1], g.sh1, w) * gauss_slots(g.t[2], g.sh2, wz);
+              // lane l of a quad takes column l: component l & 1 of y row 2 jj + (l >> 1)
+#pragma unroll
+              for (int jj = 0; jj < 4; ++jj) {
+                // (both rows' values first: a DPP move under a lane's condition
+                // would not see the other lanes)
+                const float a0 = w[2 * jj], a1 = w[2 * jj + 1];
+                const float e0[4] = {dpp_f32<0x00>(a0), dpp_f32<0x55>(a0), dpp_f32<0xAA>(a0), dpp_f32<0xFF>(a0)};
+                const float e1[4] = {dpp_f32<0x00>(a1), dpp_f32<0x55>(a1), dpp_f32<0xAA>(a1), dpp_f32<0xFF>(a1)};
+#pragma unroll
+                for (int p = 0; p < 4; ++p) wy[jj][p] = (lane & 2) ? e1[p] : e0[p];
+              }
+              for (int x0 = 0;;) {
+                gauss_planes_add(g, x0, min(most, g.nx - x0), wz, wy, lds, lane, acc, wsum);
+                wave_sync();  // the slice is loaded again
+                x0 += most;
+                if (x0 >= g.nx) break;
+                gauss_stage<B16>(fb, g, x0, min(most, g.nx - x0), N, NN, lane, lds);
+                wave_sync();
+              }
+              // the two row parities, then pixel p's components (columns 0 and 1) to lane p
+#pragma unroll
+              for (int p = 0; p < 4; ++p) acc[p] += dpp_f32<0x4E>(acc[p]);
+              const int p = lane & 3;
+              const float inv = 1.0f / (wsum * ws);
+              const float d0 = dpp_f32<0x00>(acc[0]), d1 = dpp_f32<0x00>(acc[1]), d2 = dpp_f32<0x00>(acc[2]),
+                          d3 = dpp_f32<0x00>(acc[3]);
+              const float e0 = dpp_f32<0x55>(acc[0]), e1 = dpp_f32<0x55>(acc[1]), e2 = dpp_f32<0x55>(acc[2]),
+                          e3 = dpp_f32<0x55>(acc[3]);
+              dl[0] = (p == 0 ? d0 : p == 1 ? d1 : p == 2 ? d2 : d3) * inv;
+              el[0] = (p == 0 ? e0 : p == 1 ? e1 : p == 2 ? e2 : e3) * inv;
+              // a cell that is not finite spreads by the zero weights: such pixels
+              // are taken again one by one
+              done = !__any(!(fabsf(dl[0]) < HUGE_VALF) || !(fabsf(el[0]) < HUGE_VALF));
+            }
+            if (!done) {
+              const int j = min(j0, np - 1);
+              gauss7_at<B16>(a, ox + j * sx, oy + j * sy, oz + j * sz, N, NN, dl[0], el[0]);
+            }
           } else {
           float2 c[U][8];
           float t3[U][3];
