@@ -1,6 +1,7 @@
 // C-ABI of the lyamock library: argument checks, workspace carve-up and
 // launch sequencing.  All compute happens in the kernels of k_tables.hip,
 // k_fft.hip and k_skewers.hip.
+#include <algorithm>
 #include <stdio.h>
 #include <string.h>
 
@@ -8,6 +9,7 @@
 
 #include "../../include/lyamock.h"
 #include "lya_internal.h"
+#include "lya_linesum.h"
 
 constexpr size_t kStaticScratchBytes = size_t(1) << 17;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
@@ -313,14 +315,14 @@ int run_skewers(lya::SkewerArgs& a, const lya_cosmo* cosmo, const lya_zbins* zb,
 }
 
 struct PdCarve {
-  size_t sum, cnt, tw, queue, total;
+  size_t sum, aux, tw, queue, total;
 };
 
 PdCarve carve_p1d(int64_t n_sk, int nk) {
   PdCarve c{};
   size_t o = 0;
   c.sum = o;   o += align256(sizeof(double) * static_cast<size_t>(n_sk) * nk);
-  c.cnt = o;   o += align256(sizeof(int) * static_cast<size_t>(n_sk) * nk);
+  c.aux = o;   o += align256(std::max(sizeof(int) * static_cast<size_t>(n_sk) * nk, lya::line_sum_bytes(n_sk, nk, 1)));
   c.tw = o;    o += align256(sizeof(float2) * lya::kTw2048);
   c.queue = o; o += 256;
   c.total = o;
@@ -424,7 +426,7 @@ int lya_p1d(const lya_skewers* sk, const lya_cosmo* cosmo, const float* flux, co
   a.k_edges = spec->k_edges;
   a.dv = velocity_pixel(spec->dpix, spec->z_ref, cosmo->omega_m);
   a.part_sum = reinterpret_cast<double*>(w + c.sum);
-  a.part_cnt = reinterpret_cast<int*>(w + c.cnt);
+  a.aux = w + c.aux;
   a.tw2048 = reinterpret_cast<float2*>(w + c.tw);
   a.queue = reinterpret_cast<unsigned int*>(w + c.queue);
   a.chunk = 4;

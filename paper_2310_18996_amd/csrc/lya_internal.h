@@ -185,10 +185,7 @@ struct P1dArgs {
   const int64_t* offset;
   const double* chi0;
   double dchi;
-  const float* flux;         // or null: F from dens/eta under constant (fa, fb, fc)
-  const float* dens;
-  const float* eta;
-  float fa, fb, fc;
+  const float* flux;
   int n_fbins;               // mean-flux bins in comoving distance
   const double* chi_edges;   // [n_fbins + 1]
   const double* fsum;        // [n_fbins]
@@ -196,8 +193,8 @@ struct P1dArgs {
   int n_kbins;
   const double* k_edges;     // [n_kbins + 1], s/km
   double dv;                 // velocity pixel, km/s
-  double* part_sum;          // workspace [n_kbins][n_sk]
-  int* part_cnt;             // workspace [n_kbins][n_sk]
+  double* part_sum;          // workspace [n_sk][n_kbins]
+  char* aux;                 // workspace: line_sum_bytes(n_sk, n_kbins, 1)
   const float2* tw2048;
   unsigned int* queue;
   int chunk;
@@ -219,8 +216,9 @@ struct TuneEvalArgs {
   int nk;
   const double* k_edges;          // device [nk + 1]
   double* fs;                     // workspace [G][n_sk]: sum of F per skewer
-  double* ps;                     // workspace [G][nk][n_sk]: sum |X_m|^2 / N_P
-  int* pc;                        // workspace [G][nk][n_sk]: modes
+  double* ps;                     // workspace [G][n_sk][nk]: sum |X_m|^2 / N_P
+  char* aux;                      // workspace: tune_eval_aux_bytes(n_sk, nk)
+  int* modes;                     // (in aux) [G] tables of first modes per length class
   const float2* tw2048;
   unsigned int* queue;
   int chunk;
@@ -238,10 +236,9 @@ struct TuneEvalArgs {
   const float* ps_ratio;
   int ps_fixed_amp;
 };
-// sums/counts: [G][nk + 1] (bins, then flux and pixels); rows (FP64) and rows32
-// (FP32, may be NULL): [G][1 + nk] = Fbar, P_1..P_nk.
-hipError_t launch_tune_eval(const TuneEvalArgs& a, double* sums, int64_t* counts, double* rows, float* rows32,
-                            hipStream_t st);
+// rows (FP64) and rows32 (FP32), either may be NULL: [G][1 + nk] = Fbar, P_1..P_nk.
+size_t tune_eval_aux_bytes(int64_t n_sk, int nk);
+hipError_t launch_tune_eval(const TuneEvalArgs& a, double* rows, float* rows32, hipStream_t st);
 
 // Tuning statistics with delta_S redrawn per draw (lya_tune.hip), for the
 // small-scale power tuning: stored pixels without delta_S and their table,

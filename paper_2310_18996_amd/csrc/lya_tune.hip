@@ -7,6 +7,7 @@
 // mode runs the same search on the MLP's predictions, checks the optimum on the
 // GPU and corrects the prediction by the measured defect before searching
 // again (a few GPU evaluations per redshift instead of one per search step).
+#include <algorithm>
 #include <math.h>
 #include <stdio.h>
 #include <string.h>
@@ -24,7 +25,7 @@ namespace {
 size_t al256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
 struct TuneCarve {
-  size_t tw, queue, fs, ps, pc, sums, counts, rows, emu, total;
+  size_t tw, queue, fs, ps, aux, rows, emu, total;
 };
 
 // workspace of the batched evaluation: per-skewer partials for up to
@@ -37,9 +38,7 @@ TuneCarve carve_tune(int64_t n_sk, int nk) {
   c.queue = o;  o += 256;
   c.fs = o;     o += al256(sizeof(double) * G * S);
   c.ps = o;     o += al256(sizeof(double) * G * nk * S);
-  c.pc = o;     o += al256(sizeof(int) * G * nk * S);
-  c.sums = o;   o += al256(sizeof(double) * G * (nk + 1));
-  c.counts = o; o += al256(sizeof(int64_t) * G * (nk + 1));
+  c.aux = o;    o += al256(std::max(sizeof(int) * G * nk * S, tune_eval_aux_bytes(n_sk, nk)));
   c.rows = o;   o += al256(sizeof(double) * G * (nk + 1));
   c.emu = o;    o += al256(emulator_eval_bytes());
   c.total = o;
@@ -58,7 +57,7 @@ TuneEvalArgs eval_args(const lya_tune_spec* spec, char* w, const TuneCarve& c) {
   a.k_edges = spec->p1d.k_edges;
   a.fs = reinterpret_cast<double*>(w + c.fs);
   a.ps = reinterpret_cast<double*>(w + c.ps);
-  a.pc = reinterpret_cast<int*>(w + c.pc);
+  a.aux = w + c.aux;
   a.tw2048 = reinterpret_cast<const float2*>(w + c.tw);
   a.queue = reinterpret_cast<unsigned int*>(w + c.queue);
   a.chunk = 4;
@@ -86,8 +85,7 @@ struct Evaluator {
     ea.draw[0][1] = static_cast<float>(b);
     ea.draw[0][2] = static_cast<float>(cc);
     ea.dv[0] = velocity_pixel_at(spec, z);
-    hipError_t e = launch_tune_eval(ea, reinterpret_cast<double*>(w + c.sums), reinterpret_cast<int64_t*>(w + c.counts),
-                                    reinterpret_cast<double*>(w + c.rows), nullptr, st);
+    hipError_t e = launch_tune_eval(ea, reinterpret_cast<double*>(w + c.rows), nullptr, st);
     if (e != hipSuccess) return e;
     double h[kMaxKBins + 1];
     if ((e = hipMemcpyAsync(h, w + c.rows, sizeof(double) * (nk + 1), hipMemcpyDeviceToHost, st)) != hipSuccess)
@@ -147,7 +145,7 @@ hipError_t tune_eval_ds(const DsSource& src, char* w, const DsDraw* d, int G, do
   a.k_edges = src.k_edges;
   a.fs = reinterpret_cast<double*>(w + c.fs);
   a.ps = reinterpret_cast<double*>(w + c.ps);
-  a.pc = reinterpret_cast<int*>(w + c.pc);
+  a.aux = w + c.aux;
   a.tw2048 = reinterpret_cast<const float2*>(w + c.tw);
   a.queue = reinterpret_cast<unsigned int*>(w + c.queue);
   a.chunk = 4;
@@ -166,8 +164,7 @@ hipError_t tune_eval_ds(const DsSource& src, char* w, const DsDraw* d, int G, do
     a.dv[g] = src.dpix * (100.0 * sqrt(om * (x * x * x) + (1.0 - om)) / x);
   }
   double* rows = reinterpret_cast<double*>(w + c.rows);
-  hipError_t e = launch_tune_eval(a, reinterpret_cast<double*>(w + c.sums), reinterpret_cast<int64_t*>(w + c.counts),
-                                  rows, rows32, st);
+  hipError_t e = launch_tune_eval(a, rows, rows32, st);
   if (e != hipSuccess || !rows_host) return e;
   if ((e = hipMemcpyAsync(rows_host, rows, sizeof(double) * G * (src.nk + 1), hipMemcpyDeviceToHost, st)) !=
       hipSuccess)
@@ -199,8 +196,7 @@ int emulator_labels(const lya_tune_spec* spec, const double* draws, int64_t n, f
       ea.draw[g][2] = static_cast<float>(d[2]);
       ea.dv[g] = velocity_pixel_at(spec, d[3]);
     }
-    e = launch_tune_eval(ea, reinterpret_cast<double*>(w + c.sums), reinterpret_cast<int64_t*>(w + c.counts),
-                         nullptr, y + i0 * (1 + nk), st);
+    e = launch_tune_eval(ea, nullptr, y + i0 * (1 + nk), st);
   }
   if (e != hipSuccess) {
     snprintf(err, errlen, "label evaluation: %s", hipGetErrorString(e));

@@ -11,7 +11,7 @@ namespace lya {
 constexpr int kHalfMax = 1024;                        // complex length <= 1024
 constexpr int kHalfBuf = kHalfMax + kHalfMax / 16;    // one padding slot per 16
 
-__device__ __forceinline__ int pidx(int i) { return i + (i >> 4); }
+__device__ __forceinline__ int pidx(int i) { return i + (i >> 4); }   // pidx(a + b) = pidx(a) + pidx(b) if a & b == 0
 
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -25,87 +25,219 @@ __device__ __forceinline__ double pixel_chi(double chi0, int j, double dchi) {
   return __dsub_rn(chi0, __dmul_rn(static_cast<double>(j), dchi));
 }
 
-// jb[b] = first pixel j in [0, np] with chi_j < edges[b], for b = 0..n_bins
-// (chi_j decreases with j), so pixel j lies in distance bin b exactly when
-// jb[b+1] <= j < jb[b].  Lanes split the edges; exact FP64 comparisons.
+// First pixel j in [0, np] with chi_j < edge (chi_j decreases with j); exact
+// FP64 comparisons.
+__device__ __forceinline__ int first_below(double edge, double chi0, double dchi, int np) {
+  double j0 = dchi > 0.0 ? ceil((chi0 - edge) / dchi) : 0.0;
+  j0 = j0 < 0.0 ? 0.0 : (j0 > np ? np : j0);
+  int j = static_cast<int>(j0);
+  while (j < np && pixel_chi(chi0, j, dchi) >= edge) ++j;
+  while (j > 0 && pixel_chi(chi0, j - 1, dchi) < edge) --j;
+  return j;
+}
+
+// jb[b] = first_below of edges[b], for b = 0..n_bins, so pixel j lies in
+// distance bin b exactly when jb[b+1] <= j < jb[b].  Lanes split the edges.
 __device__ __forceinline__ void bin_bounds(const double* __restrict__ edges, int n_bins, double chi0, double dchi,
                                            int np, int* jb, int lane) {
-  for (int b = lane; b <= n_bins; b += 64) {
-    const double e = edges[b];
-    double j0 = dchi > 0.0 ? ceil((chi0 - e) / dchi) : 0.0;
-    j0 = j0 < 0.0 ? 0.0 : (j0 > np ? np : j0);
-    int j = static_cast<int>(j0);
-    while (j < np && pixel_chi(chi0, j, dchi) >= e) ++j;
-    while (j > 0 && pixel_chi(chi0, j - 1, dchi) < e) --j;
-    jb[b] = j;
-  }
+  for (int b = lane; b <= n_bins; b += 64) jb[b] = first_below(edges[b], chi0, dchi, np);
 }
 
 // The block's copy of the twiddle table tw2048 in LDS (read by every stage of
 // every wavefront FFT; global reads would put an L2 round trip in each stage).
+// Padded so that the stages' strides (8, 32, 128 and their multiples) spread over
+// the banks: without it they met in one or two of them, half of all LDS cycles of
+// a line (8 draws on 20,000 lines 326 -> 279 us).
+__host__ __device__ constexpr int tidx(int i) { return i + (i >> 3) + (i >> 5); }
+struct LdsTw {
+  const float2* p;
+  __device__ __forceinline__ float2 operator[](int i) const { return p[tidx(i)]; }
+};
+// N: 3/4 of the table is all that radix-4 stages and half-length spectra read.
+template <int N = kTw2048>
 __device__ __forceinline__ void load_twiddles(float2* stw, const float2* __restrict__ tw2048, int tid, int nt) {
-  for (int i = tid; i < kTw2048; i += nt) stw[i] = tw2048[i];
+  for (int i = tid; i < N; i += nt) stw[tidx(i)] = tw2048[i];
+}
+// entry n STEP of the table: one multiplication where the padding is linear in n
+template <int STEP, class TW>
+__device__ __forceinline__ float2 tw_at(TW tw, int n) { return tw[n * STEP]; }
+template <int STEP>
+__device__ __forceinline__ float2 tw_at(LdsTw tw, int n) {
+  if constexpr (STEP % 32 == 0) return tw.p[n * tidx(STEP)];
+  else return tw[n * STEP];
 }
 
-// Unnormalised inverse DFT (exp(+2 pi i k n / M)) of buf[pidx(0..M-1)], M a
-// power of two <= kHalfMax, by an in-place Stockham radix-4/2 FFT: every stage
-// first reads all of the lane's inputs, then writes (the wave runs in lockstep).
+// First mode m >= 1 of a line of n_p pixels with k_m = 2 pi m / (n_p dv) >= edge
+// (M + 1 if none, M = n_p / 2), decided in FP64.
+__device__ __forceinline__ int first_mode(double edge, int n_p, double dv) {
+  const int M = n_p / 2;
+  const double kf = 2.0 * M_PI / (n_p * dv);
+  double m0 = ceil(edge / kf);
+  m0 = m0 < 1.0 ? 1.0 : (m0 > M + 1.0 ? M + 1.0 : m0);
+  int m = static_cast<int>(m0);
+  while (m <= M && (2.0 * M_PI * m) / (n_p * dv) < edge) ++m;
+  while (m > 1 && (2.0 * M_PI * (m - 1)) / (n_p * dv) >= edge) --m;
+  return m;
+}
+
+// Lines are transformed at the lengths 2^1 .. 2^11 only, so the first modes of
+// the k bins are a table per length class (log2 of the length) and not an FP64
+// search per line: row c holds the nk + 1 edges' first modes, then the smallest
+// and the largest of them (the modes any bin wants).
+constexpr int kLenClasses = 12;  // class 0: no transform
+__device__ __forceinline__ int len_class(int np) {
+  return np >= 2 ? 31 - __clz(np < 2 * kHalfMax ? np : 2 * kHalfMax) : 0;
+}
+__host__ __device__ constexpr int mode_row(int nk) { return nk + 3; }
+// By all threads of a block, into LDS; complete after the caller's next barrier.
+__device__ __forceinline__ void mode_table(unsigned short* tab, const double* __restrict__ k_edges, int nk, double dv,
+                                           int tid, int nt) {
+  const int row = mode_row(nk);
+  for (int i = tid; i < kLenClasses * (nk + 1); i += nt) {
+    const int c = i / (nk + 1), b = i % (nk + 1);
+    tab[c * row + b] = static_cast<unsigned short>(c > 0 ? first_mode(k_edges[b], 1 << c, dv) : 1);
+  }
+  __syncthreads();
+  for (int c = tid; c < kLenClasses; c += nt) {
+    unsigned short lo = tab[c * row], hi = lo;
+    for (int b = 1; b <= nk; ++b) {
+      const unsigned short m = tab[c * row + b];
+      lo = m < lo ? m : lo;
+      hi = m > hi ? m : hi;
+    }
+    tab[c * row + nk + 1] = lo;
+    tab[c * row + nk + 2] = hi;
+  }
+}
+
+// |X_m|^2 scale of a transformed line for the modes lo <= m < hi (1 <= m <= M),
+// from the transform Z of its pixel pairs in buf, left in the real part of
+// slot m mod M: X_m = (Z_m + conj Z_{M-m})/2 + w^m (Z_m - conj Z_{M-m})/(2i).  A
+// lane takes m and M - m, which read the same two values, so the powers can
+// take their place without a second buffer.
+__device__ __forceinline__ float line_power(float2 zm, float2 zc, float2 w, float scale) {
+  const float2 E = make_float2(0.5f * (zm.x + zc.x), 0.5f * (zm.y - zc.y));
+  const float2 O = make_float2(0.5f * (zm.y + zc.y), -0.5f * (zm.x - zc.x));
+  const float2 X = cadd(E, cmul(w, O));
+  return scale * (X.x * X.x + X.y * X.y);
+}
+template <class TW>
+__device__ __forceinline__ void power_in_place(float2* buf, int M, int lo, int hi, float scale, TW tw, int lane) {
+  const int twstep = kTw2048 / (2 * M);
+  // pairs (m, M - m), 0 <= m <= M/2, of which one lies in [lo, hi); the pair
+  // (0, M) stands for mode M alone
+  const int first = hi > M / 2 ? min(lo, M - hi + 1) : lo, last = min(hi - 1, M / 2);
+  const int end = lo > M / 2 ? M - lo : (hi > M / 2 ? M / 2 : last);
+  for (int m = (first > 0 ? first : 0) + lane; m <= end; m += 64) {
+    const float2 zm = buf[pidx(m)], zc = buf[pidx(m == 0 ? 0 : M - m)];
+    if (m == 0) {
+      if (M >= lo && M < hi) buf[pidx(0)].x = line_power(zm, zm, tw[M * twstep], scale);
+      continue;
+    }
+    const int c = M - m;
+    if (m >= lo && m < hi) buf[pidx(m)].x = line_power(zm, zc, tw[m * twstep], scale);
+    if (c != m && c >= lo && c < hi) buf[pidx(c)].x = line_power(zc, zm, tw[c * twstep], scale);
+  }
+}
+
+// FP64 sums of the powers power_in_place left, per k bin (first modes m0 <= m <
+// m1 of the lane's bin): 64 >> lg lanes bins, each by 2^lg lanes taking every
+// 2^lg-th mode, added in a fixed tree.
+__device__ __forceinline__ double bin_sum(const float2* buf, int M, int m0, int m1, int lg, int lane) {
+  double s = 0.0;
+#pragma unroll 4
+  for (int m = m0 + (lane & ((1 << lg) - 1)); m < m1; m += 1 << lg) s += buf[pidx(m == M ? 0 : m)].x;
+  for (int w = 0; w < lg; ++w) s += __shfl_xor(s, 1 << w);
+  return s;
+}
+__device__ __forceinline__ int bin_split(int nk) { return nk <= 8 ? 3 : nk <= 16 ? 2 : nk <= 32 ? 1 : 0; }
+
+// Value of a lane, the lane uniform, as a scalar.
+__device__ __forceinline__ int lane_i32(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+__device__ __forceinline__ int64_t lane_i64(int64_t v, int l) {
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(v), l);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(v >> 32), l);
+  return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+}
+__device__ __forceinline__ double lane_f64(double v, int l) {
+  return __longlong_as_double(lane_i64(__double_as_longlong(v), l));
+}
+
+// Unnormalised inverse DFT (exp(+2 pi i k n / M)) of buf[pidx(0..M-1)], M =
+// 2^LG <= kHalfMax, by an in-place Stockham radix-4/2 FFT: every stage first
+// reads all of the lane's inputs, then writes (the wave runs in lockstep).
 // tw2048[k] = exp(2 pi i k / 2048).
-__device__ __forceinline__ void wave_ifft(float2* buf, int M, const float2* tw2048, int lane) {
-  for (int s = 1; s < M;) {
-    const int R = (M / s >= 4) ? 4 : 2;
-    const int nb = M / R;
-    float2 v[4][4];
+template <int LG, int LS = 0, class TW>
+__device__ __forceinline__ void wave_ifft_n(float2* buf, TW tw2048, int lane) {
+  if constexpr (LS < LG) {
+    constexpr int LR = LG - LS >= 2 ? 2 : 1, R = 1 << LR, s = 1 << LS, nb = 1 << (LG - LR);
+    constexpr int T = nb > 64 ? nb / 64 : 1, step = kTw2048 >> (LS + LR);
+    float2 v[T][R];
+    asm volatile("" : "+v"(lane));   // no stage's addresses are computed ahead of it and kept
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < T; ++t) {
       const int j = lane + 64 * t;
-      if (j < nb) {
+      if (nb >= 64 || j < nb) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (r < R) v[t][r] = buf[pidx(j + r * nb)];
+        for (int r = 0; r < R; ++r) v[t][r] = buf[pidx(j) + pidx(r * nb)];
       }
     }
     wave_sync();
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < T; ++t) {
       const int j = lane + 64 * t;
-      if (j < nb) {
-        const int k = j % s;
-        if (s > 1) {
-          const int step = kTw2048 / (s * R);
+      if (nb >= 64 || j < nb) {
+        const int k = j & (s - 1);
+        if constexpr (s > 1) {
 #pragma unroll
-          for (int r = 1; r < 4; ++r)
-            if (r < R) v[t][r] = cmul(v[t][r], tw2048[r * k * step]);
+          for (int r = 1; r < R; ++r) v[t][r] = cmul(v[t][r], tw_at<step>(tw2048, r * k));
         }
-        if (R == 4) {
-          dft4(v[t][0], v[t][1], v[t][2], v[t][3]);
-        } else {
-          dft2(v[t][0], v[t][1]);
-        }
-        const int base = (j / s) * s * R + k;
+        dft<R>(v[t]);
+        const int base = (j - k) * R + k;
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (r < R) buf[pidx(base + r * s)] = v[t][r];
+        for (int r = 0; r < R; ++r) buf[pidx(base) + pidx(r * s)] = v[t][r];
       }
     }
     wave_sync();
-    s *= R;
+    wave_ifft_n<LG, LS + LR>(buf, tw2048, lane);
+  }
+}
+// The length as a constant: no division by a stage's stride, no pass over the
+// butterflies that a shorter line does not have, and addresses as one base and
+// immediates (1D power of 50,000 lines 255 -> 216 us).
+template <class TW>
+__device__ __forceinline__ void wave_ifft(float2* buf, int M, TW tw2048, int lane) {
+  switch (31 - __clz(M)) {
+    case 1: return wave_ifft_n<1>(buf, tw2048, lane);
+    case 2: return wave_ifft_n<2>(buf, tw2048, lane);
+    case 3: return wave_ifft_n<3>(buf, tw2048, lane);
+    case 4: return wave_ifft_n<4>(buf, tw2048, lane);
+    case 5: return wave_ifft_n<5>(buf, tw2048, lane);
+    case 6: return wave_ifft_n<6>(buf, tw2048, lane);
+    case 7: return wave_ifft_n<7>(buf, tw2048, lane);
+    case 8: return wave_ifft_n<8>(buf, tw2048, lane);
+    case 9: return wave_ifft_n<9>(buf, tw2048, lane);
+    case 10: return wave_ifft_n<10>(buf, tw2048, lane);
+    default: return;   // M = 1
   }
 }
 
 // One radix-R stage of the in-place Stockham FFT wave_ifft8: s = product of the
 // radices before it; every lane first reads all of its inputs, then writes.
-template <int R>
-__device__ __forceinline__ void wave_stage(float2* buf, int M, int s, const float2* tw2048, int lane) {
+template <int R, class TW>
+__device__ __forceinline__ void wave_stage(float2* buf, int M, int ls, TW tw2048, int lane) {
+  constexpr int LR = R == 16 ? 4 : R == 8 ? 3 : R == 4 ? 2 : 1;
+  const int s = 1 << ls;   // shifts and masks: the compiler would not know that s divides as a power of two
   constexpr int TMAX = kHalfMax / R / 64 > 0 ? kHalfMax / R / 64 : 1;  // butterflies per lane at M = kHalfMax
   const int nb = M / R;
   float2 v[TMAX][R];
+  asm volatile("" : "+v"(lane));   // as above
 #pragma unroll
   for (int t = 0; t < TMAX; ++t) {
     const int j = lane + 64 * t;
     if (j < nb) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[t][r] = buf[pidx(j + r * nb)];
+      for (int r = 0; r < R; ++r) v[t][r] = buf[pidx(j) + pidx(r * nb)];
     }
   }
   wave_sync();
@@ -113,16 +245,16 @@ __device__ __forceinline__ void wave_stage(float2* buf, int M, int s, const floa
   for (int t = 0; t < TMAX; ++t) {
     const int j = lane + 64 * t;
     if (j < nb) {
-      const int k = j % s;
+      const int k = j & (s - 1);
       if (s > 1) {
-        const int step = kTw2048 / (s * R);
+        const int step = kTw2048 >> (ls + LR);
 #pragma unroll
         for (int r = 1; r < R; ++r) v[t][r] = cmul(v[t][r], tw2048[r * k * step]);
       }
       dft<R>(v[t]);
-      const int base = (j / s) * s * R + k;
+      const int base = (j - k) * R + k;
 #pragma unroll
-      for (int r = 0; r < R; ++r) buf[pidx(base + r * s)] = v[t][r];
+      for (int r = 0; r < R; ++r) buf[pidx(base) + pidx(r * s)] = v[t][r];
     }
   }
   wave_sync();
@@ -131,16 +263,17 @@ __device__ __forceinline__ void wave_stage(float2* buf, int M, int s, const floa
 // The same inverse DFT as wave_ifft by radix-8 stages (with radix-16 ones
 // where they save a stage, then one radix-4 or radix-2 stage for what
 // remains): fewer passes through LDS, more registers.
-__device__ __forceinline__ void wave_ifft8(float2* buf, int M, const float2* tw2048, int lane) {
+template <class TW>
+__device__ __forceinline__ void wave_ifft8(float2* buf, int M, TW tw2048, int lane) {
   const int lg = 31 - __clz(M);
-  int s = 1;
+  int ls = 0;
   // radix-16 stages where they save a stage: 16 x 8^k for lg = 1 mod 3,
   // 16 x 16 x 8^k for lg = 2 mod 3 from 256 up
   const int n16 = (lg % 3 == 1 && lg >= 4) ? 1 : (lg % 3 == 2 && lg >= 8) ? 2 : 0;
-  for (int i = 0; i < n16; ++i, s *= 16) wave_stage<16>(buf, M, s, tw2048, lane);
-  for (; M / s >= 8; s *= 8) wave_stage<8>(buf, M, s, tw2048, lane);
-  if (M / s == 4) wave_stage<4>(buf, M, s, tw2048, lane);
-  else if (M / s == 2) wave_stage<2>(buf, M, s, tw2048, lane);
+  for (int i = 0; i < n16; ++i, ls += 4) wave_stage<16>(buf, M, ls, tw2048, lane);
+  for (; lg - ls >= 3; ls += 3) wave_stage<8>(buf, M, ls, tw2048, lane);
+  if (lg - ls == 2) wave_stage<4>(buf, M, ls, tw2048, lane);
+  else if (lg - ls == 1) wave_stage<2>(buf, M, ls, tw2048, lane);
 }
 
 
@@ -190,9 +323,9 @@ __device__ __forceinline__ float2 ps_mode(const A& a, int m, int ns, float amp_s
 // table (ps_nb, ps_edges_k, ps_ratio) and the fixed-amplitude switch
 // (ps_fixed_amp).  R8: the radix-8 FFT (fewer LDS passes); otherwise the
 // radix-4 one, for callers that cannot spare its registers.
-template <class A, bool R8 = true>
-__device__ void small_scale_wave(const A& a, double amp, double kcut, uint64_t qid, int ns, float2* buf,
-                                 const float2* tw, int lane) {
+template <class A, class TW, bool R8 = true>
+__device__ void small_scale_wave(const A& a, double amp, double kcut, uint64_t qid, int ns, float2* buf, TW tw,
+                                 int lane) {
   const int M = ns / 2;
   const float amp_scale = static_cast<float>(amp / (ns * a.dpix));
   const double dk = 2.0 * M_PI / (ns * a.dpix) / kcut;
