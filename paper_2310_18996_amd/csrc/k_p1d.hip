@@ -16,6 +16,7 @@
 
 #include "lya_internal.h"
 #include "lya_linesum.h"
+#include "lya_pull.h"
 #include "lya_wavefft.h"
 
 namespace lya {
@@ -30,7 +31,8 @@ constexpr int kPdTw = kTw2048 * 3 / 4;
 // modes, and the few distance edges inside a line compared one by one (a search
 // per pixel over all edges was five dependent LDS reads).  The arithmetic of each
 // power is as in a radix-4 transform of one line.  35M pixels of 50,000 lines:
-// 305 us with FP64 bin searches per line and two blocks per CU, 214 us.
+// 305 us with FP64 bin searches per line and two blocks per CU, 214 us;
+// 128 us with the queue on 16 cache lines.
 __global__ void __launch_bounds__(kPdNT, 3) k_p1d(P1dArgs a) {
   __shared__ float2 sbuf[kPdWaves][kHalfBuf];
   __shared__ float2 stw[tidx(kPdTw)];
@@ -48,12 +50,9 @@ __global__ void __launch_bounds__(kPdNT, 3) k_p1d(P1dArgs a) {
   const LdsTw tw{stw};
   float2* buf = sbuf[wv];
   float* bf = reinterpret_cast<float*>(buf);
-  for (;;) {
-    int c = 0;
-    if (lane == 0) c = static_cast<int>(atomicAdd(a.queue, 1u));
-    c = __builtin_amdgcn_readfirstlane(__shfl(c, 0));
-    const int64_t q0 = static_cast<int64_t>(static_cast<uint32_t>(c)) * a.chunk;  // pulls stay below 2^32
-    if (q0 >= a.n_sk) break;
+  LinePull<P1dArgs, kPdWaves> pull;
+  for (int64_t c = pull.first(lane); c < a.chunks; c = pull.next(lane)) {
+    const int64_t q0 = c * a.chunk;
     const int64_t q1 = q0 + a.chunk < a.n_sk ? q0 + a.chunk : a.n_sk;
     // the pull's lines, a lane each (chunk <= 64)
     const int64_t ql = q0 + lane < q1 ? q0 + lane : q0;
@@ -61,6 +60,7 @@ __global__ void __launch_bounds__(kPdNT, 3) k_p1d(P1dArgs a) {
     const int64_t offl = a.offset[ql];
     const double chil = a.chi0[ql];
     for (int64_t q = q0; q < q1; ++q) {
+      if (q == q1 - 1) pull.ask(lane);
       const int i = static_cast<int>(q - q0);
       const int np = lane_i32(npl, i);
       double* psum = a.part_sum + q * nk;   // the line's partial sums
@@ -139,9 +139,10 @@ __global__ void __launch_bounds__(256) k_p1d_final(LineSumArgs a, const double* 
 hipError_t launch_p1d(const P1dArgs& p, double* psum, int64_t* pcount, hipStream_t st) {
   P1dArgs a = p;
   int64_t blocks = static_cast<int64_t>(device_cus()) * 3;
-  a.chunk = static_cast<int>(std::min<int64_t>(a.chunk, std::max<int64_t>(1, a.n_sk / (blocks * kPdWaves))));
-  const int64_t nchunks = (a.n_sk + a.chunk - 1) / a.chunk;
-  if (blocks * kPdWaves > nchunks) blocks = (nchunks + kPdWaves - 1) / kPdWaves;
+  // eight pulls per wave or more, so that the waves end together
+  a.chunk = static_cast<int>(std::min<int64_t>(a.chunk, std::max<int64_t>(1, a.n_sk / (8 * blocks * kPdWaves))));
+  a.chunks = (a.n_sk + a.chunk - 1) / a.chunk;
+  if (blocks * kPdWaves > a.chunks) blocks = (a.chunks + kPdWaves - 1) / kPdWaves;
   if (blocks < 1) blocks = 1;
   if (a.n_sk > 0) LYA_TIMED("p1d", st, hipLaunchKernelGGL(k_p1d, dim3(static_cast<unsigned>(blocks)), dim3(kPdNT), 0, st, a));
   LineSumArgs l{};

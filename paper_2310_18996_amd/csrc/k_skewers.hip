@@ -28,6 +28,7 @@
 #include <algorithm>
 
 #include "lya_internal.h"
+#include "lya_pull.h"
 #include "lya_wavefft.h"
 
 namespace lya {
@@ -40,8 +41,14 @@ __global__ void __launch_bounds__(256) k_skewer_finalize(int n_bins, const unsig
                                                          int64_t* cnt) {
   const int t = threadIdx.x;
   if (t < n_bins) {
-    if (fsum) fsum[t] = static_cast<double>(bsum[t]) * 2.3283064365386963e-10;  // 2^-32
-    if (cnt) cnt[t] = static_cast<int64_t>(bcnt[t]);
+    unsigned long long s = 0ull, c = 0ull;
+#pragma unroll
+    for (int i = 0; i < kBinCopies; ++i) {
+      s += bsum[i * kMaxZBins + t];
+      c += bcnt[i * kMaxZBins + t];
+    }
+    if (fsum) fsum[t] = static_cast<double>(s) * 2.3283064365386963e-10;  // 2^-32
+    if (cnt) cnt[t] = static_cast<int64_t>(c);
   }
 }
 
@@ -356,6 +363,15 @@ __device__ __forceinline__ float trilerp(float tx, float ty, float tz, float c00
   return c0 + tx * (c1 - c0);
 }
 
+// What small_scale_wave reads of the arguments.
+struct LineNoise {
+  uint64_t seed;
+  double dpix;
+  const double* ps_edges_k;
+  const float* ps_ratio;
+  int ps_nb, ps_fixed_amp;
+};
+
 // (the Gaussian mode's LDS leaves two waves per SIMD)
 template <int U, int MODE, bool B16>
 __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : 1) k_skewers(SkewerArgs a) {
@@ -375,49 +391,52 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : 1) k_skewers(Ske
   const bool want_bins = a.n_bins > 0 && a.do_flux;
   float2* buf = sbuf[wv];
   int* jb = sjb[wv];
-  for (;;) {
-    int c = 0;
-    if (lane == 0) c = static_cast<int>(atomicAdd(a.queue, 1u));
-    c = __builtin_amdgcn_readfirstlane(__shfl(c, 0));
-    const int64_t q0 = static_cast<int64_t>(static_cast<uint32_t>(c)) * a.chunk;  // pulls stay below 2^32
-    if (q0 >= a.n_sk) break;
-    const int64_t q1 = q0 + a.chunk < a.n_sk ? q0 + a.chunk : a.n_sk;
+  LinePull<SkewerArgs, kSkWaves> pull;
+  for (int64_t c = pull.first(lane); c < a.chunks; c = pull.next(lane)) {
+    const auto* ca0 = kernarg_here<SkewerArgs>();
+    const int64_t q0 = c * ca0->chunk;
+    const int64_t q1 = q0 + ca0->chunk < ca0->n_sk ? q0 + ca0->chunk : ca0->n_sk;
     for (int64_t q = q0; q < q1; ++q) {
-      const int np = a.npix[q];
-      const int64_t off = a.offset[q];
-      const double chi0 = a.chi0[q];
+      if (q == q1 - 1) pull.ask(lane);
+      const auto* la = kernarg_here<SkewerArgs>();   // what a line reads once
+      const int np = la->npix[q];
+      const int64_t off = la->offset[q];
+      const double chi0 = la->chi0[q];
       int ns = 1;
       while (ns < np) ns <<= 1;
-      const bool with_ds = (gather || a.ds_in_apply) && a.ps_amp > 0.0 && ns >= 2;
+      const bool with_ds = (gather || la->ds_in_apply) && la->ps_amp > 0.0 && ns >= 2;
       // delta_S is drawn on lines of next_pow2(npix) <= 2048 pixels (the wave's
       // LDS line): a longer skewer is an input error, marked by NaN in every
       // output and left out of the bins
       if (with_ds && ns > 2 * kHalfMax) {
         const float qnan = __builtin_nanf("");
         for (int j = lane; j < np; j += 64) {
-          if (a.dens) a.dens[off + j] = qnan;
-          if (a.eta) a.eta[off + j] = qnan;
-          if (a.flux) a.flux[off + j] = qnan;
+          if (la->dens) la->dens[off + j] = qnan;
+          if (la->eta) la->eta[off + j] = qnan;
+          if (la->flux) la->flux[off + j] = qnan;
         }
         continue;
       }
       // twiddles from global memory: a copy in LDS would cost this kernel its fourth block per CU
       int dl_lane = lane;
       if constexpr (MODE == kSkGauss) asm volatile("" : "+v"(dl_lane));
-      if (with_ds) small_scale_wave(a, a.ps_amp, a.ps_kcut, a.id_base + q, ns, buf, a.tw2048, dl_lane);
+      if (with_ds) {
+        const LineNoise ps{la->seed, la->dpix, la->ps_edges_k, la->ps_ratio, la->ps_nb, la->ps_fixed_amp};
+        small_scale_wave(ps, la->ps_amp, la->ps_kcut, la->id_base + q, ns, buf, static_cast<const float2*>(la->tw2048), dl_lane);
+      }
       // bin boundaries: jb[b] = first pixel with chi_j < edges[b] (chi_j decreases with j)
       if (want_bins) {
-        bin_bounds(a.chi_edges, a.n_bins, chi0, a.dchi, np, jb, lane);
+        bin_bounds(la->chi_edges, la->n_bins, chi0, la->dchi, np, jb, lane);
         wave_sync();
       }
       int64_t ox = 0, oy = 0, oz = 0, sx = 0, sy = 0, sz = 0;
       if (gather) {
-        ox = a.origin_fx[3 * q];
-        oy = a.origin_fx[3 * q + 1];
-        oz = a.origin_fx[3 * q + 2];
-        sx = a.step_fx[3 * q];
-        sy = a.step_fx[3 * q + 1];
-        sz = a.step_fx[3 * q + 2];
+        ox = la->origin_fx[3 * q];
+        oy = la->origin_fx[3 * q + 1];
+        oz = la->origin_fx[3 * q + 2];
+        sx = la->step_fx[3 * q];
+        sy = la->step_fx[3 * q + 1];
+        sz = la->step_fx[3 * q + 2];
       }
       // wide-angle weights u_p u_q (off-diagonal ones doubled), u = step/|step|
       float wxx = 0.0f, wyy = 0.0f, wzz = 0.0f, wxy = 0.0f, wxz = 0.0f, wyz = 0.0f;
@@ -441,7 +460,7 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : 1) k_skewers(Ske
       // times 2^32 (chi_j / kZTabH = chi0 / kZTabH - j dchi / kZTabH, each term
       // rounded to 2^-32 steps: at most 2^-22 Mpc/h off at j = 2048)
       int64_t zpos[U];
-      const int64_t zstep = llrint(a.dchi * (4294967296.0 / kZTabH));
+      const int64_t zstep = llrint(la->dchi * (4294967296.0 / kZTabH));
       if (a.do_flux) {
         const int64_t z0 = llrint(chi0 * (4294967296.0 / kZTabH));
 #pragma unroll
@@ -459,7 +478,7 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : 1) k_skewers(Ske
       // pixel j is in bin b when jb[b+1] <= j < jb[b]; each lane walks j upward
       // and therefore the bins downward, accumulating one bin at a time.  U
       // pixels per lane per step: all their gathers are issued before any is used.
-      int bin = a.n_bins - 1;
+      int bin = la->n_bins - 1;
       int cur = -1;
       unsigned long long acc = 0ull, cnt = 0ull;
       // Gaussian mode: the geometry of the next 64 pixels, and their cells on the way
@@ -695,10 +714,11 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : 1) k_skewers(Ske
   }
   if (want_bins) {
     __syncthreads();
+    const int copy = static_cast<int>(blockIdx.x % kBinCopies) * kMaxZBins;
     for (int b = tid; b < a.n_bins; b += kSkNT) {
       if (s_cnt[b]) {
-        atomicAdd(&a.bin_sum[b], s_sum[b]);
-        atomicAdd(&a.bin_cnt[b], s_cnt[b]);
+        atomicAdd(&a.bin_sum[copy + b], s_sum[b]);
+        atomicAdd(&a.bin_cnt[copy + b], s_cnt[b]);
       }
     }
   }
@@ -741,12 +761,13 @@ void launch_skewer_kernel(const SkewerArgs& a, int u, dim3 grid, hipStream_t st)
 
 hipError_t launch_skewers(SkewerArgs a, hipStream_t st) {
   int64_t blocks = static_cast<int64_t>(device_cus()) * (a.blocks_per_cu > 0 ? a.blocks_per_cu : 4);
-  // no more skewers per pull than leave every wave of the grid one: 500
-  // skewers of 256 pixels in pulls of 4 ran on 125 waves, four in a row each
-  // (39.5 us; one per wave 18.6 us); from 4 skewers per wave up the tuned pull stays
-  a.chunk = static_cast<int>(std::min<int64_t>(a.chunk, std::max<int64_t>(1, a.n_sk / (blocks * kSkWaves))));
-  const int64_t nchunks = (a.n_sk + a.chunk - 1) / a.chunk;
-  if (blocks * kSkWaves > nchunks) blocks = (nchunks + kSkWaves - 1) / kSkWaves;
+  // no more skewers per pull than leave every wave of the grid eight pulls: longer
+  // ones leave it uneven at the end (35M stored pixels of 50,000 skewers 568 us in
+  // pulls of 4, 482 us one by one), and 500 skewers of 256 pixels in pulls of 4 ran
+  // on 125 waves, four in a row each (39.5 us; one per wave 18.6 us)
+  a.chunk = static_cast<int>(std::min<int64_t>(a.chunk, std::max<int64_t>(1, a.n_sk / (8 * blocks * kSkWaves))));
+  a.chunks = (a.n_sk + a.chunk - 1) / a.chunk;
+  if (blocks * kSkWaves > a.chunks) blocks = (a.chunks + kSkWaves - 1) / kSkWaves;
   if (blocks < 1) blocks = 1;
   // with at most a skewer per wave the pass is one skewer's latency: the gathers of
   // four steps of 64 pixels go out together instead of step by step (18.6 ->

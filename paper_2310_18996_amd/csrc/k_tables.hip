@@ -225,7 +225,7 @@ __device__ __forceinline__ double z_of_chi_group(double chi, double om, int l) {
 
 // What a call needs before its main kernel, in one launch (each of these was
 // a launch of 4-5 us of its own): the z(chi) table (ztab), the 2048 twiddles
-// (tw), and the work-queue counter and bin sums cleared (queue, bsum, bcnt;
+// (tw), and the work queue and bin sums cleared (queue, bsum, bcnt;
 // ordinary stores, no memset node).  Null pointers are left out.  The table's
 // blocks come first and in decreasing chi (the far nodes take the most steps).
 constexpr int kPrepNT = 256;
@@ -252,10 +252,10 @@ __global__ void __launch_bounds__(kPrepNT) k_prep(PrepArgs a) {
     a.tw[k] = make_float2(static_cast<float>(cs), static_cast<float>(sn));
     return;
   }
-  if (t == 0 && a.queue) a.queue[0] = 0u;
-  if (t < kMaxZBins && a.bsum) {
-    a.bsum[t] = 0ull;
-    a.bcnt[t] = 0ull;
+  if (t < kPullCounters && a.queue) a.queue[t * kPullStride] = 0u;
+  for (int i = t; i < kBinCopies * kMaxZBins && a.bsum; i += kPrepNT) {
+    a.bsum[i] = 0ull;
+    a.bcnt[i] = 0ull;
   }
 }
 

@@ -19,6 +19,7 @@
 
 #include "lya_internal.h"
 #include "lya_linesum.h"
+#include "lya_pull.h"
 #include "lya_wavefft.h"
 
 namespace lya {
@@ -31,7 +32,7 @@ constexpr int kTeReg = 32;  // pixels per lane kept in registers (2048 per wave)
 __global__ void __launch_bounds__(256) k_te_prep(TuneEvalArgs a) {
   __shared__ unsigned short smt[kLenClasses * mode_row(kMaxKBins)];
   const int g = blockIdx.x, n = kLenClasses * mode_row(a.nk);
-  if (g == 0 && threadIdx.x == 0) a.queue[0] = 0u;
+  if (g == 0 && threadIdx.x < kPullCounters) a.queue[threadIdx.x * kPullStride] = 0u;
   mode_table(smt, a.k_edges, a.nk, a.dv[g], threadIdx.x, 256);
   __syncthreads();
   for (int i = threadIdx.x; i < n; i += 256) a.modes[g * n + i] = smt[i];
@@ -42,7 +43,7 @@ __global__ void __launch_bounds__(256) k_te_prep(TuneEvalArgs a) {
 // powers take the transform's place in LDS), k bins from the draws' tables of
 // first modes, a line's bin sums written in one piece.  64 draws on 14M pixels of
 // 20,000 lines: 5.20 ms with FP64 bin searches per line and draw, two blocks per CU
-// and run-time transform lengths, 2.45 ms.
+// and run-time transform lengths, 2.45 ms; 2.05 ms with the queue on 16 cache lines.
 template <bool DS>
 __global__ void __launch_bounds__(kTeNT, 3) k_tune_eval(TuneEvalArgs a) {
   __shared__ float2 sbuf[kTeWaves][kHalfBuf];
@@ -55,14 +56,12 @@ __global__ void __launch_bounds__(kTeNT, 3) k_tune_eval(TuneEvalArgs a) {
   float* bf = reinterpret_cast<float*>(buf);
   const int nk = a.nk, row = mode_row(nk), lg = bin_split(nk);
   const int64_t ld = a.n_sk;
-  for (;;) {
-    int c = 0;
-    if (lane == 0) c = static_cast<int>(atomicAdd(a.queue, 1u));
-    c = __builtin_amdgcn_readfirstlane(__shfl(c, 0));
-    const int64_t q0 = static_cast<int64_t>(static_cast<uint32_t>(c)) * a.chunk;  // pulls stay below 2^32
-    if (q0 >= a.n_sk) break;
+  LinePull<TuneEvalArgs, kTeWaves> pull;
+  for (int64_t c = pull.first(lane); c < a.chunks; c = pull.next(lane)) {
+    const int64_t q0 = c * a.chunk;
     const int64_t q1 = q0 + a.chunk < a.n_sk ? q0 + a.chunk : a.n_sk;
     for (int64_t q = q0; q < q1; ++q) {
+      if (q == q1 - 1) pull.ask(lane);
       const int np = a.npix[q];
       const int64_t off = a.offset[q];
       const int cls = len_class(np);
@@ -172,9 +171,10 @@ hipError_t launch_tune_eval(const TuneEvalArgs& p, double* rows, float* rows32, 
   a.modes = reinterpret_cast<int*>(a.aux);
   LYA_TIMED("tune_eval_prep", st, hipLaunchKernelGGL(k_te_prep, dim3(a.G), dim3(256), 0, st, a));
   int64_t blocks = static_cast<int64_t>(device_cus()) * 3;
-  a.chunk = static_cast<int>(std::min<int64_t>(a.chunk, std::max<int64_t>(1, a.n_sk / (blocks * kTeWaves))));
-  const int64_t nchunks = (a.n_sk + a.chunk - 1) / a.chunk;
-  if (blocks * kTeWaves > nchunks) blocks = (nchunks + kTeWaves - 1) / kTeWaves;
+  // eight pulls per wave or more, so that the waves end together
+  a.chunk = static_cast<int>(std::min<int64_t>(a.chunk, std::max<int64_t>(1, a.n_sk / (8 * blocks * kTeWaves))));
+  a.chunks = (a.n_sk + a.chunk - 1) / a.chunk;
+  if (blocks * kTeWaves > a.chunks) blocks = (a.chunks + kTeWaves - 1) / kTeWaves;
   if (blocks < 1) blocks = 1;
   const dim3 grid(static_cast<unsigned>(blocks));
   if (a.n_sk > 0 && a.with_ds)

@@ -86,9 +86,9 @@ SkCarve carve_sk() {
   size_t o = 0;
   c.ztab = o;  o += align256(sizeof(float) * lya::kZTabN);
   c.tw = o;    o += align256(sizeof(float2) * lya::kTw2048);
-  c.queue = o; o += 256;
-  c.bsum = o;  o += align256(sizeof(unsigned long long) * lya::kMaxZBins);
-  c.bcnt = o;  o += align256(sizeof(unsigned long long) * lya::kMaxZBins);
+  c.queue = o; o += lya::kPullBytes;
+  c.bsum = o;  o += align256(sizeof(unsigned long long) * lya::kBinCopies * lya::kMaxZBins);
+  c.bcnt = o;  o += align256(sizeof(unsigned long long) * lya::kBinCopies * lya::kMaxZBins);
   c.total = o;
   return c;
 }
@@ -324,7 +324,7 @@ PdCarve carve_p1d(int64_t n_sk, int nk) {
   c.sum = o;   o += align256(sizeof(double) * static_cast<size_t>(n_sk) * nk);
   c.aux = o;   o += align256(std::max(sizeof(int) * static_cast<size_t>(n_sk) * nk, lya::line_sum_bytes(n_sk, nk, 1)));
   c.tw = o;    o += align256(sizeof(float2) * lya::kTw2048);
-  c.queue = o; o += 256;
+  c.queue = o; o += lya::kPullBytes;
   c.total = o;
   return c;
 }

@@ -76,8 +76,14 @@ int device_cus();
 double growth_lcdm(double z, double om);
 
 hipError_t launch_pk_table(const PkParams& p, int n, double dx, TableWork& w, hipStream_t st);
+// A work queue: kPullCounters counters kPullStride words apart, and the copies of
+// the bin sums that a skewer kernel's blocks add to (block b to copy b mod
+// kBinCopies: additions to one cache line are served one by one).
+constexpr int kPullCounters = 16, kPullStride = 32;
+constexpr size_t kPullBytes = sizeof(unsigned int) * kPullCounters * kPullStride;
+constexpr int kBinCopies = 16;
 // One launch for what precedes a call's main kernel: z(chi) table, the
-// kTw2048 twiddles, cleared work-queue counter and kMaxZBins bin sums (null
+// kTw2048 twiddles, cleared work queue and kBinCopies x kMaxZBins bin sums (null
 // pointers are left out).
 struct PrepArgs {
   double omega_m;
@@ -162,7 +168,7 @@ struct SkewerArgs {
   // redshift bins
   int n_bins;
   const double* chi_edges;
-  unsigned long long* bin_sum;  // workspace, fixed point F * 2^32
+  unsigned long long* bin_sum;  // workspace [kBinCopies][kMaxZBins], fixed point F * 2^32
   unsigned long long* bin_cnt;
   double* out_fsum;
   int64_t* out_count;
@@ -170,7 +176,8 @@ struct SkewerArgs {
   const float* ztab;
   const float2* tw2048;
   unsigned int* queue;
-  int chunk;
+  int chunk;          // lines per pull
+  int64_t chunks;     // pulls (set at the launch)
   int blocks_per_cu;  // persistent blocks per CU (<= 0: 4)
   int unroll;         // pixels per lane per step: 1, 2 or 4 (other values: 2)
 };
@@ -197,7 +204,8 @@ struct P1dArgs {
   char* aux;                 // workspace: line_sum_bytes(n_sk, n_kbins, 1)
   const float2* tw2048;
   unsigned int* queue;
-  int chunk;
+  int chunk;          // lines per pull
+  int64_t chunks;     // pulls (set at the launch)
 };
 hipError_t launch_p1d(const P1dArgs& a, double* psum, int64_t* pcount, hipStream_t st);
 
@@ -221,7 +229,8 @@ struct TuneEvalArgs {
   int* modes;                     // (in aux) [G] tables of first modes per length class
   const float2* tw2048;
   unsigned int* queue;
-  int chunk;
+  int chunk;          // lines per pull
+  int64_t chunks;     // pulls (set at the launch)
   // delta_S redrawn per draw (with_ds): P_s(k) = ds_amp[g] exp(-(k/ds_kcut[g])^2)
   // on every skewer (Philox key seed, line id_base + q, pixel length dpix),
   // added to dens before the FGPA; skewers above 2048 pixels then give NaN

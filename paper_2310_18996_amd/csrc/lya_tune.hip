@@ -35,7 +35,7 @@ TuneCarve carve_tune(int64_t n_sk, int nk) {
   const size_t G = kTuneEvalMaxG, S = static_cast<size_t>(n_sk > 0 ? n_sk : 1);
   size_t o = 0;
   c.tw = o;     o += al256(sizeof(float2) * kTw2048);
-  c.queue = o;  o += 256;
+  c.queue = o;  o += kPullBytes;
   c.fs = o;     o += al256(sizeof(double) * G * S);
   c.ps = o;     o += al256(sizeof(double) * G * nk * S);
   c.aux = o;    o += al256(std::max(sizeof(int) * G * nk * S, tune_eval_aux_bytes(n_sk, nk)));
