@@ -329,6 +329,8 @@ struct QsoDrawArgs {
   float dx, oz, dx3;
   double dx_d, o[3];
   float l2z[3];           // log2(1 + z_i)
+  float zb[3];            // z_i, and tiles of 64 x 8 voxels per wave (set at the launch)
+  int tiles;
   const float4* tab;      // {z, c_1, c_2, c_3} per kZTabH of comoving distance
   int n_nbar;
   const double* nbar_z;

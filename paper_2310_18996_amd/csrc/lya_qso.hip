@@ -188,24 +188,43 @@ hipError_t launch_lognormal(const PkParams& p, const LognormalArgs& a, hipStream
 }
 
 // ---- box moments ----
-// Per block: sums of re, re^2, im, im^2 over rows (x, y) of the box.
-__global__ void __launch_bounds__(256) k_box_moments(const float2* __restrict__ box, int n, size_t pitch,
-                                                     double* __restrict__ part) {
+// Per block: sums of re, re^2, im, im^2 over segments of 1024 cells (each in one
+// plane: n^2 is a multiple), two cells per 16-byte load (planes start 16-byte
+// aligned), kMomSegs segments' loads in flight.  Bound by reading the box: 1024^3 in
+// 1.49 ms, with NT (non-temporal loads) 1.27 ms.
+constexpr int kMomSeg = 1024, kMomSegs = 4;
+// NT where a box is beyond the 256 MB last-level cache: no read of it would find
+// anything there, and not allocating there is faster.
+bool box_streams(int n) { return sizeof(float2) * box_elems(n) > (size_t(256) << 20); }
+template <bool NT>
+__global__ void __launch_bounds__(256) k_box_moments(const float2* __restrict__ box, int log2n2, size_t pitch,
+                                                     int64_t segs, double* __restrict__ part) {
+  constexpr int SEGS = kMomSegs;
+  typedef float f4 __attribute__((ext_vector_type(4)));
   __shared__ double red[4];
   double s[4] = {0.0, 0.0, 0.0, 0.0};
-  const int64_t rows = static_cast<int64_t>(n) * n;
-  for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
-    // two cells per 16-byte load (rows start 16-byte aligned: n and the
-    // plane pitch are multiples of 4)
-    const float4* q = reinterpret_cast<const float4*>(box + static_cast<size_t>(row / n) * pitch +
-                                                      static_cast<size_t>(row % n) * n);
-#pragma unroll 2
-    for (int i = threadIdx.x; i < n / 2; i += 256) {
-      const float4 v = q[i];
-      s[0] += static_cast<double>(v.x) + v.z;
-      s[1] += static_cast<double>(v.x) * v.x + static_cast<double>(v.z) * v.z;
-      s[2] += static_cast<double>(v.y) + v.w;
-      s[3] += static_cast<double>(v.y) * v.y + static_cast<double>(v.w) * v.w;
+  const size_t pad = pitch - (static_cast<size_t>(1) << log2n2);
+  for (int64_t g = blockIdx.x; g < segs; g += static_cast<int64_t>(gridDim.x) * SEGS) {
+    f4 v[SEGS][2];
+#pragma unroll
+    for (int k = 0; k < SEGS; ++k) {
+      const int64_t gk = g + static_cast<int64_t>(gridDim.x) * k;
+      const size_t c = static_cast<size_t>(gk < segs ? gk : g) * kMomSeg;
+      const f4* q = reinterpret_cast<const f4*>(box + c + (c >> log2n2) * pad) + threadIdx.x;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) v[k][h] = NT ? __builtin_nontemporal_load(q + 256 * h) : q[256 * h];
+    }
+#pragma unroll
+    for (int k = 0; k < SEGS; ++k) {
+      if (g + static_cast<int64_t>(gridDim.x) * k >= segs) break;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const f4 w = v[k][h];
+        s[0] += static_cast<double>(w.x) + w.z;
+        s[1] += static_cast<double>(w.x) * w.x + static_cast<double>(w.z) * w.z;
+        s[2] += static_cast<double>(w.y) + w.w;
+        s[3] += static_cast<double>(w.y) * w.y + static_cast<double>(w.w) * w.w;
+      }
     }
   }
 #pragma unroll
@@ -238,8 +257,12 @@ __global__ void __launch_bounds__(256) k_box_moments_final(const double* __restr
 }
 
 hipError_t launch_box_moments(const float2* box, int n, double* part, double* out, hipStream_t st) {
+  int log2n2 = 0;
+  while ((int64_t(1) << log2n2) < static_cast<int64_t>(n) * n) ++log2n2;
+  const int64_t segs = static_cast<int64_t>(n) * n * n / kMomSeg;
   LYA_TIMED("box_moments", st,
-            hipLaunchKernelGGL(k_box_moments, dim3(kQsoMomBlocks), dim3(256), 0, st, box, n, plane_pitch(n), part));
+            hipLaunchKernelGGL(box_streams(n) ? k_box_moments<true> : k_box_moments<false>, dim3(kQsoMomBlocks), dim3(256),
+                               0, st, box, log2n2, plane_pitch(n), segs, part));
   const double inv = 1.0 / (static_cast<double>(n) * n * n);
   LYA_TIMED("box_moments_final", st,
             hipLaunchKernelGGL(k_box_moments_final, dim3(1), dim3(256), 0, st, part, kQsoMomBlocks, inv, out));
@@ -280,46 +303,149 @@ __global__ void __launch_bounds__(256) k_qso_coef(const float* __restrict__ ztab
 }
 
 // ---- the draw ----
-// One thread per VPT consecutive voxels along z (one Philox call gives the
-// decision uniforms of four).  Selected voxels are appended with one atomic per
-// wave; a slot at or beyond cap is counted but not written.
+// A thread takes VPT consecutive voxels along z at a time (one Philox call gives
+// the decision uniforms of four), a wave `tiles` times 64 VPT of them.  Selected
+// voxels wait in the wave's LDS list and leave it with one atomic on the count per
+// flush (one per tile was an atomic per quasar, and additions to one cache line
+// take 11.5 ns each); a slot at or beyond cap is counted but not written.
 // The transcendentals run on the hardware units (v_sqrt_f32, v_log_f32,
 // v_exp_f32: about 1 ulp each); the exponent's own rounding, |x| 2^-24 for
 // |x| up to about 10, dominates the error of p (a few 1e-7 relative).
+//
+// Almost every voxel is rejected (p about 1e-4), so p itself is formed only where
+// an upper bound does not already reject (qso_bound): Philox, two FMAs, a maximum
+// and a comparison per box and voxel in place of 8 transcendentals and two table
+// gathers.  1024^3, three boxes: 6.52 ms bound by vector issue and by the L1, 3.07 ms
+// (reading the boxes takes 2.6).
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kQsoVpt = 8;      // voxels per thread (consecutive along z)
-constexpr int kQsoBlock = 256;  // threads per block (512: 59 ms against 54.5 at 2048^3)
+constexpr int kQsoVpt = 8;      // voxels per thread and tile (consecutive along z)
+constexpr int kQsoBlock = 256;
+constexpr int kQsoMaxTiles = 64;
+constexpr int kQsoFlush = 256;
+constexpr int kQsoList = 768;   // per wave: flushed above kQsoFlush, a tile adds at most 512
 
-template <int NB, int VPT>
-__global__ void __launch_bounds__(kQsoBlock) k_qso_draw(QsoDrawArgs a) {
-  static_assert(VPT % 4 == 0, "whole Philox calls per thread");
-  __shared__ float snz[kQsoMaxNbar], snb[kQsoMaxNbar];
-  const int n = a.n;
-  // thread t of block b takes voxels v0 .. v0 + VPT - 1 along z, v0 = VPT (kQsoBlock b + t)
-  const uint64_t g = static_cast<uint64_t>(blockIdx.x) * kQsoBlock + threadIdx.x;
-  const uint64_t v0 = g * VPT;
-  // n is a power of two: shifts and masks instead of 64-bit divisions
-  const uint64_t row = v0 >> a.log2n;
-  const int iz0 = static_cast<int>(v0 & static_cast<uint64_t>(n - 1));
-  const int ix = static_cast<int>(row >> a.log2n), iy = static_cast<int>(row & static_cast<uint64_t>(n - 1));
-  const size_t e0 = static_cast<size_t>(ix) * a.pitch + static_cast<size_t>(iy) * n + iz0;
+// Voxel (ix, iy, iz0) .. + VPT - 1 along z.
+struct QsoCell {
+  int ix, iy, iz0;
+  __device__ __forceinline__ QsoCell(const QsoDrawArgs& a, uint64_t v0) {
+    // n is a power of two: shifts and masks instead of 64-bit divisions
+    const uint64_t row = v0 >> a.log2n;
+    iz0 = static_cast<int>(v0 & static_cast<uint64_t>(a.n - 1));
+    ix = static_cast<int>(row >> a.log2n);
+    iy = static_cast<int>(row & static_cast<uint64_t>(a.n - 1));
+  }
+  __device__ __forceinline__ float r2xy(const QsoDrawArgs& a) const {
+    const float rx = static_cast<float>(ix * a.dx_d - a.o[0]);
+    const float ry = static_cast<float>(iy * a.dx_d - a.o[1]);
+    return rx * rx + ry * ry;
+  }
+};
 
-  // the field loads first, so that their latency overlaps the block's
-  // set-up (nbar into LDS, the variances) and the Philox rounds
-  float d[NB][VPT];
+// Bound of VPT voxels: p = nb dx^3 sum_i c_i 2^(x_i), x_i = log2(e) (al_i d_i -
+// al_i^2 var_i / 2), is below u wherever log2 u >= max(lo_i d_i, hi_i d_i) + add_i
+// for every box i, since the voxels' al_i lie between lo_i and hi_i (over log2 e),
+// their c_i below the largest that any weight 0 <= w <= 1 gives between the ends'
+// redshifts, and nb below nb_top.  Redshift ends: the table nodes around the
+// voxels' distances; all else is widened by a few parts in 10^6 (above every
+// rounding of the exact evaluation) and 1e-3 in the exponent.  A NaN anywhere makes
+// a comparison false, which keeps the voxel.
+template <int NB>
+struct QsoBound {
+  float lo[NB], hi[NB], add[NB];
+};
+template <int VPT>
+__device__ __forceinline__ float2 qso_ends(const QsoDrawArgs& a, float r2xy, int iz0) {
+  const float ra = static_cast<float>(iz0) * a.dx - a.oz, rb = static_cast<float>(iz0 + VPT - 1) * a.dx - a.oz;
+  const float r_lo = ra <= 0.0f && rb >= 0.0f ? 0.0f : fminf(ra * ra, rb * rb), r_hi = fmaxf(ra * ra, rb * rb);
+  const float per_h = 1.0f / static_cast<float>(kZTabH);
+  const float t_lo = __builtin_amdgcn_sqrtf(r2xy + r_lo) * per_h * (1.0f - 4e-6f);
+  const float t_hi = __builtin_amdgcn_sqrtf(r2xy + r_hi) * per_h * (1.0f + 4e-6f);
+  return make_float2(a.tab[min(static_cast<int>(t_lo), kZTabN - 2)].x,
+                     a.tab[min(static_cast<int>(t_hi), kZTabN - 2) + 1].x);
+}
+template <int NB>
+__device__ __forceinline__ QsoBound<NB> qso_bound(const QsoDrawArgs& a, float2 ends, const float (&hv)[NB], float nb_top) {
+  const float z_lo = ends.x - 2e-5f, z_hi = ends.y + 2e-5f;
+  const float l_lo = __log2f(1.0f + z_lo), l_hi = __log2f(1.0f + z_hi);
+  float c = 1.0f;
+  if (NB == 3) {
+    const float i12 = 1.0f / (a.zb[1 % NB] - a.zb[0]), i23 = 1.0f / (a.zb[2 % NB] - a.zb[1 % NB]);
+    const float c0 = (a.zb[1 % NB] - z_lo) * i12, c2 = (z_hi - a.zb[1 % NB]) * i23;
+    const float c1 = fmaxf((z_hi - a.zb[0]) * i12, (a.zb[2 % NB] - z_lo) * i23);
+    c = fmaxf(c0, 0.0f) + fmaxf(c1, 0.0f) + fmaxf(c2, 0.0f);
+  }
+  // (not below 2^-127: there a p that overflows its factors is kept as well)
+  const float top = fmaxf(__log2f(nb_top * a.dx3 * c) + 1e-3f, -127.0f);
+  QsoBound<NB> b;
 #pragma unroll
-  for (int h = 0; h < VPT / 2; ++h) {
-    const float4 v = *reinterpret_cast<const float4*>(a.box_a + e0 + 2 * h);
-    d[0][2 * h] = v.x;
-    d[0][2 * h + 1] = v.z;
-    if (NB == 3) {
-      const float4 w = *reinterpret_cast<const float4*>(a.box_b + e0 + 2 * h);
-      d[1 % NB][2 * h] = v.y;
-      d[1 % NB][2 * h + 1] = v.w;
-      d[2 % NB][2 * h] = w.x;
-      d[2 % NB][2 * h + 1] = w.z;
+  for (int i = 0; i < NB; ++i) {
+    const float al_lo = __builtin_amdgcn_exp2f(0.7f * (l_lo - a.l2z[i])) * (1.0f - 4e-6f);
+    const float al_hi = __builtin_amdgcn_exp2f(0.7f * (l_hi - a.l2z[i])) * (1.0f + 4e-6f);
+    b.lo[i] = kLog2e * al_lo;
+    b.hi[i] = kLog2e * al_hi;
+    b.add[i] = top - kLog2e * (hv[i] >= 0.0f ? al_lo * al_lo : al_hi * al_hi) * hv[i];
+  }
+  return b;
+}
+
+// p of one voxel against u, the field values d.
+template <int NB>
+__device__ __forceinline__ bool qso_selected(const QsoDrawArgs& a, float r2xy, int iz, const float (&d)[NB],
+                                             const float (&hv)[NB], float nb_top, float u, const float* snz,
+                                             const float* snb) {
+  const float rz = static_cast<float>(iz) * a.dx - a.oz;
+  const float chi = __builtin_amdgcn_sqrtf(r2xy + rz * rz);
+  const float t = chi * (1.0f / static_cast<float>(kZTabH));
+  const int i0 = min(static_cast<int>(t), kZTabN - 2);
+  const float fr = t - static_cast<float>(i0);
+  const float4 c0 = a.tab[i0], c1 = a.tab[i0 + 1];
+  const float z = c0.x + fr * (c1.x - c0.x);
+  const float cf[3] = {c0.y + fr * (c1.y - c0.y), c0.z + fr * (c1.z - c0.z), c0.w + fr * (c1.w - c0.w)};
+  const float lz = __log2f(1.0f + z);
+  float acc;
+  if (NB == 1) {
+    const float al = __builtin_amdgcn_exp2f(0.7f * (lz - a.l2z[0]));
+    acc = __builtin_amdgcn_exp2f(kLog2e * (al * d[0] - al * al * hv[0]));
+  } else {
+    acc = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const float al = __builtin_amdgcn_exp2f(0.7f * (lz - a.l2z[i]));
+      acc += cf[i] * __builtin_amdgcn_exp2f(kLog2e * (al * d[i] - al * al * hv[i]));
     }
   }
+  // p <= nb_top dx^3 acc (rounding is monotone): most are rejected on that
+  // bound before nbar(z) is looked up
+  if (!(u < fminf(nb_top * a.dx3 * acc, 1.0f))) return false;
+  // nbar(z): linear between the nodes, zero outside
+  float nb = 0.0f;
+  if (z >= snz[0] && z <= snz[a.n_nbar - 1]) {
+    int lo = 0, hi = a.n_nbar - 1;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (snz[mid] <= z) lo = mid; else hi = mid;
+    }
+    const float span = snz[hi] - snz[lo];
+    nb = span > 0.0f ? snb[lo] + (snb[hi] - snb[lo]) * ((z - snz[lo]) / span) : snb[lo];
+  }
+  return u < fminf(nb * a.dx3 * acc, 1.0f);
+}
+
+// 16 bytes per lane from memory to LDS, lane after lane from dst (the same in all lanes).
+template <bool NT>
+__device__ __forceinline__ void to_lds(const void* src, const void* dst) {
+  __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) const void*)src,
+                                   (__attribute__((address_space(3))) void*)dst, 16, 0, NT ? 2 : 0);
+}
+
+template <int NB, int VPT, bool NT>
+__global__ void __launch_bounds__(kQsoBlock) k_qso_draw(QsoDrawArgs a) {
+  static_assert(VPT % 4 == 0 && 64 * VPT + kQsoFlush <= kQsoList && 64 * VPT * kQsoMaxTiles <= 65536, "list entries");
+  __shared__ float snz[kQsoMaxNbar], snb[kQsoMaxNbar];
+  __shared__ uint16_t slist[kQsoBlock / 64][kQsoList];
+  __shared__ float4 sbox[kQsoBlock / 64][NB == 3 ? 2 : 1][64 * VPT / 2];
+  const int lane = threadIdx.x & 63;
+  uint16_t* list = slist[threadIdx.x >> 6];
   for (int i = threadIdx.x; i < a.n_nbar; i += kQsoBlock) {
     snz[i] = static_cast<float>(a.nbar_z[i]);
     snb[i] = static_cast<float>(a.nbar[i]);
@@ -327,132 +453,157 @@ __global__ void __launch_bounds__(kQsoBlock) k_qso_draw(QsoDrawArgs a) {
   float hv[NB];
 #pragma unroll
   for (int i = 0; i < NB; ++i) hv[i] = 0.5f * static_cast<float>(*a.var[i]);
-  // distance, z and the three-box coefficients of the voxels (table loads
-  // issued before the barrier as well)
-  const float rx = static_cast<float>(ix * a.dx_d - a.o[0]);
-  const float ry = static_cast<float>(iy * a.dx_d - a.o[1]);
-  const float r2xy = rx * rx + ry * ry;
-  float zv[VPT], cfv[VPT][3];
-#pragma unroll
-  for (int e = 0; e < VPT; ++e) {
-    const float rz = static_cast<float>(iz0 + e) * a.dx - a.oz;
-    const float chi = __builtin_amdgcn_sqrtf(r2xy + rz * rz);
-    const float t = chi * (1.0f / static_cast<float>(kZTabH));
-    const int i0 = min(static_cast<int>(t), kZTabN - 2);
-    const float fr = t - static_cast<float>(i0);
-    const float4 c0 = a.tab[i0], c1 = a.tab[i0 + 1];
-    zv[e] = c0.x + fr * (c1.x - c0.x);
-    cfv[e][0] = c0.y + fr * (c1.y - c0.y);
-    cfv[e][1] = c0.z + fr * (c1.z - c0.z);
-    cfv[e][2] = c0.w + fr * (c1.w - c0.w);
-  }
-  // decision words: voxel m takes word m & 3 of the call for counter m >> 2
-  uint32_t words[VPT];
-#pragma unroll
-  for (int c = 0; c < VPT / 4; ++c) {
-    const uint64_t ctr = (v0 >> 2) + c;
-    const uint4 wd = philox10_x3(make_uint4(static_cast<uint32_t>(ctr), static_cast<uint32_t>(ctr >> 32), 2u, 0u),
-                                 static_cast<uint32_t>(a.seed), static_cast<uint32_t>(a.seed >> 32));
-    words[4 * c] = wd.x;
-    words[4 * c + 1] = wd.y;
-    words[4 * c + 2] = wd.z;
-    words[4 * c + 3] = wd.w;
-  }
   __syncthreads();
   // the largest density, raised by a margin over the rounding of the
   // interpolation between two nodes
   float nb_top = 0.0f;
-  for (int i = static_cast<int>(threadIdx.x & 63); i < a.n_nbar; i += 64) nb_top = fmaxf(nb_top, snb[i]);
+  for (int i = lane; i < a.n_nbar; i += 64) nb_top = fmaxf(nb_top, snb[i]);
 #pragma unroll
   for (int w = 32; w >= 1; w >>= 1) nb_top = fmaxf(nb_top, __shfl_xor(nb_top, w));  // over the wave
   nb_top *= 1.0f + 1.0e-6f;
 
-  bool sel[VPT];
+  const uint64_t wave = static_cast<uint64_t>(blockIdx.x) * (kQsoBlock / 64) + (threadIdx.x >> 6);
+  const uint64_t w0 = wave * static_cast<uint64_t>(a.tiles) * (64 * VPT);   // the wave's first voxel
+  // A tile comes through LDS, its loads issued while the one before is worked on:
+  // lanes take neighbouring 16-byte pieces of the box there (a thread's own 64 bytes
+  // would be four loads that each touch 64 cache lines), in an order that lets the
+  // threads read theirs back without bank conflicts: piece h of thread l in slot
+  // 4 l + (h ^ (l / 2 mod 4)).  A tile lies in one x plane (n^2 is a multiple of it).
+  static_assert(VPT == 8, "four pieces per thread");
+  const int swz = (lane >> 1) & 3;
+  const float4* sa = sbox[threadIdx.x >> 6][0];
+  const float4* sb = sbox[threadIdx.x >> 6][NB == 3 ? 1 : 0];
+  const int mine = 8 * (lane >> 2) + 2 * ((lane & 3) ^ ((lane >> 3) & 3));
+  const auto fetch = [&](int tile) {
+    const uint64_t vt = w0 + static_cast<uint64_t>(tile) * (64 * VPT);
+    const size_t et = static_cast<size_t>(vt) +
+                      static_cast<size_t>(vt >> (2 * a.log2n)) * (a.pitch - static_cast<size_t>(a.n) * a.n) + mine;
 #pragma unroll
-  for (int e = 0; e < VPT; ++e) {
-    const float z = zv[e];
-    const float lz = __log2f(1.0f + z);
-    float acc;
-    if (NB == 1) {
-      const float al = __builtin_amdgcn_exp2f(0.7f * (lz - a.l2z[0]));
-      acc = __builtin_amdgcn_exp2f(kLog2e * (al * d[0][e] - al * al * hv[0]));
-    } else {
-      acc = 0.0f;
+    for (int i = 0; i < VPT / 2; ++i) {
+      to_lds<NT>(a.box_a + et + 128 * i, sa + 64 * i);
+      if (NB == 3) to_lds<NT>(a.box_b + et + 128 * i, sb + 64 * i);
+    }
+  };
+  fetch(0);
+  int cnt = 0;   // list entries (uniform)
+  for (int tile = 0; tile < a.tiles; ++tile) {
+    const uint32_t o0 = static_cast<uint32_t>((tile * 64 + lane) * VPT);
+    const uint64_t v0 = w0 + o0;
+    const QsoCell c(a, v0);
+    const float r2xy = c.r2xy(a);
+    const float2 ends = qso_ends<VPT>(a, r2xy, c.iz0);
+    float d[NB][VPT];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the tile is in LDS
 #pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        const float al = __builtin_amdgcn_exp2f(0.7f * (lz - a.l2z[i]));
-        acc += cfv[e][i] * __builtin_amdgcn_exp2f(kLog2e * (al * d[i][e] - al * al * hv[i]));
+    for (int h = 0; h < VPT / 2; ++h) {
+      const int slot = lane * (VPT / 2) + (h ^ swz);
+      const float4 v = sa[slot];
+      d[0][2 * h] = v.x;
+      d[0][2 * h + 1] = v.z;
+      if (NB == 3) {
+        const float4 w = sb[slot];
+        d[1 % NB][2 * h] = v.y;
+        d[1 % NB][2 * h + 1] = v.w;
+        d[2 % NB][2 * h] = w.x;
+        d[2 % NB][2 * h + 1] = w.z;
       }
     }
-    // p <= nb_top dx^3 acc (rounding is monotone): most voxels are rejected
-    // on that bound before nbar(z) is looked up
-    const float u = u01(words[e]);
-    sel[e] = false;
-    if (u < fminf(nb_top * a.dx3 * acc, 1.0f)) {
-      // nbar(z): linear between the nodes, zero outside
-      float nb = 0.0f;
-      if (z >= snz[0] && z <= snz[a.n_nbar - 1]) {
-        int lo = 0, hi = a.n_nbar - 1;
-        while (hi - lo > 1) {
-          const int mid = (lo + hi) >> 1;
-          if (snz[mid] <= z) lo = mid; else hi = mid;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (tile + 1 < a.tiles) fetch(tile + 1);
+    const QsoBound<NB> b = qso_bound<NB>(a, ends, hv, nb_top);
+    // decision words: voxel m takes word m & 3 of the call for counter m >> 2
+    float u[VPT];
+#pragma unroll
+    for (int k = 0; k < VPT / 4; ++k) {
+      const uint64_t ctr = (v0 >> 2) + k;
+      const uint4 wd = philox10_x3(make_uint4(static_cast<uint32_t>(ctr), static_cast<uint32_t>(ctr >> 32), 2u, 0u),
+                                   static_cast<uint32_t>(a.seed), static_cast<uint32_t>(a.seed >> 32));
+      u[4 * k] = u01(wd.x);
+      u[4 * k + 1] = u01(wd.y);
+      u[4 * k + 2] = u01(wd.z);
+      u[4 * k + 3] = u01(wd.w);
+    }
+    uint32_t left = 0;   // voxels that the bound does not reject
+#pragma unroll
+    for (int e = 0; e < VPT; ++e) {
+      // a float's bits as a number: 2^23 (127 + log2 u) from below (at most 0.09 2^23)
+      const float l2u = fmaf(static_cast<float>(__float_as_int(u[e])), 1.0f / 8388608.0f, -127.0f);
+      bool reject = true;
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        reject = reject && l2u >= fmaxf(fmaf(b.lo[i], d[i][e], b.add[i]), fmaf(b.hi[i], d[i][e], b.add[i]));
+      left |= reject ? 0u : 1u << e;
+    }
+    // one of each lane's at a time
+    while (__any(left != 0u)) {
+      const int e = __ffs(left) - 1;
+      bool sel = false;
+      if (left) {
+        float de[NB], ue = u[0];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) de[i] = d[i][0];
+#pragma unroll
+        for (int k = 1; k < VPT; ++k) {
+          ue = e == k ? u[k] : ue;
+#pragma unroll
+          for (int i = 0; i < NB; ++i) de[i] = e == k ? d[i][k] : de[i];
         }
-        const float span = snz[hi] - snz[lo];
-        nb = span > 0.0f ? snb[lo] + (snb[hi] - snb[lo]) * ((z - snz[lo]) / span) : snb[lo];
+        sel = qso_selected<NB>(a, r2xy, c.iz0 + e, de, hv, nb_top, ue, snz, snb);
+        left &= left - 1u;
       }
-      sel[e] = u < fminf(nb * a.dx3 * acc, 1.0f);
+      const uint64_t m = __ballot(sel);
+      if (sel) list[cnt + __popcll(m & ((1ull << lane) - 1ull))] = static_cast<uint16_t>(o0 + e);
+      cnt += __popcll(m);
     }
-  }
-
-  uint64_t b[VPT];
-  int tot = 0;
-#pragma unroll
-  for (int e = 0; e < VPT; ++e) {
-    b[e] = __ballot(sel[e]);
-    tot += __popcll(b[e]);
-  }
-  if (tot == 0) return;  // uniform over the wave
-  const int lane = threadIdx.x & 63;
-  unsigned long long base = 0;
-  if (lane == 0) base = atomicAdd(a.count, static_cast<unsigned long long>(tot));
-  const uint32_t blo = __shfl(static_cast<uint32_t>(base), 0, 64);
-  const uint32_t bhi = __shfl(static_cast<uint32_t>(base >> 32), 0, 64);
-  base = (static_cast<unsigned long long>(bhi) << 32) | blo;
-  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  unsigned long long before = 0;
-#pragma unroll
-  for (int e = 0; e < VPT; ++e) {
-    if (sel[e]) {
-      const unsigned long long slot = base + before + __popcll(b[e] & below);
-      if (slot < static_cast<unsigned long long>(a.cap)) {
-        const uint64_t m = v0 + e;
+    // (the list is read by other lanes than wrote it)
+    if (cnt > kQsoFlush || (tile == a.tiles - 1 && cnt > 0)) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      unsigned long long base = 0;
+      if (lane == 0) base = atomicAdd(a.count, static_cast<unsigned long long>(cnt));
+      const uint32_t blo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(base));
+      const uint32_t bhi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(base >> 32));
+      base = (static_cast<unsigned long long>(bhi) << 32) | blo;
+      for (int i = lane; i < cnt; i += 64) {
+        const unsigned long long slot = base + i;
+        if (slot >= static_cast<unsigned long long>(a.cap)) break;
+        const uint64_t m = w0 + list[i];
+        const QsoCell q(a, m);
         const uint4 pw = philox10_x3(make_uint4(static_cast<uint32_t>(m), static_cast<uint32_t>(m >> 32), 4u, 0u),
                                      static_cast<uint32_t>(a.seed), static_cast<uint32_t>(a.seed >> 32));
         int64_t* o = a.pos + 3 * slot;
-        o[0] = (static_cast<int64_t>(ix) << 32) - (int64_t(1) << 31) + pw.x;
-        o[1] = (static_cast<int64_t>(iy) << 32) - (int64_t(1) << 31) + pw.y;
-        o[2] = (static_cast<int64_t>(iz0 + e) << 32) - (int64_t(1) << 31) + pw.z;
+        o[0] = (static_cast<int64_t>(q.ix) << 32) - (int64_t(1) << 31) + pw.x;
+        o[1] = (static_cast<int64_t>(q.iy) << 32) - (int64_t(1) << 31) + pw.y;
+        o[2] = (static_cast<int64_t>(q.iz0) << 32) - (int64_t(1) << 31) + pw.z;
       }
+      cnt = 0;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    before += __popcll(b[e]);
   }
 }
 
-hipError_t launch_qso_draw(const QsoCoef& c, const QsoDrawArgs& a, const float* ztab, float4* tab, hipStream_t st) {
+hipError_t launch_qso_draw(const QsoCoef& c, const QsoDrawArgs& p, const float* ztab, float4* tab, hipStream_t st) {
+  QsoDrawArgs a = p;
+  for (int i = 0; i < 3; ++i) a.zb[i] = static_cast<float>(c.z[i]);
   LYA_TIMED("qso_coef", st,
             hipLaunchKernelGGL(k_qso_coef, dim3((kZTabN + 255) / 256), dim3(256), 0, st, ztab, c, tab,
                                a.count));
-  // kQsoBlock threads x kQsoVpt voxels per block: n^3 / (kQsoBlock kQsoVpt) blocks, a
-  // whole number for every supported n (n >= 32), so every wave is full, as
-  // the wave-wide ballots need
-  const uint64_t blocks = static_cast<uint64_t>(a.n) * a.n * a.n / (kQsoBlock * kQsoVpt);
-  if (a.nb == 3) {
-    LYA_TIMED("qso_draw", st, hipLaunchKernelGGL((k_qso_draw<3, kQsoVpt>), dim3(static_cast<unsigned>(blocks)),
-                                                 dim3(kQsoBlock), 0, st, a));
-  } else {
-    LYA_TIMED("qso_draw", st, hipLaunchKernelGGL((k_qso_draw<1, kQsoVpt>), dim3(static_cast<unsigned>(blocks)),
-                                                 dim3(kQsoBlock), 0, st, a));
-  }
+  // n^3 / (64 kQsoVpt) tiles, a power of two from 64 up (n >= 32): a wave takes as
+  // many as leave the device about eight waves per SIMD, 64 at most, and every block
+  // and wave is full
+  const uint64_t all = static_cast<uint64_t>(a.n) * a.n * a.n / (64 * kQsoVpt);
+  const uint64_t waves = static_cast<uint64_t>(device_cus()) * 32;
+  a.tiles = 1;
+  while (a.tiles < kQsoMaxTiles && all / (2 * a.tiles) >= waves) a.tiles *= 2;
+  const uint64_t blocks = all / a.tiles / (kQsoBlock / 64);
+  const bool nt = box_streams(a.n);
+  const auto kernel = a.nb == 3 ? (nt ? k_qso_draw<3, kQsoVpt, true> : k_qso_draw<3, kQsoVpt, false>)
+                                : (nt ? k_qso_draw<1, kQsoVpt, true> : k_qso_draw<1, kQsoVpt, false>);
+  LYA_TIMED("qso_draw", st,
+            hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kQsoBlock), 0, st, a));
   return hipGetLastError();
 }
 
