@@ -1171,7 +1171,7 @@ def main():
         gms = (time.perf_counter() - t2) * 1e3 / 2
         gauss = dict(what="lya_draw_skewers_gauss: 7^3 Gaussian-kernel average (343 voxels per pixel) with "
                           "delta_S, FGPA and bins, same box and skewers", ms=gms, pixels_per_s=pixels / (gms * 1e-3))
-    box_names = ("pk_sigma8", "pk_finalize", "pk_table", "zorder", "fft_z_gen", "fft_y", "fft_x", "fft_x2", "fft_y2")
+    box_names = ("pk_start", "pk_table", "zorder", "fft_z_gen", "fft_y", "fft_x", "fft_x2", "fft_y2")
     sk_names = ("prep", "skewers", "skewer_finalize")
     box_ms = sum(kt[k][0] for k in box_names if k in kt) / args.steps
     sk_ms = sum(kt[k][0] for k in sk_names if k in kt) / args.steps

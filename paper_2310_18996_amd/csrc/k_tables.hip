@@ -46,11 +46,25 @@ constexpr int kSimpsonNodes = 65537;
 constexpr double kLnkMin = -11.512925464970229;  // ln 1e-5
 constexpr double kLnkMax = 6.907755278982137;    // ln 1e3
 
-__global__ void __launch_bounds__(256) k_sigma8_partial(PkParams p, double* partial) {
-  __shared__ double red[256];
+// First launch of a table: the sigma8 integral's partial sums (kSigmaBlocks blocks,
+// one node per thread and the last node with the first block: the nodes' FP64
+// exp, pow, sin and log are the launch's time, 12.7 us at four nodes per thread,
+// 5 at one), then ntw twiddles exp(+2 pi i k / ntw).  What reads the table's
+// amplitude adds the partial sums itself (pk_amplitude); a launch of one block for
+// that cost 5 us.
+__global__ void __launch_bounds__(kSigmaBlocks) k_pk_start(PkParams p, int nsig, double* partial, float2* tw, int ntw) {
+  __shared__ double red[kSigmaBlocks];
+  if (static_cast<int>(blockIdx.x) >= nsig) {
+    const int k = (blockIdx.x - nsig) * kSigmaBlocks + threadIdx.x;
+    if (k >= ntw) return;
+    double sn, cs;
+    sincospi(2.0 * k / ntw, &sn, &cs);
+    tw[k] = make_float2(static_cast<float>(cs), static_cast<float>(sn));
+    return;
+  }
   const double h = (kLnkMax - kLnkMin) / (kSimpsonNodes - 1);
   double acc = 0.0;
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < kSimpsonNodes; i += gridDim.x * 256) {
+  for (int i = blockIdx.x * kSigmaBlocks + threadIdx.x; i < kSimpsonNodes; i += kSigmaBlocks * kSigmaBlocks) {
     const double lnk = kLnkMin + h * i;
     const double k = exp(lnk);
     const double w = w_tophat(8.0 * k);
@@ -59,28 +73,28 @@ __global__ void __launch_bounds__(256) k_sigma8_partial(PkParams p, double* part
   }
   red[threadIdx.x] = acc;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
+  for (int s = kSigmaBlocks / 2; s > 0; s >>= 1) {
     if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
     __syncthreads();
   }
   if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
-// One block: amplitude A into amp[0]; all threads: twiddles exp(+2 pi i k / ntw).
-__global__ void __launch_bounds__(256) k_pk_finalize(PkParams p, const double* partial, int npartial, double* amp,
-                                                     float2* tw, int ntw) {
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int i = 0; i < npartial; ++i) s += partial[i];
-    const double h = (kLnkMax - kLnkMin) / (kSimpsonNodes - 1);
-    const double sig2 = h / 3.0 * s / (2.0 * M_PI * M_PI);
-    amp[0] = p.sigma8 * p.sigma8 / sig2;
-  }
-  for (int k = threadIdx.x; k < ntw; k += 256) {
-    double sn, cs;
-    sincospi(2.0 * k / ntw, &sn, &cs);
-    tw[k] = make_float2(static_cast<float>(cs), static_cast<float>(sn));
-  }
+// Amplitude A of the analytic form from the partial sums, by a block of
+// kSigmaBlocks threads in a fixed order (the same in every block).
+__device__ __forceinline__ double pk_amplitude(const PkParams& p, const double* __restrict__ partial) {
+  __shared__ double red[kSigmaBlocks / 64];
+  double s = partial[threadIdx.x];
+#pragma unroll
+  for (int w = 32; w >= 1; w >>= 1) s += __shfl_xor(s, w);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  s = 0.0;
+#pragma unroll
+  for (int w = 0; w < kSigmaBlocks / 64; ++w) s += red[w];
+  const double h = (kLnkMax - kLnkMin) / (kSimpsonNodes - 1);
+  const double sig2 = h / 3.0 * s / (2.0 * M_PI * M_PI);
+  return p.sigma8 * p.sigma8 / sig2;
 }
 
 // Tabulated P(k): ln P linear in ln k between the nodes; below the first and
@@ -106,15 +120,17 @@ __device__ __forceinline__ double pk_tabulated(double k, const PkParams& p) {
   return exp(y0 + (y1 - y0) * (log(k) - x0) / (x1 - x0));
 }
 
-__global__ void __launch_bounds__(256) k_amp_table(const double* amp, PkParams p, double L, int nentries, float* table) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
+__global__ void __launch_bounds__(kSigmaBlocks) k_amp_table(const double* __restrict__ partial, PkParams p, double L,
+                                                            int nentries, float* table) {
+  const double amp = p.k_tab ? 1.0 : pk_amplitude(p, partial);
+  const int e = blockIdx.x * kSigmaBlocks + threadIdx.x;
   if (e >= nentries) return;
   if (e == 0) {
     table[0] = 0.0f;
     return;
   }
   const double k = 2.0 * M_PI * sqrt(static_cast<double>(e)) / L;
-  const double P = p.k_tab ? pk_tabulated(k, p) : amp[0] * pk_shape(k, p);
+  const double P = p.k_tab ? pk_tabulated(k, p) : amp * pk_shape(k, p);
   double s = sqrt(P / (L * L * L));
   if (p.smooth > 0.0) s *= exp(-0.5 * (k * p.smooth) * (k * p.smooth));
   table[e] = static_cast<float>(s);
@@ -126,15 +142,16 @@ __global__ void __launch_bounds__(256) k_amp_table(const double* amp, PkParams p
 // (m even).  f_j is the Simpson weight times P(k_j) exp(-k_j^2 s^2) k_j (k = 0
 // carries nothing), written as the sums and differences of the node pairs that
 // k_sine_sum takes (nodes beyond m are 0).
-__global__ void __launch_bounds__(256) k_xi_weights(const double* amp, PkParams p, double s, double h, int m, int na,
-                                                    double* sd) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
+__global__ void __launch_bounds__(kSigmaBlocks) k_xi_weights(const double* __restrict__ partial, PkParams p, double s,
+                                                             double h, int m, int na, double* sd) {
+  const double amp = p.k_tab ? 1.0 : pk_amplitude(p, partial);
+  const int t = blockIdx.x * kSigmaBlocks + threadIdx.x;
   const int a = t / kSineB, b = t % kSineB;
   if (a >= na) return;
   auto f = [&](int j) {
     if (j == 0 || j > m) return 0.0;
     const double k = h * j;
-    const double P = p.k_tab ? pk_tabulated(k, p) : amp[0] * pk_shape(k, p);
+    const double P = p.k_tab ? pk_tabulated(k, p) : amp * pk_shape(k, p);
     const double w = (j == m) ? 1.0 : ((j & 1) ? 4.0 : 2.0);
     return w * h / 3.0 * P * exp(-(k * s) * (k * s)) * k;
   };
@@ -267,28 +284,31 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t st) {
 }
 
 // ---- launchers ----
+// sigma8 sums (none for a tabulated spectrum) and twiddles (ntw may be 0)
+void launch_pk_start(const PkParams& p, double* partial, float2* tw, int ntw, hipStream_t st) {
+  const int nsig = p.k_tab ? 0 : kSigmaBlocks, nt = (ntw + kSigmaBlocks - 1) / kSigmaBlocks;
+  if (nsig + nt > 0)
+    LYA_TIMED("pk_start", st,
+              hipLaunchKernelGGL(k_pk_start, dim3(nsig + nt), dim3(kSigmaBlocks), 0, st, p, nsig, partial, tw, ntw));
+}
+
 hipError_t launch_pk_table(const PkParams& p, int n, double dx, TableWork& w, hipStream_t st) {
   const double L = n * dx;
-  LYA_TIMED("pk_sigma8", st, hipLaunchKernelGGL(k_sigma8_partial, dim3(kSigmaBlocks), dim3(256), 0, st, p, w.partial));
-  LYA_TIMED("pk_finalize", st,
-            hipLaunchKernelGGL(k_pk_finalize, dim3(1), dim3(256), 0, st, p, w.partial, kSigmaBlocks, w.amp, w.tw, n));
+  launch_pk_start(p, w.partial, w.tw, n, st);
   const int ne = amp_table_entries(n);
   LYA_TIMED("pk_table", st,
-            hipLaunchKernelGGL(k_amp_table, dim3((ne + 255) / 256), dim3(256), 0, st, w.amp, p, L, ne, w.table));
+            hipLaunchKernelGGL(k_amp_table, dim3((ne + kSigmaBlocks - 1) / kSigmaBlocks), dim3(kSigmaBlocks), 0, st,
+                               w.partial, p, L, ne, w.table));
   return hipGetLastError();
 }
 
-hipError_t launch_xi_weights(const PkParams& p, double s, double h, int m, double* partial, double* amp,
-                             double* f, hipStream_t st) {
-  if (!p.k_tab) {
-    LYA_TIMED("pk_sigma8", st, hipLaunchKernelGGL(k_sigma8_partial, dim3(kSigmaBlocks), dim3(256), 0, st, p, partial));
-    LYA_TIMED("pk_finalize", st,
-              hipLaunchKernelGGL(k_pk_finalize, dim3(1), dim3(256), 0, st, p, partial, kSigmaBlocks, amp,
-                                 static_cast<float2*>(nullptr), 0));
-  }
+hipError_t launch_xi_weights(const PkParams& p, double s, double h, int m, double* partial, double* f,
+                             hipStream_t st) {
+  launch_pk_start(p, partial, nullptr, 0, st);
   const int na = sine_shape(m + 1, 1).na;
   LYA_TIMED("xi_weights", st,
-            hipLaunchKernelGGL(k_xi_weights, dim3((na * kSineB + 255) / 256), dim3(256), 0, st, amp, p, s, h, m, na,
+            hipLaunchKernelGGL(k_xi_weights, dim3((na * kSineB + kSigmaBlocks - 1) / kSigmaBlocks),
+                               dim3(kSigmaBlocks), 0, st, partial, p, s, h, m, na,
                                f));
   return hipGetLastError();
 }

@@ -55,7 +55,7 @@ bool pow2_in_range(int n) { return n >= 32 && n <= 2048 && (n & (n - 1)) == 0; }
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
 struct BoxCarve {
-  size_t partial, amp, tw, table, table_b, zorder, staging, second, total;
+  size_t partial, tw, table, table_b, zorder, staging, second, total;
 };
 
 // two_buffer: room for a second complex64 box after the staging box (the
@@ -64,7 +64,6 @@ BoxCarve carve_box(const lya_box* b, bool two_buffer = false) {
   BoxCarve c{};
   size_t o = 0;
   c.partial = o; o += align256(sizeof(double) * lya::kSigmaBlocks);
-  c.amp = o;     o += align256(sizeof(double));
   c.tw = o;      o += align256(sizeof(float2) * b->n);
   c.table = o;   o += align256(sizeof(float) * lya::amp_table_entries(b->n));
   c.table_b = o; o += align256(sizeof(float) * lya::amp_table_entries(b->n));
@@ -145,14 +144,13 @@ int64_t xi_nodes(double smooth, double rmax) {
 }
 
 struct LnCarve {
-  size_t partial, amp, f, xi, g, part, total;
+  size_t partial, f, xi, g, part, total;
 };
 
 LnCarve carve_lognormal(int64_t m, int32_t n_r) {
   LnCarve c{};
   size_t o = 0;
   c.partial = o; o += align256(sizeof(double) * lya::kSigmaBlocks);
-  c.amp = o;     o += align256(sizeof(double));
   c.f = o;       o += align256(sizeof(double) * lya::kSineJ * static_cast<size_t>(lya::sine_shape(m + 1, 1).na));
   c.xi = o;      o += align256(sizeof(double) * static_cast<size_t>(n_r));
   c.g = o;       o += align256(sizeof(double) * lya::kSineJ * static_cast<size_t>(lya::sine_shape(n_r, 1).na));
@@ -211,8 +209,8 @@ int make_pair(const lya_box* box, const lya_pk* pk, const lya_pk* pk_b, uint64_t
   const bool two_buffer = work_bytes >= carve_box(box, true).total;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* w = static_cast<char*>(work);
-  lya::TableWork tw{reinterpret_cast<double*>(w + c.partial), reinterpret_cast<double*>(w + c.amp),
-                    reinterpret_cast<float2*>(w + c.tw), reinterpret_cast<float*>(w + c.table)};
+  lya::TableWork tw{reinterpret_cast<double*>(w + c.partial), reinterpret_cast<float2*>(w + c.tw),
+                    reinterpret_cast<float*>(w + c.table)};
   hipError_t e = lya::launch_pk_table(pk_params(pk), box->n, box->dx, tw, st);
   if (e != hipSuccess) return hip_fail(e, "power-spectrum table");
   const float* table_b = nullptr;
@@ -717,7 +715,6 @@ int lya_lognormal_pk(const lya_pk* pk, double z_box, double z_ref, const lya_cos
   a.g = reinterpret_cast<double*>(w + c.g);
   a.part = reinterpret_cast<double*>(w + c.part);
   a.partial = reinterpret_cast<double*>(w + c.partial);
-  a.amp = reinterpret_cast<double*>(w + c.amp);
   hipError_t e = lya::launch_lognormal(pk_params(pk), a, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "lognormal spectrum");
   return LYA_OK;

@@ -10,7 +10,7 @@
 namespace lya {
 
 constexpr double kCOverH0 = 2997.92458;  // Mpc/h
-constexpr int kSigmaBlocks = 64;          // partial sums of the sigma8 integral
+constexpr int kSigmaBlocks = 256;         // partial sums of the sigma8 integral
 constexpr double kZTabH = 0.5;            // Mpc/h spacing of the z(chi) table
 constexpr int kZTabN = 20001;             // covers chi in [0, 10000] Mpc/h
 constexpr int kMaxZBins = 64;
@@ -41,7 +41,6 @@ __host__ __device__ constexpr size_t box_elems(int n) { return static_cast<size_
 // Workspace carve-up of lya_make_box / lya_make_eta.
 struct TableWork {
   double* partial;  // kSigmaBlocks
-  double* amp;      // 1
   float2* tw;       // n twiddles exp(+2 pi i k/n)
   float* table;     // amp_table_entries(n)
 };
@@ -97,9 +96,9 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t st);
 hipError_t launch_zchi_table(double omega_m, float* ztab, hipStream_t st);
 // Simpson-weighted integrand of xi_m (k_j = j h, j = 0..m) in the groups of
 // k_sine_sum: sigma8 normalisation first for the analytic form (partial:
-// kSigmaBlocks, amp: 1).
-hipError_t launch_xi_weights(const PkParams& p, double s, double h, int m, double* partial, double* amp,
-                             double* f, hipStream_t st);
+// kSigmaBlocks).
+hipError_t launch_xi_weights(const PkParams& p, double s, double h, int m, double* partial, double* f,
+                             hipStream_t st);
 hipError_t launch_twiddles(float2* tw, int ntw, hipStream_t st);
 // second: a complex64 box buffer of the same size (workspace) for the
 // two-buffer order, or null for the in-place order.  zorder: zorder_words(n)
@@ -302,7 +301,6 @@ struct LognormalArgs {
   double* g;         // workspace [sine_shape(n_r, .).na][kSineJ]: r weights in groups
   double* part;      // workspace [kSineParts]
   double* partial;   // workspace [kSigmaBlocks]
-  double* amp;       // workspace [1]
 };
 hipError_t launch_lognormal(const PkParams& p, const LognormalArgs& a, hipStream_t st);
 

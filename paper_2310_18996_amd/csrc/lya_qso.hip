@@ -114,9 +114,17 @@ SineShape sine_shape(int n_nodes, int nx) {
   return s;
 }
 
+// in order, the loads of 16 segments in flight at once (one after another they
+// were most of k_lognormal_pq's 17 us)
 __device__ __forceinline__ double sine_total(const double* part, int segs, int nx, int i) {
   double s = 0.0;
-  for (int k = 0; k < segs; ++k) s += part[static_cast<size_t>(k) * nx + i];
+  for (int k0 = 0; k0 < segs; k0 += 16) {
+    double v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = part[static_cast<size_t>(min(k0 + k, segs - 1)) * nx + i];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) s += k0 + k < segs ? v[k] : 0.0;
+  }
   return s;
 }
 
@@ -166,7 +174,7 @@ __global__ void __launch_bounds__(1024) k_lognormal_pq(const double* part, int s
 }
 
 hipError_t launch_lognormal(const PkParams& p, const LognormalArgs& a, hipStream_t st) {
-  hipError_t e = launch_xi_weights(p, a.smooth, a.h, a.m, a.partial, a.amp, a.f, st);
+  hipError_t e = launch_xi_weights(p, a.smooth, a.h, a.m, a.partial, a.f, st);
   if (e != hipSuccess) return e;
   const SineShape sx = sine_shape(a.m + 1, a.n_r), sk = sine_shape(a.n_r, a.n_k);
   double* px = sx.segs == 1 ? a.xi : a.part;  // the caller's array where one segment holds the sums
