@@ -204,6 +204,18 @@ struct Pass {
   // LDS layout with one padding slot per R0 elements along the FFT axis (R0 =
   // first radix): the first stage scatters its outputs with stride R0, which
   // without padding lands every lane group on the same banks.
+  // Non-temporal accesses of the strided passes, where a box is beyond the 256 MB
+  // last-level cache and they measured faster: 512^3 y 0.44 -> 0.42, x 0.46 ->
+  // 0.42 ms (BF16 output 0.37 -> 0.34); 1024^3 y, loads split over the stages, 3.45 ->
+  // 3.32 ms with the stores alone (loads as well: 3.33; x: 3.72 and 3.70, left).
+  static constexpr bool kNtLoad = KIND != KIND_GENZ && N == 512;
+  static constexpr bool kNtStore = (KIND == KIND_X && N == 512) || (KIND == KIND_Y && N == 1024);
+  __device__ static __forceinline__ float2 ld2(const float2* q) {
+    typedef float f2v __attribute__((ext_vector_type(2)));
+    if constexpr (!kNtLoad) return *q;
+    const f2v w = __builtin_nontemporal_load(reinterpret_cast<const f2v*>(q));
+    return make_float2(w.x, w.y);
+  }
   static constexpr int R0 = radix_of(N, 0);
   static constexpr int LDS_ELEMS = T * (N + N / R0);
   __device__ static __forceinline__ int lidx(int i, int p) {
@@ -253,7 +265,7 @@ struct Pass {
         const uint32_t o = off_in(j, p);
 #pragma unroll
         for (int r = 0; r < R; ++r)
-          if (b * R + r >= EL && b * R + r < EH) v[b * R + r] = plane[o + static_cast<uint32_t>(r * (N / R) * N)];
+          if (b * R + r >= EL && b * R + r < EH) v[b * R + r] = ld2(plane + o + static_cast<uint32_t>(r * (N / R) * N));
       }
     } else {
 #pragma unroll
@@ -263,7 +275,7 @@ struct Pass {
         coords<R>(tid + b * NT, p, j);
 #pragma unroll
         for (int r = 0; r < R; ++r)
-          if (b * R + r >= EL && b * R + r < EH) v[b * R + r] = data[gidx(outer, t0, j + r * (N / R), p)];
+          if (b * R + r >= EL && b * R + r < EH) v[b * R + r] = ld2(data + gidx(outer, t0, j + r * (N / R), p));
       }
     }
   }
@@ -374,7 +386,7 @@ struct Pass {
         const float2 o = make_float2(v[b * R + r].x, zero_b ? 0.0f : v[b * R + r].y);
         if (out_bf16) {
           out_bf16[gi] = pack_bf16x2(o.x, o.y);
-        } else if (KIND == KIND_GENZ) {
+        } else if (KIND == KIND_GENZ || kNtStore) {
           // nontemporal: the synthesising pass writes lines it never read, and a
           // plain store first fetches each line into L2 (counter-measured)
           typedef float f2v __attribute__((ext_vector_type(2)));
@@ -394,10 +406,40 @@ struct Pass {
 // lin >> 1, words (x, y) for even iz and (z, w) for odd iz), one Box-Muller per
 // owner mode, and each owner mode also fills its partner (N-ix, -iy, -iz) with
 // the conjugate noise.  Result goes to LDS in pencil-major order.
-// GM selects the synthesiser: GEN_GENERIC handles any component pair and the
-// test hooks; GEN_DELTA_ETAZ ({delta, f mu_z^2 delta}) and GEN_DELTA ({delta, 0})
-// are the branch-free forms used by lya_make_box.
-enum { GEN_GENERIC = 0, GEN_DELTA_ETAZ = 1, GEN_DELTA = 2 };
+// GM selects the synthesiser: GEN_DELTA_ETAZ ({delta, f mu_z^2 delta}) and
+// GEN_DELTA ({delta, 0}) are the branch-free forms used by lya_make_box,
+// GEN_COMPS makes any component pair of one spectrum (CompPoly), GEN_GENERIC the
+// test hooks and two spectra besides.
+enum { GEN_GENERIC = 0, GEN_DELTA_ETAZ = 1, GEN_DELTA = 2, GEN_COMPS = 3 };
+
+// Multiplier of a component along a pencil (nx, ny), 0 < nx < N/2: one real
+// number, d + (p + q nz + r nz^2) / n^2, the factor i of the velocities apart
+// (odd).  At the partner mode it is the same for delta and eta and the negative
+// for the velocities; q nz vanishes on the plane nz = -N/2 and the terms in ny on
+// ny = -N/2, as in comp_mult2.  Evaluating comp_mult2 four times per mode made the
+// pass of a 512^3 velocity box 563 us long; 427 us (bound by vector issue).
+struct CompPoly {
+  float d, p, q, r;
+  __device__ __forceinline__ CompPoly(int comp, int nx, int ny, int n, float f, float vscale) : d(0), p(0), q(0), r(0) {
+    const float fx = static_cast<float>(nx), fy = static_cast<float>(ny);
+    const float hy = ny == -(n / 2) ? 0.0f : fy;   // of the odd terms
+    switch (comp) {
+      case 0: d = 1.0f; break;
+      case 1: p = f * (fx * fx); break;
+      case 2: p = f * (fy * fy); break;
+      case 3: r = f; break;
+      case 4: p = f * (fx * hy); break;
+      case 5: q = f * fx; break;
+      case 6: q = f * hy; break;
+      case 7: p = vscale * fx; break;
+      case 8: p = vscale * hy; break;
+      case 9: q = vscale; break;
+      default: break;   // none
+    }
+  }
+  // z: nz, h: nz or 0 on its Nyquist plane, inv = 1 / n^2
+  __device__ __forceinline__ float at(float z, float h, float inv) const { return fmaf(fmaf(q, h, fmaf(r, z * z, p)), inv, d); }
+};
 
 template <int N, int T, int NT, int GM, typename LIDX>
 __device__ __forceinline__ void gen_paired(const GenParams& g, int ix, int iy0, float2* lds, LIDX lidx, float* stab,
@@ -447,6 +489,8 @@ __device__ __forceinline__ void gen_paired(const GenParams& g, int ix, int iy0, 
     const int iy = iy0 + po;
     const int ny = sfreq(iy, N);
     const uint4 wd = wds[p];
+    const CompPoly ca(GM == GEN_COMPS ? g.comp_a : -1, nx, ny, N, g.f, g.vscale);
+    const CompPoly cb(GM == GEN_COMPS ? g.comp_b : -1, nx, ny, N, g.f, g.vscale);
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       const int iz = 2 * m + e;
@@ -473,6 +517,18 @@ __device__ __forceinline__ void gen_paired(const GenParams& g, int ix, int iy0, 
         const float2 db = comp_mult2(g.comp_b, -nx, pny, pnz, n2, N, g.f, g.vscale);
         const float pr = s * ca.x - sb * cb.y, pi = s * ca.y + sb * cb.x;
         const float qr = s * da.x - sb * db.y, qi = s * da.y + sb * db.x;
+        lds[lidx(iz, po)] = make_float2(wv.x * pr - wv.y * pi, wv.y * pr + wv.x * pi);
+        lds[lidx((N - iz) & (N - 1), H + po)] = make_float2(wv.x * qr + wv.y * qi, wv.x * qi - wv.y * qr);
+        continue;
+      } else if (GM == GEN_COMPS) {
+        // P = s c_a + i s c_b and P' as above, with c' = -c for the velocities
+        const float z = static_cast<float>(nz), h = nz == -(N / 2) ? 0.0f : z;
+        const float inv = __builtin_amdgcn_rcpf(static_cast<float>(n2));  // n2 > 0 here (ix > 0)
+        const float a = s * ca.at(z, h, inv), b = s * cb.at(z, h, inv);
+        const bool va = g.comp_a >= 7, vb = g.comp_b >= 7;
+        // i b of an even, -b of an odd second component
+        const float pr = (va ? 0.0f : a) - (vb ? b : 0.0f), pi = (va ? a : 0.0f) + (vb ? 0.0f : b);
+        const float qr = (va ? 0.0f : a) + (vb ? b : 0.0f), qi = (vb ? 0.0f : b) - (va ? a : 0.0f);
         lds[lidx(iz, po)] = make_float2(wv.x * pr - wv.y * pi, wv.y * pr + wv.x * pi);
         lds[lidx((N - iz) & (N - 1), H + po)] = make_float2(wv.x * qr + wv.y * qi, wv.x * qi - wv.y * qr);
         continue;
@@ -545,7 +601,7 @@ __global__ void __launch_bounds__(N * T / E) k_fft_pass(float2* __restrict__ dat
       int p, j;
       P::template coords<R>(tid + b * NT, p, j);
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[b * R + r] = gen_mode<N, GM == GEN_GENERIC>(g, outer, t0 + p, j + r * (N / R));
+      for (int r = 0; r < R; ++r) v[b * R + r] = gen_mode<N, GM == GEN_GENERIC || GM == GEN_COMPS>(g, outer, t0 + p, j + r * (N / R));
     }
   } else {
     P::load_global0(v, data, outer, t0, tid);
@@ -676,8 +732,9 @@ namespace {
 // order 0 and x with order 1; from 1024 up the pipelined kernel with full
 // tiles of half the elements per thread, y order 0 (variant 8), x order 1
 // with its loads split over the FFT stages (15: 36.6 ms against 42.0 ms for
-// 9 at 2048^3, bit-identical; for y the split measured 31.4 against 31.1 ms)
-std::atomic<int> g_variant[2][12] = {{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 8, 8}, {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 15, 15}};
+// 9 at 2048^3, bit-identical; for y the split measured 31.4 against 31.1 ms there,
+// and 3.32 against 3.6 ms at 1024^3: variant 14)
+std::atomic<int> g_variant[2][12] = {{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 14, 8}, {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 15, 15}};
 int ilog2(int n) {
   int l = 0;
   while ((1 << l) < n && l < 11) ++l;
@@ -892,6 +949,10 @@ hipError_t launch_zgen(const GenParams& g, int gm, const float2* tw, float2* out
     LYA_TIMED("fft_z_gen", st,
               hipLaunchKernelGGL((k_fft_pass<N, S::TZ, S::EZ, KIND_GENZ, 0, GEN_DELTA, SWZ>), dim3(tz),
                                  dim3(N * S::TZ / S::EZ), 0, st, out, nullptr, tw, g));
+  } else if (gm == GEN_COMPS) {
+    LYA_TIMED("fft_z_gen", st,
+              hipLaunchKernelGGL((k_fft_pass<N, S::TZ, S::EZ, KIND_GENZ, 0, GEN_COMPS, SWZ>), dim3(tz),
+                                 dim3(N * S::TZ / S::EZ), 0, st, out, nullptr, tw, g));
   } else {
     LYA_TIMED("fft_z_gen", st,
               hipLaunchKernelGGL((k_fft_pass<N, S::TZ, S::EZ, KIND_GENZ, 0, GEN_GENERIC, SWZ>), dim3(tz),
@@ -945,9 +1006,10 @@ template <int N>
 hipError_t run_box_fft(GenParams g, const float2* tw, float2* field, uint32_t* field_bf16, float2* second,
                        uint32_t* zorder, hipStream_t st) {
   const bool hooks = g.fixed_amp || g.only_n2 >= 0 || g.table_b;
-  const int gm = (!hooks && g.comp_a == 0 && g.comp_b == 3)    ? GEN_DELTA_ETAZ
-                 : (!hooks && g.comp_a == 0 && g.comp_b == -1) ? GEN_DELTA
-                                                               : GEN_GENERIC;
+  const int gm = hooks                                 ? GEN_GENERIC
+                 : g.comp_a == 0 && g.comp_b == 3  ? GEN_DELTA_ETAZ
+                 : g.comp_a == 0 && g.comp_b == -1 ? GEN_DELTA
+                                                   : GEN_COMPS;
   hipError_t e;
   g.order = nullptr;
   if constexpr (N >= kZOrderMinN) {
