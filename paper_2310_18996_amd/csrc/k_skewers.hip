@@ -352,15 +352,207 @@ __device__ __forceinline__ float gauss_slots(float t, int sh, float (&w)[8]) {
   return s;
 }
 
+// c: values at the pixel's z in the columns (x0, y0), (x0, y1), (x1, y0), (x1, y1)
+__device__ __forceinline__ float bilerp(float tx, float ty, const float (&c)[4]) {
+  const float c0 = c[0] + ty * (c[1] - c[0]);
+  const float c1 = c[2] + ty * (c[3] - c[2]);
+  return c0 + tx * (c1 - c0);
+}
 __device__ __forceinline__ float trilerp(float tx, float ty, float tz, float c000, float c001, float c010, float c011,
                                          float c100, float c101, float c110, float c111) {
-  const float c00 = c000 + tz * (c001 - c000);
-  const float c01 = c010 + tz * (c011 - c010);
-  const float c10 = c100 + tz * (c101 - c100);
-  const float c11 = c110 + tz * (c111 - c110);
-  const float c0 = c00 + ty * (c01 - c00);
-  const float c1 = c10 + ty * (c11 - c10);
-  return c0 + tx * (c1 - c0);
+  const float c[4] = {c000 + tz * (c001 - c000), c010 + tz * (c011 - c010), c100 + tz * (c101 - c100),
+                      c110 + tz * (c111 - c110)};
+  return bilerp(tx, ty, c);
+}
+
+// Sum over the wave, in lane 63: an inclusive scan by DPP moves (a shuffle per
+// step would be an LDS round trip).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long dpp_add_u64(unsigned long long v) {
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(v >> 32), CTRL, ROWS, 0xf, true);
+  return v + ((static_cast<unsigned long long>(hi) << 32) | lo);
+}
+__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
+  v = dpp_add_u64<0x111, 0xf>(v);   // row_shr 1, 2, 4, 8
+  v = dpp_add_u64<0x112, 0xf>(v);
+  v = dpp_add_u64<0x114, 0xf>(v);
+  v = dpp_add_u64<0x118, 0xf>(v);
+  v = dpp_add_u64<0x142, 0xa>(v);   // row_bcast 15 into rows 1 and 3
+  return dpp_add_u64<0x143, 0xc>(v);   // row_bcast 31 into rows 2 and 3
+}
+
+// Bin sums along one line for the cell walk.  The bin is the wave's, not a lane's:
+// nearly every 64 consecutive pixels lie in one bin as a whole (two scalar
+// comparisons), and where one ends its lanes are added first and leave by one LDS
+// addition.  With a bin per lane every pixel reads its bounds from LDS and 64 lanes
+// add to one address, twice per bin (LDS conflicts 570M -> 140M cycles on the 2048^3
+// lines); the other modes keep that, it needs fewer scalar registers (7^3 mode
+// 1.80 against 1.83 ms).  Pixel counts follow from the bounds.
+struct BinWalk {
+  int bin, lo, hi;           // uniform; bin < 0: past the last
+  unsigned long long acc;    // this lane's pixels of the bin, F 2^32
+  __device__ __forceinline__ void bounds(const int* jb) {
+    lo = bin < 0 ? 0x7fffffff : __builtin_amdgcn_readfirstlane(jb[bin + 1]);
+    hi = bin < 0 ? 0x7fffffff : __builtin_amdgcn_readfirstlane(jb[bin]);
+  }
+  __device__ __forceinline__ void start(const int* jb, int n_bins) {
+    bin = n_bins - 1;
+    acc = 0ull;
+    bounds(jb);
+  }
+  __device__ __forceinline__ void flush(unsigned long long* s_sum, int lane) {
+    const unsigned long long t = wave_sum_u64(acc);
+    if (lane == 63 && t) atomicAdd(&s_sum[bin], t);   // t = 0 past the last bin
+    acc = 0ull;
+  }
+  // pixels j0 .. j0 + 63 of np, j this lane's
+  __device__ __forceinline__ void add(const int* jb, int j0, int np, int j, float F, unsigned long long* s_sum,
+                                      int lane) {
+    const int end = j0 + 64 < np ? j0 + 64 : np;
+    const unsigned long long f = __float2ull_rn(F * 4294967296.0f);
+    if (j0 >= lo && j0 + 64 <= hi) {   // hi <= np
+      acc += f;
+      return;
+    }
+    while (bin >= 0) {
+      if (j >= lo && j < hi) acc += f;
+      if (hi >= end) break;
+      flush(s_sum, lane);
+      --bin;
+      bounds(jb);
+    }
+  }
+  __device__ __forceinline__ void end(const int* jb, int n_bins, unsigned long long* s_sum,
+                                      unsigned long long* s_cnt, int lane) {
+    flush(s_sum, lane);
+    for (int b = lane; b < n_bins; b += 64)
+      if (jb[b] > jb[b + 1]) atomicAdd(&s_cnt[b], static_cast<unsigned long long>(jb[b] - jb[b + 1]));
+  }
+};
+
+// Trilinear interpolation through the wave's cells.  64 consecutive pixels of a
+// line (steps of a tenth of a cell, say) lie in some 10 cells, so the eight corner
+// gathers of each pixel read the same few voxels over and over.  Instead a lane
+// takes one (x, y) corner column of one cell: it loads both its voxels (two
+// gathers in place of eight, in flight during the 64 pixels before), and leaves
+// {delta, its z difference, eta, its z difference} in LDS, from where a pixel
+// reads its cell's four columns.  The arithmetic is the same to the bit.
+// Cells are numbered by the boundaries crossed since the wave's first pixel, all
+// axes together; a number that no pixel has stays unused.  Lines with steps that
+// may cross more than 15 boundaries in 64 pixels (above a fifth of a cell along an
+// axis) gather pixel by pixel.
+// What bounded the gathers: the address unit (20 cycles each, 70% busy) and that
+// every step waited for the stores of the step before (loads and stores complete
+// in order).  1.1e9 pixels of 1M lines in a 2048^3 box without delta_S and FGPA
+// 6.7 -> 6.0 ms, with both and bins 11.9 -> 11.1 ms; 35M wide-angle pixels (four
+// BF16 boxes, 512^3) 592 -> 496 us.  The columns alone, without the order of loads
+// and stores, took 13.1 ms.
+constexpr int kCells = 16;
+__device__ __forceinline__ bool cells_fit(int64_t sx, int64_t sy, int64_t sz) {
+  // 63 steps cross at most floor(63 |s|) + 1 boundaries of an axis
+  const uint64_t a = static_cast<uint64_t>(sx < 0 ? -sx : sx), b = static_cast<uint64_t>(sy < 0 ? -sy : sy),
+                 c = static_cast<uint64_t>(sz < 0 ? -sz : sz);
+  return a < (1u << 30) && b < (1u << 30) && c < (1u << 30) &&
+         ((63 * a) >> 32) + ((63 * b) >> 32) + ((63 * c) >> 32) + 3 < kCells;
+}
+__device__ __forceinline__ uint32_t abs_diff(uint32_t a, uint32_t b) { return max(a, b) - min(a, b); }
+
+template <int MODE, bool B16>
+struct CellWalk {
+  static constexpr int F = MODE == kSkWide ? 4 : 1;   // boxes
+  typedef typename GaussCell<B16>::type V;
+  uint64_t p[3];       // this lane's pixel of the step on its way, biased by 2^63 (cell order without signs)
+  uint32_t fr[3], k;   // its fractions and cell number
+  V v[F][2];           // the lane's column
+
+  __device__ __forceinline__ void start(int64_t ox, int64_t oy, int64_t oz, int64_t sx, int64_t sy, int64_t sz,
+                                        int lane) {
+    constexpr uint64_t kBias = uint64_t(1) << 63;
+    p[0] = kBias + static_cast<uint64_t>(ox) + static_cast<uint64_t>(sx) * static_cast<uint32_t>(lane);
+    p[1] = kBias + static_cast<uint64_t>(oy) + static_cast<uint64_t>(sy) * static_cast<uint32_t>(lane);
+    p[2] = kBias + static_cast<uint64_t>(oz) + static_cast<uint64_t>(sz) * static_cast<uint32_t>(lane);
+  }
+
+  // The cells of the 64 pixels at p: their columns are sent for, p goes on.  All lanes.
+  __device__ __forceinline__ void send(const SkewerArgs& a, int64_t sx, int64_t sy, int64_t sz, int N, size_t NN,
+                                       int lane) {
+    const int64_t s[3] = {sx, sy, sz};
+    uint32_t first[3], r[3];
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+      const uint32_t cell = static_cast<uint32_t>(p[ax] >> 32);
+      first[ax] = __builtin_amdgcn_readfirstlane(cell);
+      r[ax] = abs_diff(cell, first[ax]);
+      fr[ax] = static_cast<uint32_t>(p[ax]);
+      p[ax] += static_cast<uint64_t>(s[ax]) * 64u;
+    }
+    k = r[0] + r[1] + r[2];   // < kCells
+    // the cell to its number's quad of lanes (any of its pixels: the last one stays)
+    const uint32_t pack = r[0] | r[1] << 8 | r[2] << 16;
+    const uint32_t c = dpp_i32<0x00>(__builtin_amdgcn_ds_permute(static_cast<int>(k << 4), static_cast<int>(pack)));
+    const int dir[3] = {sx < 0 ? -1 : 1, sy < 0 ? -1 : 1, sz < 0 ? -1 : 1};
+    const uint32_t msk = static_cast<uint32_t>(N - 1);
+    const uint32_t x = (first[0] + dir[0] * static_cast<int>(c & 255u) + ((lane >> 1) & 1)) & msk;
+    const uint32_t y = (first[1] + dir[1] * static_cast<int>(c >> 8 & 255u) + (lane & 1)) & msk;
+    const uint32_t z = (first[2] + dir[2] * static_cast<int>(c >> 16 & 255u)) & msk;
+    const uint32_t row = y * static_cast<uint32_t>(N);
+    const uint64_t plane = static_cast<uint64_t>(x) * static_cast<uint32_t>(NN);   // n^2 + padding < 2^32
+    const uint64_t i0 = plane + (row + z), i1 = plane + (row + ((z + 1) & msk));
+#pragma unroll
+    for (int f = 0; f < F; ++f) {
+      const V* b;
+      if constexpr (B16) b = f == 0 ? a.field_bf16 : a.wide_bf16[f - 1];
+      else b = f == 0 ? a.field : a.wide[f - 1];
+      v[f][0] = b[i0];
+      v[f][1] = b[i1];
+    }
+  }
+};
+
+// A line's pixels of one output as a bounded buffer: lanes past the end, and all
+// of an output that is not wanted, are dropped by the bounds check, so that a
+// step's stores need no branch.  Loads and stores complete in order here, and
+// where a branch may skip a store the wait for a later load is a wait for
+// everything before it.
+struct LineOut {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ LineOut(float* p, int64_t off, int np)
+      : r(__builtin_amdgcn_make_buffer_rsrc(p ? p + off : p, 0, p ? 4 * np : 0, 0x00020000)) {}
+  __device__ __forceinline__ void put(int j, float v) const {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, 4 * j, 0, 0);
+  }
+};
+
+// Position of a line's pixels in the z(chi) table, in table steps times 2^32:
+// chi_j / kZTabH = chi0 / kZTabH - j dchi / kZTabH, each term rounded to 2^-32
+// steps (at most 2^-22 Mpc/h off at j = 2048).
+__device__ __forceinline__ int64_t z_start(double chi0) { return llrint(chi0 * (4294967296.0 / kZTabH)); }
+__device__ __forceinline__ int64_t z_step(double dchi) { return llrint(dchi * (4294967296.0 / kZTabH)); }
+// The two nodes of the z(chi) table around a position in table steps times 2^32,
+// and the place between them.
+struct ZNodes {
+  float z0, z1, t;
+  __device__ __forceinline__ void send(const float* ztab, int64_t zp) {
+    const int64_t ip = zp >> 32;
+    int iu;
+    if (ip >= 0 && ip <= kZTabN - 2) {
+      iu = static_cast<int>(ip);
+      t = static_cast<float>(static_cast<uint32_t>(zp)) * 2.3283064365386963e-10f;
+    } else {  // beyond the table: the end interval continued linearly
+      iu = ip < 0 ? 0 : kZTabN - 2;
+      t = static_cast<float>(static_cast<double>(zp - (static_cast<int64_t>(iu) << 32)) * 2.3283064365386963e-10);
+    }
+    z0 = ztab[iu];
+    z1 = ztab[iu + 1];
+  }
+};
+__device__ __forceinline__ float fgpa_flux(const SkewerArgs& a, const ZNodes& z, float d, float e) {
+  const float x = (z.z0 + z.t * (z.z1 - z.z0)) + (1.0f - kFgpaX0);   // (1+z) - x0
+  const float ca = a.cf[0][0] + x * (a.cf[0][1] + x * a.cf[0][2]);
+  const float cb = a.cf[1][0] + x * (a.cf[1][1] + x * a.cf[1][2]);
+  const float cc = a.cf[2][0] + x * (a.cf[2][1] + x * a.cf[2][2]);
+  return __expf(-ca * __expf(cb * (d + cc * e)));
 }
 
 // What small_scale_wave reads of the arguments.
@@ -374,9 +566,11 @@ struct LineNoise {
 
 // (the Gaussian mode's LDS leaves two waves per SIMD)
 template <int U, int MODE, bool B16>
-__global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : 1) k_skewers(SkewerArgs a) {
+__global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : 1) k_skewers(SkewerArgs a) {
   __shared__ float2 sbuf[kSkWaves][kHalfBuf];
   __shared__ float sgauss[MODE == kSkGauss ? kSkWaves : 1][MODE == kSkGauss ? kGaussWords : 1];
+  constexpr bool kCellWalk = U == 1 && MODE != kSkGauss;
+  __shared__ float4 scell[kCellWalk ? kSkWaves : 1][kCellWalk ? 4 * kCells : 1];
   __shared__ int sjb[kSkWaves][kMaxZBins + 1];
   __shared__ unsigned long long s_sum[kMaxZBins], s_cnt[kMaxZBins];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -451,18 +645,75 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : 1) k_skewers(Ske
         wxz = static_cast<float>(2.0 * ux * uz * ir2);
         wyz = static_cast<float>(2.0 * uy * uz * ir2);
       }
+      if constexpr (kCellWalk) {
+        if (gather && cells_fit(sx, sy, sz) && np < (1 << 28)) {
+          // all loads of the next 64 pixels are sent for before the stores of these
+          const int64_t uoff = lane_i64(off, 0);
+          const LineOut dens(la->dens, uoff, np), eta(la->eta, uoff, np), flux(la->do_flux ? la->flux : nullptr, uoff, np);
+          BinWalk bins;
+          if (want_bins) bins.start(jb, la->n_bins);
+          CellWalk<MODE, B16> walk;
+          ZNodes zn;
+          const int64_t zstep = z_step(la->dchi);
+          int64_t zp = z_start(chi0) - lane * zstep;
+          walk.start(ox, oy, oz, sx, sy, sz, lane);
+          walk.send(a, sx, sy, sz, N, NN, lane);
+          zn.send(a.ztab, zp);
+          float4* rec = scell[wv];
+          for (int it = 0; it < np; it += 64) {
+            const int j = it + lane;
+            float2 v0 = gauss_cell(walk.v[0][0]), v1 = gauss_cell(walk.v[0][1]);
+            if constexpr (MODE == kSkWide) {
+              auto wide = [&](const float2& a0, const float2& a1, const float2& a2, const float2& a3) {
+                return wzz * a0.y + wxx * a1.x + wyy * a1.y + wxy * a2.x + wxz * a2.y + wyz * a3.x;
+              };
+              v0.y = wide(v0, gauss_cell(walk.v[1][0]), gauss_cell(walk.v[2][0]), gauss_cell(walk.v[3][0]));
+              v1.y = wide(v1, gauss_cell(walk.v[1][1]), gauss_cell(walk.v[2][1]), gauss_cell(walk.v[3][1]));
+            }
+            rec[lane] = make_float4(v0.x, v1.x - v0.x, v0.y, v1.y - v0.y);
+            const float tx = static_cast<float>(walk.fr[0]) * 2.3283064365386963e-10f;
+            const float ty = static_cast<float>(walk.fr[1]) * 2.3283064365386963e-10f;
+            const float tz = static_cast<float>(walk.fr[2]) * 2.3283064365386963e-10f;
+            const int k = static_cast<int>(walk.k);
+            const ZNodes z = zn;
+            wave_sync();
+            walk.send(a, sx, sy, sz, N, NN, lane);   // (past the line's end too: every address is in the box)
+            zp -= 64 * zstep;
+            zn.send(a.ztab, zp);
+            float col[2][4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const float4 r = rec[4 * k + c];
+              col[0][c] = r.x + tz * r.y;
+              col[1][c] = r.z + tz * r.w;
+            }
+            float d = bilerp(tx, ty, col[0]);
+            const float e = bilerp(tx, ty, col[1]);
+            if (with_ds) {
+              const float2 z2 = buf[pidx((j < ns ? j : 0) >> 1)];   // (in the line's slots also past its end)
+              d += (j & 1) ? z2.y : z2.x;
+            }
+            wave_sync();   // the records are written again
+            dens.put(j, d);
+            eta.put(j, e);
+            const float F = fgpa_flux(a, z, d, e);
+            flux.put(j, F);
+            if (want_bins) bins.add(jb, it, np, j, F, s_sum, lane);
+          }
+          if (want_bins) bins.end(jb, la->n_bins, s_sum, s_cnt, lane);
+          wave_sync();  // the wave's LDS slice is reused by its next skewer
+          continue;
+        }
+      }
       // fixed-point positions of the lane's pixels j = lane + 64 u, advanced by
       // one addition per step of 64 U pixels (pixels past the end wrap like any
       // other and are dropped)
       int64_t pos[U][3];
       const int64_t adv[3] = {64 * U * sx, 64 * U * sy, 64 * U * sz};
-      // position of the lane's pixels in the z(chi) table, in table steps
-      // times 2^32 (chi_j / kZTabH = chi0 / kZTabH - j dchi / kZTabH, each term
-      // rounded to 2^-32 steps: at most 2^-22 Mpc/h off at j = 2048)
-      int64_t zpos[U];
-      const int64_t zstep = llrint(la->dchi * (4294967296.0 / kZTabH));
+      int64_t zpos[U];   // the lane's pixels in the z(chi) table
+      const int64_t zstep = z_step(la->dchi);
       if (a.do_flux) {
-        const int64_t z0 = llrint(chi0 * (4294967296.0 / kZTabH));
+        const int64_t z0 = z_start(chi0);
 #pragma unroll
         for (int u = 0; u < U; ++u) zpos[u] = z0 - (lane + 64 * u) * zstep;
       }
@@ -584,20 +835,27 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : 1) k_skewers(Ske
               const uint32_t y0 = iy * static_cast<uint32_t>(N), y1 = jy * static_cast<uint32_t>(N);
               const size_t ci[8] = {x0 + (y0 + iz), x0 + (y0 + jz), x0 + (y1 + iz), x0 + (y1 + jz),
                                     x1 + (y0 + iz), x1 + (y0 + jz), x1 + (y1 + iz), x1 + (y1 + jz)};
-              // all 32 gathers first, then eta_par = u_p u_q eta^pq per corner
-              float2 w0[8], w1[8], w2[8], w3[8];
+              // the gathers of G corners, then eta_par = u_p u_q eta^pq per corner: all
+              // 32 at once, but for U = 1 (lines whose steps are too long for the
+              // cell walk) what the walk's registers leave
+              constexpr int G = U == 1 ? 2 : 8;
 #pragma unroll
-              for (int k = 0; k < 8; ++k) {
-                w0[k] = ld_field<B16>(a, ci[k]);
-                w1[k] = ld_wide<B16>(a, 0, ci[k]);
-                w2[k] = ld_wide<B16>(a, 1, ci[k]);
-                w3[k] = ld_wide<B16>(a, 2, ci[k]);
-              }
+              for (int h = 0; h < 8; h += G) {
+                float2 w0[G], w1[G], w2[G], w3[G];
 #pragma unroll
-              for (int k = 0; k < 8; ++k) {
-                const float e = wzz * w0[k].y + wxx * w1[k].x + wyy * w1[k].y + wxy * w2[k].x + wxz * w2[k].y +
-                                wyz * w3[k].x;
-                c[u][k] = make_float2(w0[k].x, e);
+                for (int k = 0; k < G; ++k) {
+                  w0[k] = ld_field<B16>(a, ci[h + k]);
+                  w1[k] = ld_wide<B16>(a, 0, ci[h + k]);
+                  w2[k] = ld_wide<B16>(a, 1, ci[h + k]);
+                  w3[k] = ld_wide<B16>(a, 2, ci[h + k]);
+                }
+#pragma unroll
+                for (int k = 0; k < G; ++k) {
+                  const float e = wzz * w0[k].y + wxx * w1[k].x + wyy * w1[k].y + wxy * w2[k].x + wxz * w2[k].y +
+                                  wyz * w3[k].x;
+                  c[u][h + k] = make_float2(w0[k].x, e);
+                }
+                if constexpr (G < 8) __builtin_amdgcn_sched_barrier(0);
               }
             } else {
               // byte addresses: each x plane's start as one 32 x 32 -> 64-bit
@@ -664,24 +922,9 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : 1) k_skewers(Ske
             const int j = j0 + 64 * u;
             if (j >= np) break;
             const float d = dd[u], e = ee[u];
-            const int64_t zp = zpos[u];
-            const int64_t ip = zp >> 32;
-            int iu;
-            float t;
-            if (ip >= 0 && ip <= kZTabN - 2) {
-              iu = static_cast<int>(ip);
-              t = static_cast<float>(static_cast<uint32_t>(zp)) * 2.3283064365386963e-10f;
-            } else {  // beyond the table: the end interval continued linearly
-              iu = ip < 0 ? 0 : kZTabN - 2;
-              t = static_cast<float>(static_cast<double>(zp - (static_cast<int64_t>(iu) << 32)) *
-                                     2.3283064365386963e-10);
-            }
-            const float zt0 = a.ztab[iu], zt1 = a.ztab[iu + 1];
-            const float x = (zt0 + t * (zt1 - zt0)) + (1.0f - kFgpaX0);   // (1+z) - x0
-            const float ca = a.cf[0][0] + x * (a.cf[0][1] + x * a.cf[0][2]);
-            const float cb = a.cf[1][0] + x * (a.cf[1][1] + x * a.cf[1][2]);
-            const float cc = a.cf[2][0] + x * (a.cf[2][1] + x * a.cf[2][2]);
-            const float F = __expf(-ca * __expf(cb * (d + cc * e)));
+            ZNodes z;
+            z.send(a.ztab, zpos[u]);
+            const float F = fgpa_flux(a, z, d, e);
             if (a.flux) a.flux[off + j] = F;
             if (want_bins) {
               while (bin >= 0 && j >= jb[bin]) --bin;  // pixel j lies below bin's upper edge

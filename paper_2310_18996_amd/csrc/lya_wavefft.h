@@ -9,7 +9,7 @@
 namespace lya {
 
 constexpr int kHalfMax = 1024;                        // complex length <= 1024
-constexpr int kHalfBuf = kHalfMax + kHalfMax / 16;    // one padding slot per 16
+constexpr int kHalfBuf = kHalfMax + kHalfMax / 16 - 1;   // a padding slot after every 16 but the last
 
 __device__ __forceinline__ int pidx(int i) { return i + (i >> 4); }   // pidx(a + b) = pidx(a) + pidx(b) if a & b == 0
 
