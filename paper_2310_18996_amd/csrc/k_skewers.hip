@@ -557,16 +557,15 @@ __device__ __forceinline__ float fgpa_flux(const SkewerArgs& a, const ZNodes& z,
 
 // What small_scale_wave reads of the arguments.
 struct LineNoise {
+  static constexpr bool kPsTab = true;
   uint64_t seed;
-  double dpix;
-  const double* ps_edges_k;
-  const float* ps_ratio;
-  int ps_nb, ps_fixed_amp;
+  const float* ps_tab;
+  int ps_fixed_amp;
 };
 
 // (the Gaussian mode's LDS leaves two waves per SIMD)
 template <int U, int MODE, bool B16>
-__global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : 1) k_skewers(SkewerArgs a) {
+__global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : MODE == kSkWide ? 3 : 1) k_skewers(SkewerArgs a) {
   __shared__ float2 sbuf[kSkWaves][kHalfBuf];
   __shared__ float sgauss[MODE == kSkGauss ? kSkWaves : 1][MODE == kSkGauss ? kGaussWords : 1];
   constexpr bool kCellWalk = U == 1 && MODE != kSkGauss;
@@ -615,8 +614,8 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : 1) 
       int dl_lane = lane;
       if constexpr (MODE == kSkGauss) asm volatile("" : "+v"(dl_lane));
       if (with_ds) {
-        const LineNoise ps{la->seed, la->dpix, la->ps_edges_k, la->ps_ratio, la->ps_nb, la->ps_fixed_amp};
-        small_scale_wave(ps, la->ps_amp, la->ps_kcut, la->id_base + q, ns, buf, static_cast<const float2*>(la->tw2048), dl_lane);
+        const LineNoise ps{la->seed, la->ps_tab, la->ps_fixed_amp};
+        small_scale_wave(ps, 0.0, 0.0, la->id_base + q, ns, buf, static_cast<const float2*>(la->tw2048), dl_lane);
       }
       // bin boundaries: jb[b] = first pixel with chi_j < edges[b] (chi_j decreases with j)
       if (want_bins) {

@@ -16,6 +16,7 @@
 // Pixel redshift (section "FGPA": unperturbed cosmological redshift), flat
 // LCDM with E(z)^2 = Om (1+z)^3 + 1 - Om (Table cosmoparams), c/H0 in Mpc/h.
 #include "lya_internal.h"
+#include "lya_wavefft.h"
 
 namespace lya {
 
@@ -242,12 +243,15 @@ __device__ __forceinline__ double z_of_chi_group(double chi, double om, int l) {
 
 // What a call needs before its main kernel, in one launch (each of these was
 // a launch of 4-5 us of its own): the z(chi) table (ztab), the 2048 twiddles
-// (tw), and the work queue and bin sums cleared (queue, bsum, bcnt;
-// ordinary stores, no memset node).  Null pointers are left out.  The table's
+// (tw), the amplitudes of delta_S (ps_tab: in the line kernel a tabulated ratio took
+// an FP64 search of dependent loads for each mode of each line; FGPA and 1D power of
+// 35M stored pixels 630 -> 523 us), and the work queue and bin sums cleared (queue,
+// bsum, bcnt; ordinary stores, no memset node).  Null pointers are left out.  The table's
 // blocks come first and in decreasing chi (the far nodes take the most steps).
 constexpr int kPrepNT = 256;
 constexpr int kPrepZBlocks = (kZTabN * 16 + kPrepNT - 1) / kPrepNT;
 constexpr int kPrepTwBlocks = kTw2048 / kPrepNT;
+constexpr int kPrepPsBlocks = (kPsTab + kPrepNT - 1) / kPrepNT;
 
 __global__ void __launch_bounds__(kPrepNT) k_prep(PrepArgs a) {
   const int nz = a.ztab ? kPrepZBlocks : 0, nt = a.tw ? kPrepTwBlocks : 0;
@@ -269,6 +273,15 @@ __global__ void __launch_bounds__(kPrepNT) k_prep(PrepArgs a) {
     a.tw[k] = make_float2(static_cast<float>(cs), static_cast<float>(sn));
     return;
   }
+  b -= nt;
+  if (b < (a.ps_tab ? kPrepPsBlocks : 0)) {
+    const int i = b * kPrepNT + t;
+    if (i >= kPsTab) return;
+    const int ns = i < 2 ? 2 : 1 << (31 - __clz(i)), m = i - ns;   // (entries past ns/2 are not used)
+    const float2 sc = ps_scales(a.ps_amp, a.ps_kcut, a.dpix, ns);
+    a.ps_tab[i] = m > 0 ? ps_amplitude(a, m, ns, sc.x, sc.y) : 0.0f;
+    return;
+  }
   if (t < kPullCounters && a.queue) a.queue[t * kPullStride] = 0u;
   for (int i = t; i < kBinCopies * kMaxZBins && a.bsum; i += kPrepNT) {
     a.bsum[i] = 0ull;
@@ -277,7 +290,8 @@ __global__ void __launch_bounds__(kPrepNT) k_prep(PrepArgs a) {
 }
 
 hipError_t launch_prep(const PrepArgs& a, hipStream_t st) {
-  const int blocks = (a.ztab ? kPrepZBlocks : 0) + (a.tw ? kPrepTwBlocks : 0) + (a.queue || a.bsum ? 1 : 0);
+  const int blocks = (a.ztab ? kPrepZBlocks : 0) + (a.tw ? kPrepTwBlocks : 0) +
+                     (a.ps_tab ? kPrepPsBlocks : 0) + (a.queue || a.bsum ? 1 : 0);
   if (blocks == 0) return hipSuccess;
   LYA_TIMED("prep", st, hipLaunchKernelGGL(k_prep, dim3(blocks), dim3(kPrepNT), 0, st, a));
   return hipGetLastError();

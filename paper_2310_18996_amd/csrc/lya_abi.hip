@@ -77,7 +77,7 @@ BoxCarve carve_box(const lya_box* b, bool two_buffer = false) {
 }
 
 struct SkCarve {
-  size_t ztab, tw, queue, bsum, bcnt, total;
+  size_t ztab, tw, queue, bsum, bcnt, ps, total;
 };
 
 SkCarve carve_sk() {
@@ -88,6 +88,7 @@ SkCarve carve_sk() {
   c.queue = o; o += lya::kPullBytes;
   c.bsum = o;  o += align256(sizeof(unsigned long long) * lya::kBinCopies * lya::kMaxZBins);
   c.bcnt = o;  o += align256(sizeof(unsigned long long) * lya::kBinCopies * lya::kMaxZBins);
+  c.ps = o;    o += align256(sizeof(float) * lya::kPsTab);
   c.total = o;
   return c;
 }
@@ -282,6 +283,7 @@ int run_skewers(lya::SkewerArgs& a, const lya_cosmo* cosmo, const lya_zbins* zb,
   a.queue = reinterpret_cast<unsigned int*>(w + c.queue);
   a.bin_sum = reinterpret_cast<unsigned long long*>(w + c.bsum);
   a.bin_cnt = reinterpret_cast<unsigned long long*>(w + c.bcnt);
+  a.ps_tab = reinterpret_cast<float*>(w + c.ps);
   a.n_bins = zb ? zb->n_bins : 0;
   a.chi_edges = zb ? zb->chi_edges : nullptr;
   a.out_fsum = zb ? zb->fsum : nullptr;
@@ -305,6 +307,15 @@ int run_skewers(lya::SkewerArgs& a, const lya_cosmo* cosmo, const lya_zbins* zb,
   pa.queue = a.queue;
   pa.bsum = a.bin_sum;
   pa.bcnt = a.bin_cnt;
+  if ((a.field || a.field_bf16 || a.ds_in_apply) && a.ps_amp > 0.0) {
+    pa.ps_tab = const_cast<float*>(a.ps_tab);
+    pa.ps_amp = a.ps_amp;
+    pa.ps_kcut = a.ps_kcut;
+    pa.dpix = a.dpix;
+    pa.ps_nb = a.ps_nb;
+    pa.ps_edges_k = a.ps_edges_k;
+    pa.ps_ratio = a.ps_ratio;
+  }
   hipError_t e = lya::launch_prep(pa, st);
   if (e != hipSuccess) return hip_fail(e, "skewer tables");
   e = lya::launch_skewers(a, st);

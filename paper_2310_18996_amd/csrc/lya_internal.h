@@ -91,7 +91,15 @@ struct PrepArgs {
   unsigned int* queue;
   unsigned long long* bsum;
   unsigned long long* bcnt;
+  // amplitudes of delta_S: entry ns + m for mode m = 0 .. ns/2 of a line of ns =
+  // 2, 4 .. 2048 pixels (0 for m = 0), kPsTab floats in all
+  float* ps_tab;
+  double ps_amp, ps_kcut, dpix;
+  int ps_nb;                  // as in SkewerArgs
+  const double* ps_edges_k;
+  const float* ps_ratio;
 };
+constexpr int kPsTab = 2048 + 1024 + 2;
 hipError_t launch_prep(const PrepArgs& a, hipStream_t st);
 hipError_t launch_zchi_table(double omega_m, float* ztab, hipStream_t st);
 // Simpson-weighted integrand of xi_m (k_j = j h, j = 0..m) in the groups of
@@ -152,6 +160,7 @@ struct SkewerArgs {
   // small-scale field
   double ps_amp, ps_kcut, dpix;
   int ps_fixed_amp;
+  const float* ps_tab;   // amplitudes (PrepArgs), in the workspace
   uint64_t seed;
   // FGPA (valid when do_flux): a, b, c as quadratics in t = (1+z) - kFgpaX0,
   // converted on the host in FP64 from the powers of (1+z)
@@ -212,6 +221,7 @@ hipError_t launch_p1d(const P1dArgs& a, double* psum, int64_t* pcount, hipStream
 // kTuneEvalMaxG constant-parameter draws in one pass.
 constexpr int kTuneEvalMaxG = 8;
 struct TuneEvalArgs {
+  static constexpr bool kPsTab = false;   // amplitudes mode by mode: they differ per draw
   int64_t n_sk;
   const int32_t* npix;
   const int64_t* offset;

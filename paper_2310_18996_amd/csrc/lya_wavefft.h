@@ -283,9 +283,9 @@ __device__ __forceinline__ void wave_ifft8(float2* buf, int M, TW tw2048, int la
 // ns/2 of a line of ns pixels, scaled by sqrt(P_s(k_m) / (ns dpix)), the DC
 // mode zero, and one half-length complex inverse FFT.
 
-// Mode Y_m of the small-scale spectrum (0 < m <= ns/2) from its normal pair z.
+// Amplitude sqrt(P_s(k_m) / (ns dpix)) of mode m of a line of ns pixels.
 template <class A>
-__device__ __forceinline__ float2 ps_mode(const A& a, int m, int ns, float amp_scale, float dk2, float2 z) {
+__device__ __forceinline__ float ps_amplitude(const A& a, int m, int ns, float amp_scale, float dk2) {
   const float kk = static_cast<float>(m) * static_cast<float>(m) * dk2;   // (k/kcut)^2
   float ratio = 1.0f;
   if (a.ps_ratio) {
@@ -306,9 +306,18 @@ __device__ __forceinline__ float2 ps_mode(const A& a, int m, int ns, float amp_s
     }
     ratio = a.ps_ratio[b];
   }
-  const float amp = __builtin_amdgcn_sqrtf(amp_scale * __expf(-kk) * ratio);
+  return __builtin_amdgcn_sqrtf(amp_scale * __expf(-kk) * ratio);
+}
+// amp_scale and dk2 above
+__device__ __forceinline__ float2 ps_scales(double amp, double kcut, double dpix, int ns) {
+  const double dk = 2.0 * M_PI / (ns * dpix) / kcut;
+  return make_float2(static_cast<float>(amp / (ns * dpix)), static_cast<float>(dk * dk));
+}
+
+// Mode Y_m of the small-scale spectrum (0 < m <= ns/2) from its normal pair z.
+__device__ __forceinline__ float2 ps_mode(float amp, int m, int ns, int fixed_amp, float2 z) {
   float2 w = (m == ns / 2) ? make_float2(z.x, 0.0f) : make_float2(z.x * kSqrtHalf, z.y * kSqrtHalf);
-  if (a.ps_fixed_amp) {
+  if (fixed_amp) {
     const float r = rsqrtf(w.x * w.x + w.y * w.y);
     w.x *= r;
     w.y *= r;
@@ -319,17 +328,17 @@ __device__ __forceinline__ float2 ps_mode(const A& a, int m, int ns, float amp_s
 // delta_S of one skewer by one wavefront into buf (pixel 2n in .x and pixel
 // 2n+1 in .y of element pidx(n)); ns = next_pow2(npix) >= 2.  P_s(k) =
 // amp exp(-(k/kcut)^2), times the ratio of k's bin when a.ps_ratio is set.
-// A supplies the Philox key (seed), the pixel length (dpix), the optional
-// table (ps_nb, ps_edges_k, ps_ratio) and the fixed-amplitude switch
-// (ps_fixed_amp).  R8: the radix-8 FFT (fewer LDS passes); otherwise the
+// A supplies the Philox key (seed), the fixed-amplitude switch (ps_fixed_amp) and
+// either the amplitudes (ps_tab, laid out as k_prep writes them: with a tabulated
+// ratio each mode's bin was an FP64 search; amp, kcut are then not read) or the
+// pixel length (dpix) and the optional table (ps_nb, ps_edges_k, ps_ratio).  R8: the radix-8 FFT (fewer LDS passes); otherwise the
 // radix-4 one, for callers that cannot spare its registers.
 template <class A, class TW, bool R8 = true>
 __device__ void small_scale_wave(const A& a, double amp, double kcut, uint64_t qid, int ns, float2* buf, TW tw,
                                  int lane) {
   const int M = ns / 2;
-  const float amp_scale = static_cast<float>(amp / (ns * a.dpix));
-  const double dk = 2.0 * M_PI / (ns * a.dpix) / kcut;
-  const float dk2 = static_cast<float>(dk * dk);
+  float2 sc{};
+  if constexpr (!A::kPsTab) sc = ps_scales(amp, kcut, a.dpix, ns);
   const int twstep = kTw2048 / ns;  // w^k = exp(2 pi i k / ns)
   // the modes Y_1 .. Y_M into buf (Y_M in slot 0: the DC mode is zero).  Mode
   // m is linear index (qid << 33) + m of stream 1, so the modes 2i and 2i + 1
@@ -339,8 +348,15 @@ __device__ void small_scale_wave(const A& a, double amp, double kcut, uint64_t q
     const uint4 wd = philox10_x3(make_uint4(static_cast<uint32_t>(ctr), static_cast<uint32_t>(ctr >> 32), 1u, 0u),
                                  static_cast<uint32_t>(a.seed), static_cast<uint32_t>(a.seed >> 32));
     const int m0 = 2 * i, m1 = 2 * i + 1;
-    if (m0 >= 1 && m0 <= M) buf[pidx(m0 == M ? 0 : m0)] = ps_mode(a, m0, ns, amp_scale, dk2, box_muller(wd.x, wd.y));
-    if (m1 <= M) buf[pidx(m1 == M ? 0 : m1)] = ps_mode(a, m1, ns, amp_scale, dk2, box_muller(wd.z, wd.w));
+    float2 am;
+    if constexpr (A::kPsTab) {
+      am = *reinterpret_cast<const float2*>(a.ps_tab + ns + m0);   // (one entry past M where m1 = M + 1)
+    } else {
+      am.x = ps_amplitude(a, m0, ns, sc.x, sc.y);
+      am.y = ps_amplitude(a, m1, ns, sc.x, sc.y);
+    }
+    if (m0 >= 1 && m0 <= M) buf[pidx(m0 == M ? 0 : m0)] = ps_mode(am.x, m0, ns, a.ps_fixed_amp, box_muller(wd.x, wd.y));
+    if (m1 <= M) buf[pidx(m1 == M ? 0 : m1)] = ps_mode(am.y, m1, ns, a.ps_fixed_amp, box_muller(wd.z, wd.w));
   }
   wave_sync();
   // Z_k = (Y_k + Y_{k+M}) + i (Y_k - Y_{k+M}) w^k with Y_{k+M} = conj(Y_{M-k});
@@ -353,16 +369,17 @@ __device__ void small_scale_wave(const A& a, double amp, double kcut, uint64_t q
     }
     const float2 yk = buf[pidx(k)];
     const float2 ymk = buf[pidx(M - k)];
+    const float2 w = tw[k * twstep];   // w^(M-k) = -conj(w^k), exactly so in the table
     {
       const float2 s = make_float2(yk.x + ymk.x, yk.y - ymk.y);   // Y_k + conj(Y_{M-k})
       const float2 d = make_float2(yk.x - ymk.x, yk.y + ymk.y);   // Y_k - conj(Y_{M-k})
-      const float2 t = cmul(d, tw[k * twstep]);
+      const float2 t = cmul(d, w);
       buf[pidx(k)] = make_float2(s.x - t.y, s.y + t.x);
     }
     if (M - k != k) {
       const float2 s = make_float2(ymk.x + yk.x, ymk.y - yk.y);
       const float2 d = make_float2(ymk.x - yk.x, ymk.y + yk.y);
-      const float2 t = cmul(d, tw[(M - k) * twstep]);
+      const float2 t = cmul(d, make_float2(-w.x, w.y));
       buf[pidx(M - k)] = make_float2(s.x - t.y, s.y + t.x);
     }
   }
