@@ -26,6 +26,7 @@
 // atomic queue and owns a skewer at a time (its small-scale FFT lives in the
 // wave's slice of LDS, so no block-wide barrier is needed per skewer).
 #include <algorithm>
+#include <type_traits>
 
 #include "lya_internal.h"
 #include "lya_pull.h"
@@ -352,6 +353,19 @@ __device__ __forceinline__ float gauss_slots(float t, int sh, float (&w)[8]) {
   return s;
 }
 
+// eta_par of a voxel from its four boxes; explicit fused multiply-adds, so that
+// every path rounds alike.
+struct WideWeights {
+  float xx, yy, zz, xy, xz, yz;
+  __device__ __forceinline__ float eta(float2 a0, float2 a1, float2 a2, float2 a3) const {
+    float e = __builtin_fmaf(zz, a0.y, xx * a1.x);
+    e = __builtin_fmaf(yy, a1.y, e);
+    e = __builtin_fmaf(xy, a2.x, e);
+    e = __builtin_fmaf(xz, a2.y, e);
+    return __builtin_fmaf(yz, a3.x, e);
+  }
+};
+
 // c: values at the pixel's z in the columns (x0, y0), (x0, y1), (x1, y0), (x1, y1)
 __device__ __forceinline__ float bilerp(float tx, float ty, const float (&c)[4]) {
   const float c0 = c[0] + ty * (c[1] - c[0]);
@@ -445,9 +459,9 @@ struct BinWalk {
 // What bounded the gathers: the address unit (20 cycles each, 70% busy) and that
 // every step waited for the stores of the step before (loads and stores complete
 // in order).  1.1e9 pixels of 1M lines in a 2048^3 box without delta_S and FGPA
-// 6.7 -> 6.0 ms, with both and bins 11.9 -> 11.1 ms; 35M wide-angle pixels (four
-// BF16 boxes, 512^3) 592 -> 496 us.  The columns alone, without the order of loads
-// and stores, took 13.1 ms.
+// 6.7 -> 5.6 ms, with both and bins 11.9 -> 10.6 ms (now two thirds vector issue);
+// 35M wide-angle pixels in 512^3 (four BF16 boxes) 592 -> 481 us, (FP32) 788 -> 696
+// us.  The columns alone, without the order of loads and stores, took 13.1 ms.
 constexpr int kCells = 16;
 __device__ __forceinline__ bool cells_fit(int64_t sx, int64_t sy, int64_t sz) {
   // 63 steps cross at most floor(63 |s|) + 1 boundaries of an axis
@@ -456,7 +470,11 @@ __device__ __forceinline__ bool cells_fit(int64_t sx, int64_t sy, int64_t sz) {
   return a < (1u << 30) && b < (1u << 30) && c < (1u << 30) &&
          ((63 * a) >> 32) + ((63 * b) >> 32) + ((63 * c) >> 32) + 3 < kCells;
 }
-__device__ __forceinline__ uint32_t abs_diff(uint32_t a, uint32_t b) { return max(a, b) - min(a, b); }
+__device__ __forceinline__ uint32_t abs_diff(uint32_t a, uint32_t uniform) {
+  uint32_t r;
+  asm("v_sad_u32 %0, %1, %2, 0" : "=v"(r) : "v"(a), "s"(uniform));
+  return r;
+}
 
 template <int MODE, bool B16>
 struct CellWalk {
@@ -533,10 +551,11 @@ __device__ __forceinline__ int64_t z_step(double dchi) { return llrint(dchi * (4
 // and the place between them.
 struct ZNodes {
   float z0, z1, t;
-  __device__ __forceinline__ void send(const float* ztab, int64_t zp) {
+  // inside (uniform): the position is known to lie in the table
+  __device__ __forceinline__ void send(const float* ztab, int64_t zp, bool inside = false) {
     const int64_t ip = zp >> 32;
     int iu;
-    if (ip >= 0 && ip <= kZTabN - 2) {
+    if (inside || (ip >= 0 && ip <= kZTabN - 2)) {
       iu = static_cast<int>(ip);
       t = static_cast<float>(static_cast<uint32_t>(zp)) * 2.3283064365386963e-10f;
     } else {  // beyond the table: the end interval continued linearly
@@ -632,42 +651,47 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : MOD
         sz = la->step_fx[3 * q + 2];
       }
       // wide-angle weights u_p u_q (off-diagonal ones doubled), u = step/|step|
-      float wxx = 0.0f, wyy = 0.0f, wzz = 0.0f, wxy = 0.0f, wxz = 0.0f, wyz = 0.0f;
+      WideWeights ww{};
       if (MODE == kSkWide) {
         const double ux = static_cast<double>(sx), uy = static_cast<double>(sy), uz = static_cast<double>(sz);
         const double r2 = ux * ux + uy * uy + uz * uz;
         const double ir2 = r2 > 0.0 ? 1.0 / r2 : 0.0;
-        wxx = static_cast<float>(ux * ux * ir2);
-        wyy = static_cast<float>(uy * uy * ir2);
-        wzz = static_cast<float>(uz * uz * ir2);
-        wxy = static_cast<float>(2.0 * ux * uy * ir2);
-        wxz = static_cast<float>(2.0 * ux * uz * ir2);
-        wyz = static_cast<float>(2.0 * uy * uz * ir2);
+        ww.xx = static_cast<float>(ux * ux * ir2);
+        ww.yy = static_cast<float>(uy * uy * ir2);
+        ww.zz = static_cast<float>(uz * uz * ir2);
+        ww.xy = static_cast<float>(2.0 * ux * uy * ir2);
+        ww.xz = static_cast<float>(2.0 * ux * uz * ir2);
+        ww.yz = static_cast<float>(2.0 * uy * uz * ir2);
       }
       if constexpr (kCellWalk) {
         if (gather && cells_fit(sx, sy, sz) && np < (1 << 28)) {
           // all loads of the next 64 pixels are sent for before the stores of these
           const int64_t uoff = lane_i64(off, 0);
-          const LineOut dens(la->dens, uoff, np), eta(la->eta, uoff, np), flux(la->do_flux ? la->flux : nullptr, uoff, np);
+          const LineOut dens(la->dens, uoff, np), eta(la->eta, uoff, np), flux(la->flux, uoff, np);
           BinWalk bins;
           if (want_bins) bins.start(jb, la->n_bins);
+          const float* ds = reinterpret_cast<const float*>(buf) + lane + 2 * (lane >> 5);   // pixel j at j + 2 (j / 32)
           CellWalk<MODE, B16> walk;
           ZNodes zn;
           const int64_t zstep = z_step(la->dchi);
           int64_t zp = z_start(chi0) - lane * zstep;
+          // the line, and the step sent for past its end, within the z(chi) table
+          const int64_t zfirst = lane_i64(zp, 0), zlast = zfirst - static_cast<int64_t>(np + 127) * zstep;
+          constexpr int64_t kZEnd = static_cast<int64_t>(kZTabN - 1) << 32;
+          const bool inside = zfirst >= 0 && zfirst < kZEnd && zlast >= 0 && zlast < kZEnd;
           walk.start(ox, oy, oz, sx, sy, sz, lane);
           walk.send(a, sx, sy, sz, N, NN, lane);
-          zn.send(a.ztab, zp);
           float4* rec = scell[wv];
+          // (as two loops: a branch around the nodes' loads would hide their number)
+          auto line = [&](auto with_flux) {
+          constexpr bool FLUX = decltype(with_flux)::value;
+          if (FLUX) zn.send(a.ztab, zp, inside);
           for (int it = 0; it < np; it += 64) {
             const int j = it + lane;
             float2 v0 = gauss_cell(walk.v[0][0]), v1 = gauss_cell(walk.v[0][1]);
             if constexpr (MODE == kSkWide) {
-              auto wide = [&](const float2& a0, const float2& a1, const float2& a2, const float2& a3) {
-                return wzz * a0.y + wxx * a1.x + wyy * a1.y + wxy * a2.x + wxz * a2.y + wyz * a3.x;
-              };
-              v0.y = wide(v0, gauss_cell(walk.v[1][0]), gauss_cell(walk.v[2][0]), gauss_cell(walk.v[3][0]));
-              v1.y = wide(v1, gauss_cell(walk.v[1][1]), gauss_cell(walk.v[2][1]), gauss_cell(walk.v[3][1]));
+              v0.y = ww.eta(v0, gauss_cell(walk.v[1][0]), gauss_cell(walk.v[2][0]), gauss_cell(walk.v[3][0]));
+              v1.y = ww.eta(v1, gauss_cell(walk.v[1][1]), gauss_cell(walk.v[2][1]), gauss_cell(walk.v[3][1]));
             }
             rec[lane] = make_float4(v0.x, v1.x - v0.x, v0.y, v1.y - v0.y);
             const float tx = static_cast<float>(walk.fr[0]) * 2.3283064365386963e-10f;
@@ -677,8 +701,10 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : MOD
             const ZNodes z = zn;
             wave_sync();
             walk.send(a, sx, sy, sz, N, NN, lane);   // (past the line's end too: every address is in the box)
-            zp -= 64 * zstep;
-            zn.send(a.ztab, zp);
+            if (FLUX) {
+              zp -= 64 * zstep;
+              zn.send(a.ztab, zp, inside);
+            }
             float col[2][4];
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -688,17 +714,19 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : MOD
             }
             float d = bilerp(tx, ty, col[0]);
             const float e = bilerp(tx, ty, col[1]);
-            if (with_ds) {
-              const float2 z2 = buf[pidx((j < ns ? j : 0) >> 1)];   // (in the line's slots also past its end)
-              d += (j & 1) ? z2.y : z2.x;
-            }
+            if (with_ds) d += ds[it + (it >> 4)];   // (past the line's end: unused slots of the buffer)
             wave_sync();   // the records are written again
             dens.put(j, d);
             eta.put(j, e);
-            const float F = fgpa_flux(a, z, d, e);
-            flux.put(j, F);
-            if (want_bins) bins.add(jb, it, np, j, F, s_sum, lane);
+            if (FLUX) {
+              const float F = fgpa_flux(a, z, d, e);
+              flux.put(j, F);
+              if (want_bins) bins.add(jb, it, np, j, F, s_sum, lane);
+            }
           }
+          };
+          if (la->do_flux) line(std::true_type{});
+          else line(std::false_type{});
           if (want_bins) bins.end(jb, la->n_bins, s_sum, s_cnt, lane);
           wave_sync();  // the wave's LDS slice is reused by its next skewer
           continue;
@@ -850,9 +878,7 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : MOD
                 }
 #pragma unroll
                 for (int k = 0; k < G; ++k) {
-                  const float e = wzz * w0[k].y + wxx * w1[k].x + wyy * w1[k].y + wxy * w2[k].x + wxz * w2[k].y +
-                                  wyz * w3[k].x;
-                  c[u][h + k] = make_float2(w0[k].x, e);
+                  c[u][h + k] = make_float2(w0[k].x, ww.eta(w0[k], w1[k], w2[k], w3[k]));
                 }
                 if constexpr (G < 8) __builtin_amdgcn_sched_barrier(0);
               }
