@@ -1039,9 +1039,12 @@ hipError_t launch_skewers(SkewerArgs a, hipStream_t st) {
   if (blocks < 1) blocks = 1;
   // with at most a skewer per wave the pass is one skewer's latency: the gathers of
   // four steps of 64 pixels go out together instead of step by step (18.6 ->
-  // 17.4 us for 500 skewers of 256 pixels; every unroll gives the same bits)
+  // 17.4 us for 500 skewers of 256 pixels; every unroll gives the same bits).  The
+  // wide-angle pass walks cells there as well: 8 loads a step in flight against 64 of
+  // two steps at three waves per SIMD (500 lines in 512^3, the call: 59 -> 49 us, FP32
+  // boxes 64 -> 55 us; 3000 lines 70 -> 61 and 88 -> 78 us)
   const bool few = a.n_sk <= blocks * kSkWaves;
-  const int u = few ? 4 : a.unroll == 1 || a.unroll == 4 ? a.unroll : 2;
+  const int u = few && !a.is_wide ? 4 : a.unroll == 1 || a.unroll == 4 ? a.unroll : 2;
   const dim3 grid(static_cast<unsigned>(blocks));
   if (a.field_bf16)
     launch_skewer_kernel<true>(a, u, grid, st);

@@ -2,7 +2,9 @@
 waves, steps that cross few cells in 64 pixels) against the per-pixel gathers of
 a call with few lines, bit for bit, and those against the oracle: steps up to and
 past what 16 records hold, in all directions and along single axes, both storage
-types, the wide-angle boxes, lines ending around 64 pixels, and outputs left out."""
+types, the wide-angle boxes (whose calls with few lines walk cells too, and are held
+against the oracle in test_gpu_wide), lines ending around 64 pixels, and outputs
+left out."""
 import numpy as np
 import pytest
 import torch
