@@ -664,7 +664,7 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : MOD
         ww.yz = static_cast<float>(2.0 * uy * uz * ir2);
       }
       if constexpr (kCellWalk) {
-        if (gather && cells_fit(sx, sy, sz) && np < (1 << 28)) {
+        if (gather && cells_fit(sx, sy, sz) && np > 0 && np < (1 << 28)) {
           // all loads of the next 64 pixels are sent for before the stores of these
           const int64_t uoff = lane_i64(off, 0);
           const LineOut dens(la->dens, uoff, np), eta(la->eta, uoff, np), flux(la->flux, uoff, np);
@@ -675,10 +675,12 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : MOD
           ZNodes zn;
           const int64_t zstep = z_step(la->dchi);
           int64_t zp = z_start(chi0) - lane * zstep;
-          // the line, and the step sent for past its end, within the z(chi) table
+          // the line, and the step sent for past its end, within the z(chi) table (a
+          // line that is shorter than the table, so that zlast cannot wrap back into it)
           const int64_t zfirst = lane_i64(zp, 0), zlast = zfirst - static_cast<int64_t>(np + 127) * zstep;
           constexpr int64_t kZEnd = static_cast<int64_t>(kZTabN - 1) << 32;
-          const bool inside = zfirst >= 0 && zfirst < kZEnd && zlast >= 0 && zlast < kZEnd;
+          const bool inside = static_cast<double>(np + 127) * la->dchi < kZTabN * kZTabH && zfirst >= 0 &&
+                              zfirst < kZEnd && zlast >= 0 && zlast < kZEnd;
           walk.start(ox, oy, oz, sx, sy, sz, lane);
           walk.send(a, sx, sy, sz, N, NN, lane);
           float4* rec = scell[wv];
