@@ -470,6 +470,14 @@ __device__ __forceinline__ bool cells_fit(int64_t sx, int64_t sy, int64_t sz) {
   return a < (1u << 30) && b < (1u << 30) && c < (1u << 30) &&
          ((63 * a) >> 32) + ((63 * b) >> 32) + ((63 * c) >> 32) + 3 < kCells;
 }
+// A line from here whose steps reach less than 2^62 in all (2^28 pixels of a quarter
+// of a cell, 2^31 of a third) stays within 64 bits.  Positions that wrap, at +-2^31
+// cells, are right modulo the box, but their cells are no longer in the order that
+// the cell walk and the 7^3 windows count them in.
+__device__ __forceinline__ bool no_wrap(int64_t ox, int64_t oy, int64_t oz) {
+  constexpr int64_t kHalf = int64_t(1) << 62;
+  return ox >= -kHalf && ox < kHalf && oy >= -kHalf && oy < kHalf && oz >= -kHalf && oz < kHalf;
+}
 __device__ __forceinline__ uint32_t abs_diff(uint32_t a, uint32_t uniform) {
   uint32_t r;
   asm("v_sad_u32 %0, %1, %2, 0" : "=v"(r) : "v"(a), "s"(uniform));
@@ -664,7 +672,7 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : MOD
         ww.yz = static_cast<float>(2.0 * uy * uz * ir2);
       }
       if constexpr (kCellWalk) {
-        if (gather && cells_fit(sx, sy, sz) && np > 0 && np < (1 << 28)) {
+        if (gather && cells_fit(sx, sy, sz) && no_wrap(ox, oy, oz) && np > 0 && np < (1 << 28)) {
           // all loads of the next 64 pixels are sent for before the stores of these
           const int64_t uoff = lane_i64(off, 0);
           const LineOut dens(la->dens, uoff, np), eta(la->eta, uoff, np), flux(la->flux, uoff, np);
@@ -773,7 +781,8 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : MOD
         if constexpr (B16) fb = a.field_bf16;
         else fb = a.field;
         constexpr int64_t kThird = (int64_t(1) << 32) / 3;
-        shared = sx < kThird && sx > -kThird && sy < kThird && sy > -kThird && sz < kThird && sz > -kThird;
+        shared = sx < kThird && sx > -kThird && sy < kThird && sy > -kThird && sz < kThird && sz > -kThird &&
+                 no_wrap(ox, oy, oz);
         if (shared && np > 0) {
           geo = gauss_geo(o3, s3, 0, np, lane);
           if (geo.fast) gauss_load<B16>(fb, geo, N, NN, lane, pre);
