@@ -75,22 +75,12 @@ enum { kSkTri = 0, kSkWide = 1, kSkGauss = 2 };
 // point c (standard deviation one voxel, section "Gaussian fields along lines
 // of sight"): the weights separate into 7 per axis, exp(-(o - t)^2/2) with
 // t = u - c in [-1/2, 1/2), and the average divides by their product sum.
-// The general form, straight from the box: for lines with steps of a third of a
-// cell or more (gauss_geo), whose neighbouring pixels share little; x and y
-// weights where they are needed.
-template <bool B16>
-__device__ __forceinline__ void gauss7_at(const SkewerArgs& a, int64_t px, int64_t py, int64_t pz, int N, size_t NN,
-                                          float& d, float& e) {
-  const int64_t p3[3] = {px, py, pz};
-  float t[3];
-  int c[3];
-#pragma unroll
-  for (int ax = 0; ax < 3; ++ax) {
-    const uint32_t fr = static_cast<uint32_t>(p3[ax]);
-    const int up = static_cast<int>(fr >> 31);
-    c[ax] = static_cast<int>(((p3[ax] >> 32) + up) & (N - 1));
-    t[ax] = static_cast<float>(fr) * 2.3283064365386963e-10f - static_cast<float>(up);
-  }
+// The general form, a pixel per lane, for lines with steps of a third of a cell or
+// more (gauss_geo), whose neighbouring pixels share little; x and y weights where
+// they are needed.  row(i, jy): where the z run of plane i and y row jy starts;
+// cell(r, k): its k-th voxel.
+template <class ROW, class CELL>
+__device__ __forceinline__ void gauss7_sum(const float (&t)[3], ROW row, CELL cell, float& d, float& e) {
   auto weight = [](int o, float tt) {
     const float dd = static_cast<float>(o - 3) - tt;
     return __expf(-0.5f * dd * dd);
@@ -104,16 +94,15 @@ __device__ __forceinline__ void gauss7_at(const SkewerArgs& a, int64_t px, int64
   float ax_ = 0.0f, ay_ = 0.0f;
 #pragma unroll 1
   for (int i = 0; i < 7; ++i) {
-    const size_t rx = static_cast<size_t>((c[0] + i - 3) & (N - 1)) * NN;
     float bx = 0.0f, by = 0.0f;
     sy = 0.0f;
 #pragma unroll
     for (int jy = 0; jy < 7; ++jy) {
-      const size_t row = rx + static_cast<size_t>((c[1] + jy - 3) & (N - 1)) * N;
+      const auto r = row(i, jy);
       float rx_ = 0.0f, ry_ = 0.0f;
 #pragma unroll
       for (int k = 0; k < 7; ++k) {
-        const float2 f = ld_field<B16>(a, row + ((c[2] + k - 3) & (N - 1)));
+        const float2 f = cell(r, k);
         rx_ += gz[k] * f.x;
         ry_ += gz[k] * f.y;
       }
@@ -130,6 +119,30 @@ __device__ __forceinline__ void gauss7_at(const SkewerArgs& a, int64_t px, int64
   const float inv = 1.0f / (sx * sy * sz);
   d = ax_ * inv;
   e = ay_ * inv;
+}
+// the pixel's nearest grid point and its offset from it
+__device__ __forceinline__ void gauss_centre(const int64_t (&p)[3], int (&c)[3], float (&t)[3]) {
+#pragma unroll
+  for (int ax = 0; ax < 3; ++ax) {
+    const uint32_t fr = static_cast<uint32_t>(p[ax]);
+    const int up = static_cast<int>(fr >> 31);
+    c[ax] = static_cast<int>((p[ax] >> 32) + up);
+    t[ax] = static_cast<float>(fr) * 2.3283064365386963e-10f - static_cast<float>(up);
+  }
+}
+// straight from the box
+template <bool B16>
+__device__ __forceinline__ void gauss7_at(const SkewerArgs& a, const int64_t (&p)[3], int N, size_t NN, float& d,
+                                          float& e) {
+  int c[3];
+  float t[3];
+  gauss_centre(p, c, t);
+  gauss7_sum(
+      t,
+      [&](int i, int jy) {
+        return static_cast<size_t>((c[0] + i - 3) & (N - 1)) * NN + static_cast<size_t>((c[1] + jy - 3) & (N - 1)) * N;
+      },
+      [&](size_t r, int k) { return ld_field<B16>(a, r + ((c[2] + k - 3) & (N - 1))); }, d, e);
 }
 
 // The Gaussian-kernel average of 64 consecutive pixels on the matrix cores.
@@ -301,6 +314,59 @@ __device__ __forceinline__ void gauss_stage(const typename GaussCell<B16>::type*
     y -= wrap ? g.ny : 0;
     x += wrap ? 1 : 0;
   }
+}
+
+// The cells around pixels j1 .. j1 + last of a line without shared windows, where
+// all of them fit the wave's slice at once (steps of a third of a cell and more: up to
+// some 30 pixels, so short lines and the ends of others): loaded once, then read by
+// every pixel.  50,000 lines of 8-64 pixels at 0.35 cells per pixel: 1.97 ms straight
+// from the box, 0.96 ms so.
+struct GaussBox {
+  int lo[3], ny, nz, cells;   // first cell (to be taken modulo N), y rows, z cells, cells in all; 0: they do not fit
+};
+__device__ __forceinline__ GaussBox gauss_box(const int64_t (&o)[3], const int64_t (&st)[3], int j1, int last) {
+  constexpr int kCap = kGaussWords / 2;
+  constexpr int64_t kHalf = int64_t(1) << 31, kFar = int64_t(1) << 62, kStep = int64_t(1) << 37;
+  GaussBox g;
+  int n[3];
+  bool fits = true;
+#pragma unroll
+  for (int ax = 0; ax < 3; ++ax) {
+    // as in gauss_geo; below 2^5 cells a step from within +-2^30 cells nothing wraps
+    const int64_t pf = o[ax] + static_cast<int64_t>(j1) * st[ax] + kHalf;
+    fits = fits && st[ax] < kStep && st[ax] > -kStep && pf >= -kFar && pf < kFar;
+    const int64_t cf = pf >> 32, cl = (pf + static_cast<int64_t>(last) * st[ax]) >> 32;
+    const int64_t lo = cf < cl ? cf : cl, span = cf < cl ? cl - cf : cf - cl;
+    fits = fits && span < kCap;
+    g.lo[ax] = static_cast<int>(lo - 3);
+    n[ax] = static_cast<int>(span < kCap ? span : 0) + 7;
+  }
+  g.ny = n[1];
+  g.nz = n[2];
+  fits = fits && n[1] * n[2] <= kCap;   // (each below 2^11)
+  g.cells = fits && n[0] * (n[1] * n[2]) <= kCap ? n[0] * (n[1] * n[2]) : 0;
+  return g;
+}
+template <bool B16>
+__device__ __forceinline__ void gauss7_staged(const typename GaussCell<B16>::type* fb, const GaussBox& g,
+                                              const int64_t (&p)[3], int N, size_t NN, int lane, float2* lds, float& d,
+                                              float& e) {
+  const uint32_t msk = static_cast<uint32_t>(N - 1);
+  const int plane = g.ny * g.nz;
+  for (int v = lane; v < g.cells; v += 64) {
+    const int x = v / plane, r = v - x * plane, y = r / g.nz, z = r - y * g.nz;
+    lds[v] = gauss_cell(fb[static_cast<size_t>(static_cast<uint32_t>(g.lo[0] + x) & msk) * NN +
+                           (static_cast<uint32_t>(g.lo[1] + y) & msk) * static_cast<uint32_t>(N) +
+                           (static_cast<uint32_t>(g.lo[2] + z) & msk)]);
+  }
+  wave_sync();
+  int c[3];
+  float t[3];
+  gauss_centre(p, c, t);
+  const float2* at = lds + ((c[0] - 3 - g.lo[0]) * plane + (c[1] - 3 - g.lo[1]) * g.nz + (c[2] - 3 - g.lo[2]));
+  gauss7_sum(
+      t, [&](int i, int jy) { return at + i * plane + jy * g.nz; }, [](const float2* r, int k) { return r[k]; }, d, e);
+  wave_sync();   // the slice is loaded again
 }
 
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -594,7 +660,7 @@ struct LineNoise {
 template <int U, int MODE, bool B16>
 __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : MODE == kSkWide ? 3 : 1) k_skewers(SkewerArgs a) {
   __shared__ float2 sbuf[kSkWaves][kHalfBuf];
-  __shared__ float sgauss[MODE == kSkGauss ? kSkWaves : 1][MODE == kSkGauss ? kGaussWords : 1];
+  __shared__ __align__(8) float sgauss[MODE == kSkGauss ? kSkWaves : 1][MODE == kSkGauss ? kGaussWords : 1];
   constexpr bool kCellWalk = U == 1 && MODE != kSkGauss;
   __shared__ float4 scell[kCellWalk ? kSkWaves : 1][kCellWalk ? 4 * kCells : 1];
   __shared__ int sjb[kSkWaves][kMaxZBins + 1];
@@ -775,6 +841,7 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : MOD
       [[maybe_unused]] const int64_t o3[3] = {ox, oy, oz};
       [[maybe_unused]] const int32_t s3[3] = {static_cast<int32_t>(sx), static_cast<int32_t>(sy),
                                               static_cast<int32_t>(sz)};
+      [[maybe_unused]] const int64_t st3[3] = {sx, sy, sz};
       [[maybe_unused]] const typename GaussCell<B16>::type* fb = nullptr;
       [[maybe_unused]] bool shared = false;   // quads share their window (steps below a third of a cell)
       if constexpr (MODE == kSkGauss) {
@@ -847,8 +914,13 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : MOD
               done = !__any(!(fabsf(dl[0]) < HUGE_VALF) || !(fabsf(el[0]) < HUGE_VALF));
             }
             if (!done) {
-              const int j = min(j0, np - 1);
-              gauss7_at<B16>(a, ox + j * sx, oy + j * sy, oz + j * sz, N, NN, dl[0], el[0]);
+              const int last = min(63, np - 1 - it), j = it + min(lane, last);
+              const int64_t p3[3] = {ox + j * sx, oy + j * sy, oz + j * sz};
+              GaussBox box;
+              box.cells = 0;
+              if (!shared) box = gauss_box(o3, st3, it, last);
+              if (box.cells) gauss7_staged<B16>(fb, box, p3, N, NN, lane, reinterpret_cast<float2*>(sgauss[wv]), dl[0], el[0]);
+              else gauss7_at<B16>(a, p3, N, NN, dl[0], el[0]);
             }
           } else {
           float2 c[U][8];
