@@ -157,7 +157,8 @@ __device__ __forceinline__ float2 gen_mode(const GenParams& g, int ix, int iy, i
 }
 
 // SWZ (pass Z of the two-buffer order): pencil (kx, ky) goes to plane ky, row kx.
-template <int N, int T, int E, int KIND, bool SWZ = false>
+// LAST: the box's last pass.
+template <int N, int T, int E, int KIND, bool SWZ = false, bool LAST = KIND == KIND_X>
 struct Pass {
   static constexpr int NT = N * T / E;
   static constexpr bool PF = KIND != KIND_GENZ;  // lanes walk the T contiguous pencils first
@@ -205,11 +206,13 @@ struct Pass {
   // first radix): the first stage scatters its outputs with stride R0, which
   // without padding lands every lane group on the same banks.
   // Non-temporal accesses of the strided passes, where a box is beyond the 256 MB
-  // last-level cache and they measured faster: 512^3 y 0.44 -> 0.42, x 0.46 ->
-  // 0.42 ms (BF16 output 0.37 -> 0.34); 1024^3 y, loads split over the stages, 3.45 ->
-  // 3.32 ms with the stores alone (loads as well: 3.33; x: 3.72 and 3.70, left).
+  // last-level cache and they measured faster: 512^3 y 0.40 -> 0.37, x 0.44 ->
+  // 0.41 ms (BF16 output 0.37 -> 0.34), in the two-buffer order 0.45 -> 0.43 and 0.42 ->
+  // 0.40 ms; 1024^3 y, loads split over the stages, 3.45 -> 3.32 ms with the stores
+  // alone (loads as well: 3.33; x: 3.72 and 3.70, left).  Not the last pass of the
+  // two-buffer order at 1024^3, whose loads are not split: 3.47 ms, 3.88 with them.
   static constexpr bool kNtLoad = KIND != KIND_GENZ && N == 512;
-  static constexpr bool kNtStore = (KIND == KIND_X && N == 512) || (KIND == KIND_Y && N == 1024);
+  static constexpr bool kNtStore = (KIND == KIND_X && N == 512) || (KIND == KIND_Y && N == 1024 && !LAST);
   __device__ static __forceinline__ float2 ld2(const float2* q) {
     typedef float f2v __attribute__((ext_vector_type(2)));
     if constexpr (!kNtLoad) return *q;
@@ -550,7 +553,7 @@ template <int N, int T, int E, int KIND, int ORDER = 1, int GM = GEN_GENERIC, bo
           bool LAST = KIND == KIND_X>
 __global__ void __launch_bounds__(N * T / E) k_fft_pass(float2* __restrict__ data, uint32_t* __restrict__ out_bf16,
                                                         const float2* __restrict__ tw, GenParams g) {
-  using P = Pass<N, T, E, KIND, SWZ>;
+  using P = Pass<N, T, E, KIND, SWZ, LAST>;
   constexpr int NT = P::NT;
   __shared__ float2 lds[P::LDS_ELEMS];
   float2 v[E];
@@ -630,7 +633,7 @@ __global__ void __launch_bounds__(N * T / E) k_fft_pass(float2* __restrict__ dat
 template <int N, int T, int E, int KIND, int ORDER, bool LAST = KIND == KIND_X, bool DEFER = false, bool SPLIT = false>
 __global__ void __launch_bounds__(N * T / E) __attribute__((amdgpu_waves_per_eu(1, 2)))
 k_fft_pipe(float2* __restrict__ data, uint32_t* __restrict__ out_bf16, const float2* __restrict__ tw, GenParams g) {
-  using P = Pass<N, T, E, KIND>;
+  using P = Pass<N, T, E, KIND, false, LAST>;
   constexpr int ntiles = N * (N / T);
   __shared__ float2 lds[P::LDS_ELEMS];
   // twiddles in LDS: a global twiddle load issued after the next tile's loads
