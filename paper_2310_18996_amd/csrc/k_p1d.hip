@@ -45,7 +45,7 @@ __global__ void __launch_bounds__(kPdNT, 3) k_p1d(P1dArgs a) {
     sfm[b] = c > 0.0 ? static_cast<float>(a.fsum[b] / c) : 1.0f;
   }
   const int nk = a.n_kbins, row = mode_row(nk), lg = bin_split(nk);
-  mode_table(smt, a.k_edges, nk, a.dv, tid, kPdNT);
+  for (int i = tid; i < kLenClasses * row; i += kPdNT) smt[i] = a.modes[i];
   __syncthreads();
   const LdsTw tw{stw};
   float2* buf = sbuf[wv];
@@ -121,18 +121,22 @@ __global__ void __launch_bounds__(kPdNT, 3) k_p1d(P1dArgs a) {
 
 __global__ void __launch_bounds__(256) k_p1d_sum(LineSumArgs a) { line_sum_block(a, blockIdx.x, 0); }
 
-__global__ void __launch_bounds__(256) k_p1d_final(LineSumArgs a, const double* __restrict__ k_edges, double dv,
-                                                   double* psum, int64_t* pcount) {
+// ONE: the sums of stage 1 as well (R = 1)
+template <bool ONE>
+__global__ void __launch_bounds__(256) k_p1d_final(LineSumArgs a, const unsigned short* __restrict__ modes, double* psum,
+                                                   int64_t* pcount) {
   __shared__ long long cls[kLenClasses + 1];
-  __shared__ unsigned short smt[kLenClasses * mode_row(kMaxKBins)];
   const int b = threadIdx.x, row = mode_row(a.nk);
-  line_counts(a, cls);
-  mode_table(smt, k_edges, a.nk, dv, threadIdx.x, 256);
+  if constexpr (ONE) {
+    line_sum_block(a, 0, 0);
+    __syncthreads();
+  }
+  line_counts(a, 0, cls);
   if (b < a.nk && psum) psum[b] = line_total(a, 0, b);
   __syncthreads();
   if (b >= a.nk || !pcount) return;
   long long n = 0;
-  for (int c = 1; c < kLenClasses; ++c) n += cls[c] * max(0, smt[c * row + b + 1] - smt[c * row + b]);
+  for (int c = 1; c < kLenClasses; ++c) n += cls[c] * max(0, modes[c * row + b + 1] - modes[c * row + b]);
   pcount[b] = n;
 }
 
@@ -153,9 +157,9 @@ hipError_t launch_p1d(const P1dArgs& p, double* psum, int64_t* pcount, hipStream
   l.rows = a.part_sum;
   l.part = reinterpret_cast<double*>(a.aux);
   l.hist = reinterpret_cast<long long*>(l.part + static_cast<size_t>(l.R) * (l.nk + 1));
-  LYA_TIMED("p1d_sum", st, hipLaunchKernelGGL(k_p1d_sum, dim3(l.R), dim3(256), 0, st, l));
-  LYA_TIMED("p1d_final", st,
-            hipLaunchKernelGGL(k_p1d_final, dim3(1), dim3(256), 0, st, l, a.k_edges, a.dv, psum, pcount));
+  if (l.R > 1) LYA_TIMED("p1d_sum", st, hipLaunchKernelGGL(k_p1d_sum, dim3(l.R), dim3(256), 0, st, l));
+  const auto fin = l.R > 1 ? k_p1d_final<false> : k_p1d_final<true>;
+  LYA_TIMED("p1d_final", st, hipLaunchKernelGGL(fin, dim3(1), dim3(256), 0, st, l, a.modes, psum, pcount));
   return hipGetLastError();
 }
 

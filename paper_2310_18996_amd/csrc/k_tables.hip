@@ -245,8 +245,8 @@ __device__ __forceinline__ double z_of_chi_group(double chi, double om, int l) {
 // a launch of 4-5 us of its own): the z(chi) table (ztab), the 2048 twiddles
 // (tw), the amplitudes of delta_S (ps_tab: in the line kernel a tabulated ratio took
 // an FP64 search of dependent loads for each mode of each line; FGPA and 1D power of
-// 35M stored pixels 630 -> 523 us), and the work queue and bin sums cleared (queue,
-// bsum, bcnt; ordinary stores, no memset node).  Null pointers are left out.  The table's
+// 35M stored pixels 630 -> 523 us), the first modes of the k bins (modes), and the work
+// queue and bin sums cleared (queue, bsum, bcnt; ordinary stores, no memset node).  Null pointers are left out.  The table's
 // blocks come first and in decreasing chi (the far nodes take the most steps).
 constexpr int kPrepNT = 256;
 constexpr int kPrepZBlocks = (kZTabN * 16 + kPrepNT - 1) / kPrepNT;
@@ -282,6 +282,11 @@ __global__ void __launch_bounds__(kPrepNT) k_prep(PrepArgs a) {
     a.ps_tab[i] = m > 0 ? ps_amplitude(a, m, ns, sc.x, sc.y) : 0.0f;
     return;
   }
+  b -= a.ps_tab ? kPrepPsBlocks : 0;
+  if (a.modes && b < kModeBlocks) {
+    mode_table(a.modes, a.k_edges, a.nk, a.dv, b, t, kPrepNT);
+    return;
+  }
   if (t < kPullCounters && a.queue) a.queue[t * kPullStride] = 0u;
   for (int i = t; i < kBinCopies * kMaxZBins && a.bsum; i += kPrepNT) {
     a.bsum[i] = 0ull;
@@ -291,7 +296,7 @@ __global__ void __launch_bounds__(kPrepNT) k_prep(PrepArgs a) {
 
 hipError_t launch_prep(const PrepArgs& a, hipStream_t st) {
   const int blocks = (a.ztab ? kPrepZBlocks : 0) + (a.tw ? kPrepTwBlocks : 0) +
-                     (a.ps_tab ? kPrepPsBlocks : 0) + (a.queue || a.bsum ? 1 : 0);
+                     (a.ps_tab ? kPrepPsBlocks : 0) + (a.modes ? kModeBlocks : 0) + (a.queue || a.bsum ? 1 : 0);
   if (blocks == 0) return hipSuccess;
   LYA_TIMED("prep", st, hipLaunchKernelGGL(k_prep, dim3(blocks), dim3(kPrepNT), 0, st, a));
   return hipGetLastError();

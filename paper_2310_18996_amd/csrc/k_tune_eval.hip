@@ -30,12 +30,9 @@ constexpr int kTeReg = 32;  // pixels per lane kept in registers (2048 per wave)
 
 // Each draw's table of first modes, and the queue cleared.
 __global__ void __launch_bounds__(256) k_te_prep(TuneEvalArgs a) {
-  __shared__ unsigned short smt[kLenClasses * mode_row(kMaxKBins)];
-  const int g = blockIdx.x, n = kLenClasses * mode_row(a.nk);
-  if (g == 0 && threadIdx.x < kPullCounters) a.queue[threadIdx.x * kPullStride] = 0u;
-  mode_table(smt, a.k_edges, a.nk, a.dv[g], threadIdx.x, 256);
-  __syncthreads();
-  for (int i = threadIdx.x; i < n; i += 256) a.modes[g * n + i] = smt[i];
+  const int part = blockIdx.x, g = blockIdx.y;
+  if (g == 0 && part == 0 && threadIdx.x < kPullCounters) a.queue[threadIdx.x * kPullStride] = 0u;
+  mode_table(a.modes + g * kLenClasses * mode_row(a.nk), a.k_edges, a.nk, a.dv[g], part, threadIdx.x, 256);
 }
 
 // DS: delta_S redrawn per draw (a separate instantiation, so that the plain
@@ -139,12 +136,18 @@ __global__ void __launch_bounds__(kTeNT, 3) k_tune_eval(TuneEvalArgs a) {
 __global__ void __launch_bounds__(256) k_te_sum(LineSumArgs a) { line_sum_block(a, blockIdx.x, blockIdx.y); }
 
 // Statistics per draw: Fbar, then P_b (NaN for an empty bin); FP64 rows and,
-// when rows32 is given, FP32 rows (emulator labels).
-__global__ void __launch_bounds__(128) k_te_stats(TuneEvalArgs a, LineSumArgs l, double* rows, float* rows32) {
+// when rows32 is given, FP32 rows (emulator labels).  ONE: the sums of stage 1 as
+// well (R = 1).
+template <bool ONE>
+__global__ void __launch_bounds__(ONE ? 256 : 128) k_te_stats(TuneEvalArgs a, LineSumArgs l, double* rows, float* rows32) {
   __shared__ long long cls[kLenClasses + 1];
   __shared__ double sf;
-  line_counts(l, cls);
   const int g = blockIdx.x, b = threadIdx.x, nk = a.nk, row = mode_row(nk);
+  if constexpr (ONE) {
+    line_sum_block(l, 0, g);
+    __syncthreads();
+  }
+  line_counts(l, g, cls);
   if (b == 127) sf = line_total(l, g, nk);
   __syncthreads();
   if (b > nk) return;
@@ -169,7 +172,7 @@ hipError_t launch_tune_eval(const TuneEvalArgs& p, double* rows, float* rows32, 
   if (p.G < 1 || p.G > kTuneEvalMaxG || p.nk < 1 || p.nk > kMaxKBins) return hipErrorInvalidValue;
   TuneEvalArgs a = p;
   a.modes = reinterpret_cast<int*>(a.aux);
-  LYA_TIMED("tune_eval_prep", st, hipLaunchKernelGGL(k_te_prep, dim3(a.G), dim3(256), 0, st, a));
+  LYA_TIMED("tune_eval_prep", st, hipLaunchKernelGGL(k_te_prep, dim3(kModeBlocks, a.G), dim3(256), 0, st, a));
   int64_t blocks = static_cast<int64_t>(device_cus()) * 3;
   // eight pulls per wave or more, so that the waves end together
   a.chunk = static_cast<int>(std::min<int64_t>(a.chunk, std::max<int64_t>(1, a.n_sk / (8 * blocks * kTeWaves))));
@@ -190,8 +193,14 @@ hipError_t launch_tune_eval(const TuneEvalArgs& p, double* rows, float* rows32, 
   l.fs = a.fs;
   l.part = reinterpret_cast<double*>(a.aux + sizeof(int) * kTuneEvalMaxG * kLenClasses * ((mode_row(a.nk) + 1) & ~1));
   l.hist = reinterpret_cast<long long*>(l.part + static_cast<size_t>(a.G) * l.R * (l.nk + 1));
-  LYA_TIMED("tune_eval_sum", st, hipLaunchKernelGGL(k_te_sum, dim3(l.R, a.G), dim3(256), 0, st, l));
-  LYA_TIMED("tune_eval_stats", st, hipLaunchKernelGGL(k_te_stats, dim3(a.G), dim3(128), 0, st, a, l, rows, rows32));
+  if (l.R > 1) {
+    LYA_TIMED("tune_eval_sum", st, hipLaunchKernelGGL(k_te_sum, dim3(l.R, a.G), dim3(256), 0, st, l));
+    LYA_TIMED("tune_eval_stats", st,
+              hipLaunchKernelGGL(k_te_stats<false>, dim3(a.G), dim3(128), 0, st, a, l, rows, rows32));
+  } else {
+    LYA_TIMED("tune_eval_stats", st,
+              hipLaunchKernelGGL(k_te_stats<true>, dim3(a.G), dim3(256), 0, st, a, l, rows, rows32));
+  }
   return hipGetLastError();
 }
 

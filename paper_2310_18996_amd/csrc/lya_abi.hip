@@ -324,7 +324,7 @@ int run_skewers(lya::SkewerArgs& a, const lya_cosmo* cosmo, const lya_zbins* zb,
 }
 
 struct PdCarve {
-  size_t sum, aux, tw, queue, total;
+  size_t sum, aux, tw, modes, queue, total;
 };
 
 PdCarve carve_p1d(int64_t n_sk, int nk) {
@@ -333,6 +333,7 @@ PdCarve carve_p1d(int64_t n_sk, int nk) {
   c.sum = o;   o += align256(sizeof(double) * static_cast<size_t>(n_sk) * nk);
   c.aux = o;   o += align256(std::max(sizeof(int) * static_cast<size_t>(n_sk) * nk, lya::line_sum_bytes(n_sk, nk, 1)));
   c.tw = o;    o += align256(sizeof(float2) * lya::kTw2048);
+  c.modes = o; o += align256(sizeof(unsigned short) * lya::kLenClasses * lya::mode_row(nk));
   c.queue = o; o += lya::kPullBytes;
   c.total = o;
   return c;
@@ -437,14 +438,19 @@ int lya_p1d(const lya_skewers* sk, const lya_cosmo* cosmo, const float* flux, co
   a.part_sum = reinterpret_cast<double*>(w + c.sum);
   a.aux = w + c.aux;
   a.tw2048 = reinterpret_cast<float2*>(w + c.tw);
+  a.modes = reinterpret_cast<unsigned short*>(w + c.modes);
   a.queue = reinterpret_cast<unsigned int*>(w + c.queue);
   a.chunk = 4;
   hipStream_t st = static_cast<hipStream_t>(stream);
   lya::PrepArgs pa{};
   pa.tw = const_cast<float2*>(a.tw2048);
   pa.queue = a.queue;
+  pa.modes = reinterpret_cast<unsigned short*>(w + c.modes);
+  pa.nk = a.n_kbins;
+  pa.k_edges = a.k_edges;
+  pa.dv = a.dv;
   hipError_t e = lya::launch_prep(pa, st);
-  if (e != hipSuccess) return hip_fail(e, "twiddles");
+  if (e != hipSuccess) return hip_fail(e, "1D power tables");
   e = lya::launch_p1d(a, psum, pcount, st);
   if (e != hipSuccess) return hip_fail(e, "1D power kernel");
   return LYA_OK;

@@ -98,6 +98,11 @@ struct PrepArgs {
   int ps_nb;                  // as in SkewerArgs
   const double* ps_edges_k;
   const float* ps_ratio;
+  // first modes of nk bins (mode_table)
+  unsigned short* modes;
+  int nk;
+  const double* k_edges;
+  double dv;
 };
 constexpr int kPsTab = 2048 + 1024 + 2;
 hipError_t launch_prep(const PrepArgs& a, hipStream_t st);
@@ -211,6 +216,7 @@ struct P1dArgs {
   double* part_sum;          // workspace [n_sk][n_kbins]
   char* aux;                 // workspace: line_sum_bytes(n_sk, n_kbins, 1)
   const float2* tw2048;
+  const unsigned short* modes;   // first modes of the bins (PrepArgs), in the workspace
   unsigned int* queue;
   int chunk;          // lines per pull
   int64_t chunks;     // pulls (set at the launch)

@@ -5,7 +5,9 @@
 // integers); stage 2 adds the R partial sums in order, and gets each bin's modes
 // from the class counts and the table of first modes.  (A block per bin over
 // [bin][line] rows took 58 us for 50,000 lines and 32 bins, and each line's 32
-// sums went to as many cache lines.)
+// sums went to as many cache lines.)  Below 256 lines R is 1, and the two stages are
+// one launch (the 1D power of one line and 1, 22, 64 bins: 17.3, 18.3, 20.8 us with two
+// and the table of first modes in both kernels, 15.8, 16.3, 17.0 us with one).
 #pragma once
 
 #include "lya_internal.h"
@@ -20,10 +22,11 @@ struct LineSumArgs {
   const double* rows;     // [draw][n][nk]
   const double* fs;       // [draw][n], or null
   double* part;           // [draw][R][nk + 1]: bins, then fs
-  long long* hist;        // [R][kLenClasses + 1]: lines per class, then pixels
+  long long* hist;        // [R, or draws if R = 1][kLenClasses + 1]: lines per class, then pixels
 };
 
-// stage 1: block (r, draw) of 256 threads
+// stage 1: block (r, draw) of 256 threads; the counts by the first draw's blocks,
+// or each draw's own where R = 1
 __device__ __forceinline__ void line_sum_block(const LineSumArgs& a, int r, int g) {
   __shared__ double ss[256];
   __shared__ int sh[kLenClasses];
@@ -57,7 +60,7 @@ __device__ __forceinline__ void line_sum_block(const LineSumArgs& a, int r, int 
     }
     if (t == 0) out[a.nk] = ss[0];
   }
-  if (g == 0) {
+  if (g == 0 || a.R == 1) {
     unsigned long long pix = 0ull;
     for (int64_t q = q0 + t; q < q1; q += 256) {
       const int np = a.npix[q];
@@ -66,7 +69,7 @@ __device__ __forceinline__ void line_sum_block(const LineSumArgs& a, int r, int 
     }
     atomicAdd(&spix, pix);
     __syncthreads();
-    long long* h = a.hist + static_cast<size_t>(r) * (kLenClasses + 1);
+    long long* h = a.hist + static_cast<size_t>(r + g) * (kLenClasses + 1);   // (one of them is 0)
     if (t < kLenClasses) h[t] = sh[t];
     if (t == 0) h[kLenClasses] = static_cast<long long>(spix);
   }
@@ -87,11 +90,11 @@ __device__ __forceinline__ T sum_parts(int R, X x) {
 }
 // stage 2 (a block of at least 64 threads): class counts and pixels into cls
 // [kLenClasses + 1] (shared), valid after the caller's barrier
-__device__ __forceinline__ void line_counts(const LineSumArgs& a, long long* cls) {
+__device__ __forceinline__ void line_counts(const LineSumArgs& a, int g, long long* cls) {
   const int t = threadIdx.x;
+  const long long* h = a.hist + (a.R == 1 ? static_cast<size_t>(g) * (kLenClasses + 1) : 0);
   if (t <= kLenClasses)
-    cls[t] = sum_parts<long long>(
-        a.R, [&](int r) { return a.hist[static_cast<size_t>(r) * (kLenClasses + 1) + t]; });
+    cls[t] = sum_parts<long long>(a.R, [&](int r) { return h[static_cast<size_t>(r) * (kLenClasses + 1) + t]; });
 }
 __device__ __forceinline__ double line_total(const LineSumArgs& a, int g, int b) {
   const double* p = a.part + static_cast<size_t>(g) * a.R * (a.nk + 1) + b;
@@ -101,7 +104,8 @@ __device__ __forceinline__ double line_total(const LineSumArgs& a, int g, int b)
 // blocks of stage 1, and the bytes of part and hist for G draws
 inline int line_sum_blocks(int64_t n) { return n < 256 ? 1 : n >= 128 * 128 ? 128 : static_cast<int>(n / 128); }
 inline size_t line_sum_bytes(int64_t n, int nk, int G) {
-  return sizeof(double) * line_sum_blocks(n) * (static_cast<size_t>(G) * (nk + 1) + kLenClasses + 1);
+  const size_t R = line_sum_blocks(n), counts = R == 1 ? G : R;
+  return sizeof(double) * (R * G * (nk + 1) + counts * (kLenClasses + 1));
 }
 
 }  // namespace lya

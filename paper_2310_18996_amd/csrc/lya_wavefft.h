@@ -89,16 +89,23 @@ __device__ __forceinline__ int len_class(int np) {
   return np >= 2 ? 31 - __clz(np < 2 * kHalfMax ? np : 2 * kHalfMax) : 0;
 }
 __host__ __device__ constexpr int mode_row(int nk) { return nk + 3; }
-// By all threads of a block, into LDS; complete after the caller's next barrier.
-__device__ __forceinline__ void mode_table(unsigned short* tab, const double* __restrict__ k_edges, int nk, double dv,
-                                           int tid, int nt) {
-  const int row = mode_row(nk);
-  for (int i = tid; i < kLenClasses * (nk + 1); i += nt) {
-    const int c = i / (nk + 1), b = i % (nk + 1);
+// Part b of kModeBlocks, by a block of nt threads, into out; once per call, in the
+// launch before the lines' (its FP64 divisions in every block of those were 3 us of
+// each, and as one part 2 us more of that launch at 64 bins).
+constexpr int kModeBlocks = 4;
+template <typename T>
+__device__ __forceinline__ void mode_table(T* __restrict__ out, const double* __restrict__ k_edges, int nk, double dv,
+                                           int part, int tid, int nt) {
+  constexpr int nc = kLenClasses / kModeBlocks;
+  static_assert(kLenClasses % kModeBlocks == 0, "whole rows per part");
+  __shared__ unsigned short tab[kLenClasses * mode_row(kMaxKBins)];
+  const int row = mode_row(nk), c0 = part * nc;
+  for (int i = tid; i < nc * (nk + 1); i += nt) {
+    const int c = c0 + i / (nk + 1), b = i % (nk + 1);
     tab[c * row + b] = static_cast<unsigned short>(c > 0 ? first_mode(k_edges[b], 1 << c, dv) : 1);
   }
   __syncthreads();
-  for (int c = tid; c < kLenClasses; c += nt) {
+  for (int c = c0 + tid; c < c0 + nc; c += nt) {
     unsigned short lo = tab[c * row], hi = lo;
     for (int b = 1; b <= nk; ++b) {
       const unsigned short m = tab[c * row + b];
@@ -108,6 +115,8 @@ __device__ __forceinline__ void mode_table(unsigned short* tab, const double* __
     tab[c * row + nk + 1] = lo;
     tab[c * row + nk + 2] = hi;
   }
+  __syncthreads();
+  for (int i = c0 * row + tid; i < (c0 + nc) * row; i += nt) out[i] = tab[i];
 }
 
 // |X_m|^2 scale of a transformed line for the modes lo <= m < hi (1 <= m <= M),
