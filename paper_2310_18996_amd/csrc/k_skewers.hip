@@ -656,9 +656,9 @@ struct LineNoise {
   int ps_fixed_amp;
 };
 
-// (the Gaussian mode's LDS leaves two waves per SIMD)
+// (the Gaussian mode's LDS leaves two waves per SIMD; four FP32 boxes need 145 registers)
 template <int U, int MODE, bool B16>
-__global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : MODE == kSkWide ? 3 : 1) k_skewers(SkewerArgs a) {
+__global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : MODE == kSkWide && !B16 ? 3 : U == 1 ? 4 : 1) k_skewers(SkewerArgs a) {
   __shared__ float2 sbuf[kSkWaves][kHalfBuf];
   __shared__ __align__(8) float sgauss[MODE == kSkGauss ? kSkWaves : 1][MODE == kSkGauss ? kGaussWords : 1];
   constexpr bool kCellWalk = U == 1 && MODE != kSkGauss;
@@ -945,20 +945,28 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : MOD
               const uint32_t y0 = iy * static_cast<uint32_t>(N), y1 = jy * static_cast<uint32_t>(N);
               const size_t ci[8] = {x0 + (y0 + iz), x0 + (y0 + jz), x0 + (y1 + iz), x0 + (y1 + jz),
                                     x1 + (y0 + iz), x1 + (y0 + jz), x1 + (y1 + iz), x1 + (y1 + jz)};
-              // the gathers of G corners, then eta_par = u_p u_q eta^pq per corner: all
-              // 32 at once, but for U = 1 (lines whose steps are too long for the
-              // cell walk) what the walk's registers leave
-              constexpr int G = U == 1 ? 2 : 8;
+              // the gathers of G corners box by box, then eta_par = u_p u_q eta^pq per
+              // corner.  Lines come here whose steps are too long for the cell walk, and
+              // most of a corner's cache line is then a neighbouring corner's: with the
+              // four boxes in turn at each corner their 64 lanes' lines left the L1 in
+              // between (100M FP32 pixels in directions all over, 0.3 and 1 cells a step:
+              // 12.0 and 31.5 ms by two corners, 11.4 and 30.7 ms by eight; box by box
+              // 8.6 and 24.8).  BF16 takes four corners, what four waves per SIMD leave
+              // (8.8 and 26.9 ms; all eight on three waves 8.1 and 25.5, but then the
+              // cell walk is slower: 416 against 404 us for 30M pixels at 0.09 cells a
+              // step; FP32 on three waves 563 against 571 us, its walk spilled on four)
+              constexpr int G = B16 ? 4 : 8;
 #pragma unroll
               for (int h = 0; h < 8; h += G) {
                 float2 w0[G], w1[G], w2[G], w3[G];
 #pragma unroll
-                for (int k = 0; k < G; ++k) {
-                  w0[k] = ld_field<B16>(a, ci[h + k]);
-                  w1[k] = ld_wide<B16>(a, 0, ci[h + k]);
-                  w2[k] = ld_wide<B16>(a, 1, ci[h + k]);
-                  w3[k] = ld_wide<B16>(a, 2, ci[h + k]);
-                }
+                for (int k = 0; k < G; ++k) w0[k] = ld_field<B16>(a, ci[h + k]);
+#pragma unroll
+                for (int k = 0; k < G; ++k) w1[k] = ld_wide<B16>(a, 0, ci[h + k]);
+#pragma unroll
+                for (int k = 0; k < G; ++k) w2[k] = ld_wide<B16>(a, 1, ci[h + k]);
+#pragma unroll
+                for (int k = 0; k < G; ++k) w3[k] = ld_wide<B16>(a, 2, ci[h + k]);
 #pragma unroll
                 for (int k = 0; k < G; ++k) {
                   c[u][h + k] = make_float2(w0[k].x, ww.eta(w0[k], w1[k], w2[k], w3[k]));
@@ -1093,11 +1101,8 @@ void launch_skewer_kernel(const SkewerArgs& a, int u, dim3 grid, hipStream_t st)
     // 343 gathers per pixel: one pixel per lane at a time
     LYA_TIMED("skewers_gauss", st, hipLaunchKernelGGL((k_skewers<1, kSkGauss, B16>), grid, dim3(kSkNT), 0, st, a));
   } else if (a.is_wide) {
-    // four boxes per pixel: at most two pixels per lane in flight
-    if (u == 1)
-      LYA_TIMED("skewers_wide", st, hipLaunchKernelGGL((k_skewers<1, kSkWide, B16>), grid, dim3(kSkNT), 0, st, a));
-    else
-      LYA_TIMED("skewers_wide", st, hipLaunchKernelGGL((k_skewers<2, kSkWide, B16>), grid, dim3(kSkNT), 0, st, a));
+    // four boxes per pixel: one pixel per lane at a time, whatever the unroll
+    LYA_TIMED("skewers_wide", st, hipLaunchKernelGGL((k_skewers<1, kSkWide, B16>), grid, dim3(kSkNT), 0, st, a));
   } else if (u == 1) {
     LYA_TIMED(a.in_dens ? "apply_fgpa" : "skewers", st,
               hipLaunchKernelGGL((k_skewers<1, kSkTri, B16>), grid, dim3(kSkNT), 0, st, a));
@@ -1120,12 +1125,13 @@ hipError_t launch_skewers(SkewerArgs a, hipStream_t st) {
   a.chunks = (a.n_sk + a.chunk - 1) / a.chunk;
   if (blocks * kSkWaves > a.chunks) blocks = (a.chunks + kSkWaves - 1) / kSkWaves;
   if (blocks < 1) blocks = 1;
-  // with at most a skewer per wave the pass is one skewer's latency: the gathers of
-  // four steps of 64 pixels go out together instead of step by step (18.6 ->
-  // 17.4 us for 500 skewers of 256 pixels; every unroll gives the same bits).  The
-  // wide-angle pass walks cells there as well: 8 loads a step in flight against 64 of
-  // two steps at three waves per SIMD (500 lines in 512^3, the call: 59 -> 49 us, FP32
-  // boxes 64 -> 55 us; 3000 lines 70 -> 61 and 88 -> 78 us)
+  // with at most a skewer per wave the trilinear pass is one skewer's latency: the
+  // gathers of four steps of 64 pixels go out together, against one step's on the
+  // cell walk (calls without FGPA in a 512^3 box, 250 and 1500 pixels: one line 9.8
+  // and 21.8 us, walk 12.0 and 27.2; 500 lines 11.3 and 26.7, walk 13.0 and 30.6; with
+  // FGPA 26.1 and 47.2, walk 26.6 and 45.3).  From about half the waves up the
+  // walk would gain again (4000 lines 19.4 and 59.0 us, walk 17.4 and 51.1; 20-2000
+  // pixels 42.4, walk 50.0).  Every unroll gives the same bits.
   const bool few = a.n_sk <= blocks * kSkWaves;
   const int u = few && !a.is_wide ? 4 : a.unroll == 1 || a.unroll == 4 ? a.unroll : 2;
   const dim3 grid(static_cast<unsigned>(blocks));
