@@ -662,11 +662,17 @@ int lya_quasar_skewers(const lya_box* box, const lya_qso_los_spec* spec, const l
  *                     the next tile's loads issued in parts, one before each
  *                     FFT stage.  All variants give bit-identical boxes.
  *                     Boxes below 1024 have variants 0 and 1 only.
- *                     Defaults: y 8, x 15 from 1024 up, y 0, x 1 below.
- *   sk_chunk          skewers taken per pull from the skewer work queue (default 4);
+ *                     Defaults: y 14 at 1024 and 8 at 2048, x 15 at both; y 0,
+ *                     x 1 below.
+ *   sk_chunk          skewers taken per pull from the skewer work queue (default 4),
+ *                     at most: a call takes fewer where that would leave a wave
+ *                     less than eight pulls;
  *   sk_blocks_per_cu  persistent skewer blocks per CU, 1..4 (default 4);
  *   sk_unroll         pixels per lane whose gathers are issued together, 1, 2 or 4
- *                     (default 1).
+ *                     (default 1, which also reads lines of short steps, up to about
+ *                     a fifth of a cell summed over the axes, cell by cell).  For
+ *                     lya_draw_skewers only, and there 4 whatever it says in calls
+ *                     with at most a skewer per wave; results are the same.
  * The table is process-wide and applies to every later call for that n. */
 #define LYA_FFT_VARIANTS 16
 typedef struct {
