@@ -694,7 +694,9 @@ int lya_autotune_fft(const lya_box* box, void* field, void* work, size_t work_by
 
 /* Times lya_draw_skewers (same arguments; outputs overwritten) for skewer
  * chunks {1, 2, 4, 8, 16, 32, 64} x blocks per CU {1, 2, 3, 4} x unroll
- * {1, 2, 4}, `reps` runs each; stores the fastest in the table for box->n.
+ * {1, 2, 4}, `reps` runs each; stores the fastest in the table for box->n, if it
+ * launches something else than the current shape does for this many skewers and
+ * is at least 2% faster.
  * ms (may be NULL) receives 7 x 4 x 3 mean milliseconds, [chunk][blocks][unroll].
  * Synchronous. */
 int lya_autotune_skewers(const lya_box* box, const void* field, const lya_skewers* sk, const lya_ps1d* ps,

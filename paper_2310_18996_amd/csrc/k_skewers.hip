@@ -1115,16 +1115,17 @@ void launch_skewer_kernel(const SkewerArgs& a, int u, dim3 grid, hipStream_t st)
   }
 }
 
-hipError_t launch_skewers(SkewerArgs a, hipStream_t st) {
-  int64_t blocks = static_cast<int64_t>(device_cus()) * (a.blocks_per_cu > 0 ? a.blocks_per_cu : 4);
+SkLaunch sk_launch(int64_t n_sk, int chunk, int blocks_per_cu, int unroll) {
+  SkLaunch l{};
+  l.blocks = static_cast<int64_t>(device_cus()) * (blocks_per_cu > 0 ? blocks_per_cu : 4);
   // no more skewers per pull than leave every wave of the grid eight pulls: longer
   // ones leave it uneven at the end (35M stored pixels of 50,000 skewers 568 us in
   // pulls of 4, 482 us one by one), and 500 skewers of 256 pixels in pulls of 4 ran
   // on 125 waves, four in a row each (39.5 us; one per wave 18.6 us)
-  a.chunk = static_cast<int>(std::min<int64_t>(a.chunk, std::max<int64_t>(1, a.n_sk / (8 * blocks * kSkWaves))));
-  a.chunks = (a.n_sk + a.chunk - 1) / a.chunk;
-  if (blocks * kSkWaves > a.chunks) blocks = (a.chunks + kSkWaves - 1) / kSkWaves;
-  if (blocks < 1) blocks = 1;
+  l.chunk = static_cast<int>(std::min<int64_t>(chunk, std::max<int64_t>(1, n_sk / (8 * l.blocks * kSkWaves))));
+  l.chunks = (n_sk + l.chunk - 1) / l.chunk;
+  if (l.blocks * kSkWaves > l.chunks) l.blocks = (l.chunks + kSkWaves - 1) / kSkWaves;
+  if (l.blocks < 1) l.blocks = 1;
   // with at most a skewer per wave the trilinear pass is one skewer's latency: the
   // gathers of four steps of 64 pixels go out together, against one step's on the
   // cell walk (calls without FGPA in a 512^3 box, 250 and 1500 pixels: one line 9.8
@@ -1132,13 +1133,20 @@ hipError_t launch_skewers(SkewerArgs a, hipStream_t st) {
   // FGPA 26.1 and 47.2, walk 26.6 and 45.3).  From about half the waves up the
   // walk would gain again (4000 lines 19.4 and 59.0 us, walk 17.4 and 51.1; 20-2000
   // pixels 42.4, walk 50.0).  Every unroll gives the same bits.
-  const bool few = a.n_sk <= blocks * kSkWaves;
-  const int u = few && !a.is_wide ? 4 : a.unroll == 1 || a.unroll == 4 ? a.unroll : 2;
-  const dim3 grid(static_cast<unsigned>(blocks));
+  const bool few = n_sk <= l.blocks * kSkWaves;
+  l.unroll = few ? 4 : unroll == 1 || unroll == 4 ? unroll : 2;
+  return l;
+}
+
+hipError_t launch_skewers(SkewerArgs a, hipStream_t st) {
+  const SkLaunch l = sk_launch(a.n_sk, a.chunk, a.blocks_per_cu, a.unroll);
+  a.chunk = l.chunk;
+  a.chunks = l.chunks;
+  const dim3 grid(static_cast<unsigned>(l.blocks));
   if (a.field_bf16)
-    launch_skewer_kernel<true>(a, u, grid, st);
+    launch_skewer_kernel<true>(a, l.unroll, grid, st);
   else
-    launch_skewer_kernel<false>(a, u, grid, st);
+    launch_skewer_kernel<false>(a, l.unroll, grid, st);
   if (a.n_bins > 0 && a.do_flux)
     LYA_TIMED("skewer_finalize", st,
               hipLaunchKernelGGL(k_skewer_finalize, dim3(1), dim3(256), 0, st, a.n_bins, a.bin_sum, a.bin_cnt,

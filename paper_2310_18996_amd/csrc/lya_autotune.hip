@@ -179,32 +179,38 @@ int lya_autotune_skewers(const lya_box* box, const void* field, const lya_skewer
   if (reps < 1) return afail(LYA_EINVAL, "reps must be >= 1");
   const int n = box->n;
   const int c0 = lya::sk_chunk(n), b0 = lya::sk_blocks_per_cu(n), u0 = lya::sk_unroll(n);
-  double bt = 1e300;
+  const auto time_shape = [&](int c, int b, int u, double* t) {
+    lya::set_sk_shape(n, c, b, u);
+    int rc = LYA_OK;
+    hipError_t e = time_ms(
+        [&] {
+          rc = lya_draw_skewers(box, field, sk, ps, seed, cosmo, fgpa, dens, eta, flux, zb, work, work_bytes, stream);
+          return rc == LYA_OK ? hipSuccess : hipErrorUnknown;
+        },
+        reps, static_cast<hipStream_t>(stream), t);
+    lya::set_sk_shape(n, c0, b0, u0);
+    if (rc != LYA_OK) {
+      snprintf(g_aerr, sizeof(g_aerr), "lya_draw_skewers: %s", lya_last_error());
+      return rc;
+    }
+    return e == hipSuccess ? static_cast<int>(LYA_OK) : ahip(e, "timing a skewer launch shape");
+  };
+  // the current shape stays unless another is at least 2% faster and launches
+  // something else for this many skewers (few of them resolve most shapes to one)
+  double bt = 0.0;
+  int rc = time_shape(c0, b0, u0, &bt);
+  if (rc != LYA_OK) return rc;
+  bt *= 0.98;
+  const lya::SkLaunch l0 = lya::sk_launch(sk->n_sk, c0, b0, u0);
   int bc = c0, bb = b0, bu = u0;
   for (int i = 0; i < kNChunks; ++i) {
     for (int j = 0; j < kNBpc; ++j) {
       for (int k = 0; k < kNUnroll; ++k) {
-        lya::set_sk_shape(n, kChunks[i], kBpc[j], kUnroll[k]);
-        int rc = LYA_OK;
         double t = 0.0;
-        hipError_t e = time_ms(
-            [&] {
-              rc = lya_draw_skewers(box, field, sk, ps, seed, cosmo, fgpa, dens, eta, flux, zb, work, work_bytes,
-                                    stream);
-              return rc == LYA_OK ? hipSuccess : hipErrorUnknown;
-            },
-            reps, static_cast<hipStream_t>(stream), &t);
-        if (rc != LYA_OK) {
-          lya::set_sk_shape(n, c0, b0, u0);
-          snprintf(g_aerr, sizeof(g_aerr), "lya_draw_skewers: %s", lya_last_error());
-          return rc;
-        }
-        if (e != hipSuccess) {
-          lya::set_sk_shape(n, c0, b0, u0);
-          return ahip(e, "timing a skewer launch shape");
-        }
+        if ((rc = time_shape(kChunks[i], kBpc[j], kUnroll[k], &t)) != LYA_OK) return rc;
         if (ms) ms[(i * kNBpc + j) * kNUnroll + k] = t;
-        if (t < bt) {
+        const lya::SkLaunch l = lya::sk_launch(sk->n_sk, kChunks[i], kBpc[j], kUnroll[k]);
+        if (t < bt && (l.chunk != l0.chunk || l.blocks != l0.blocks || l.unroll != l0.unroll)) {
           bt = t;
           bc = kChunks[i];
           bb = kBpc[j];

@@ -197,6 +197,13 @@ struct SkewerArgs {
 
 hipError_t launch_skewers(SkewerArgs a, hipStream_t st);
 
+// What a call with n_sk lines makes of a launch shape (unroll: of the trilinear mode).
+struct SkLaunch {
+  int chunk, unroll;
+  int64_t chunks, blocks;
+};
+SkLaunch sk_launch(int64_t n_sk, int chunk, int blocks_per_cu, int unroll);
+
 // 1D flux power spectrum.
 constexpr int kMaxKBins = 64;
 struct P1dArgs {
