@@ -52,7 +52,7 @@ int hip_fail(hipError_t e, const char* where) {
 
 bool pow2_in_range(int n) { return n >= 32 && n <= 2048 && (n & (n - 1)) == 0; }
 
-size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
+constexpr size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
 struct BoxCarve {
   size_t partial, tw, table, table_b, zorder, staging, second, total;
@@ -80,7 +80,7 @@ struct SkCarve {
   size_t ztab, tw, queue, bsum, bcnt, ps, total;
 };
 
-SkCarve carve_sk() {
+constexpr SkCarve carve_sk() {
   SkCarve c{};
   size_t o = 0;
   c.ztab = o;  o += align256(sizeof(float) * lya::kZTabN);
@@ -92,6 +92,7 @@ SkCarve carve_sk() {
   c.total = o;
   return c;
 }
+static_assert(carve_sk().total <= kStaticScratchBytes, "lya_draw_skewers_static's workspace in its array");
 
 // Workspace of lya_draw_skewers_static: the file-scope device array
 // `scratch` (below), one copy in every GPU the library runs on, held until the
@@ -331,6 +332,7 @@ PdCarve carve_p1d(int64_t n_sk, int nk) {
   PdCarve c{};
   size_t o = 0;
   c.sum = o;   o += align256(sizeof(double) * static_cast<size_t>(n_sk) * nk);
+  // (at least the 4 bytes per line and bin that the size call has always asked for here)
   c.aux = o;   o += align256(std::max(sizeof(int) * static_cast<size_t>(n_sk) * nk, lya::line_sum_bytes(n_sk, nk, 1)));
   c.tw = o;    o += align256(sizeof(float2) * lya::kTw2048);
   c.modes = o; o += align256(sizeof(unsigned short) * lya::kLenClasses * lya::mode_row(nk));
@@ -569,9 +571,6 @@ int lya_draw_skewers_static(const lya_box* box, const void* field, const lya_ske
                             uint64_t seed, const lya_cosmo* cosmo, const lya_fgpa* fgpa, float* dens, float* eta,
                             float* flux, const lya_zbins* zb, void* stream) {
   g_err[0] = 0;
-  const size_t need = carve_sk().total;
-  if (need > kStaticScratchBytes)
-    return fail(LYA_EWORKSPACE, "the skewer workspace exceeds the static scratch array%s");
   if (zb && zb->n_bins > lya::kMaxZBins) return fail(LYA_EINVAL, "n_bins must be in [0, 64]%s");
   void* work = nullptr;
   const int rc = scratch_address(&work);

@@ -7,7 +7,6 @@
 // mode runs the same search on the MLP's predictions, checks the optimum on the
 // GPU and corrects the prediction by the measured defect before searching
 // again (a few GPU evaluations per redshift instead of one per search step).
-#include <algorithm>
 #include <math.h>
 #include <stdio.h>
 #include <string.h>
@@ -38,7 +37,7 @@ TuneCarve carve_tune(int64_t n_sk, int nk) {
   c.queue = o;  o += kPullBytes;
   c.fs = o;     o += al256(sizeof(double) * G * S);
   c.ps = o;     o += al256(sizeof(double) * G * nk * S);
-  c.aux = o;    o += al256(std::max(sizeof(int) * G * nk * S, tune_eval_aux_bytes(n_sk, nk)));
+  c.aux = o;    o += al256(tune_eval_aux_bytes(n_sk, nk));
   c.rows = o;   o += al256(sizeof(double) * G * (nk + 1));
   c.emu = o;    o += al256(emulator_eval_bytes());
   c.total = o;
