@@ -439,14 +439,21 @@ __device__ __forceinline__ bool qso_selected(const QsoDrawArgs& a, float r2xy, i
   return u < fminf(nb * a.dx3 * acc, 1.0f);
 }
 
-// 16 bytes per lane from memory to LDS, lane after lane from dst (the same in all lanes).
-template <bool NT>
-__device__ __forceinline__ void to_lds(const void* src, const void* dst) {
-  __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) const void*)src,
-                                   (__attribute__((address_space(3))) void*)dst, 16, 0, NT ? 2 : 0);
+// Two cells (16 bytes) per lane from memory to LDS, lane after lane from dst (the same
+// in all lanes).  DMA: straight there, for boxes that start 16-byte aligned (and
+// so do their rows and planes); other boxes cell by cell through registers.
+template <bool NT, bool DMA>
+__device__ __forceinline__ void to_lds(const float2* src, float4* dst, int lane) {
+  if constexpr (DMA) {
+    __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) const void*)src,
+                                     (__attribute__((address_space(3))) void*)dst, 16, 0, NT ? 2 : 0);
+  } else {
+    const float2 a = src[0], b = src[1];
+    dst[lane] = make_float4(a.x, a.y, b.x, b.y);
+  }
 }
 
-template <int NB, int VPT, bool NT>
+template <int NB, int VPT, bool NT, bool DMA>
 __global__ void __launch_bounds__(kQsoBlock) k_qso_draw(QsoDrawArgs a) {
   static_assert(VPT % 4 == 0 && 64 * VPT + kQsoFlush <= kQsoList && 64 * VPT * kQsoMaxTiles <= 65536, "list entries");
   __shared__ float snz[kQsoMaxNbar], snb[kQsoMaxNbar];
@@ -479,8 +486,8 @@ __global__ void __launch_bounds__(kQsoBlock) k_qso_draw(QsoDrawArgs a) {
   // 4 l + (h ^ (l / 2 mod 4)).  A tile lies in one x plane (n^2 is a multiple of it).
   static_assert(VPT == 8, "four pieces per thread");
   const int swz = (lane >> 1) & 3;
-  const float4* sa = sbox[threadIdx.x >> 6][0];
-  const float4* sb = sbox[threadIdx.x >> 6][NB == 3 ? 1 : 0];
+  float4* sa = sbox[threadIdx.x >> 6][0];
+  float4* sb = sbox[threadIdx.x >> 6][NB == 3 ? 1 : 0];
   const int mine = 8 * (lane >> 2) + 2 * ((lane & 3) ^ ((lane >> 3) & 3));
   const auto fetch = [&](int tile) {
     const uint64_t vt = w0 + static_cast<uint64_t>(tile) * (64 * VPT);
@@ -488,8 +495,8 @@ __global__ void __launch_bounds__(kQsoBlock) k_qso_draw(QsoDrawArgs a) {
                       static_cast<size_t>(vt >> (2 * a.log2n)) * (a.pitch - static_cast<size_t>(a.n) * a.n) + mine;
 #pragma unroll
     for (int i = 0; i < VPT / 2; ++i) {
-      to_lds<NT>(a.box_a + et + 128 * i, sa + 64 * i);
-      if (NB == 3) to_lds<NT>(a.box_b + et + 128 * i, sb + 64 * i);
+      to_lds<NT, DMA>(a.box_a + et + 128 * i, sa + 64 * i, lane);
+      if (NB == 3) to_lds<NT, DMA>(a.box_b + et + 128 * i, sb + 64 * i, lane);
     }
   };
   fetch(0);
@@ -608,8 +615,14 @@ hipError_t launch_qso_draw(const QsoCoef& c, const QsoDrawArgs& p, const float* 
   while (a.tiles < kQsoMaxTiles && all / (2 * a.tiles) >= waves) a.tiles *= 2;
   const uint64_t blocks = all / a.tiles / (kQsoBlock / 64);
   const bool nt = box_streams(a.n);
-  const auto kernel = a.nb == 3 ? (nt ? k_qso_draw<3, kQsoVpt, true> : k_qso_draw<3, kQsoVpt, false>)
-                                : (nt ? k_qso_draw<1, kQsoVpt, true> : k_qso_draw<1, kQsoVpt, false>);
+  const bool dma = (reinterpret_cast<uintptr_t>(a.box_a) | reinterpret_cast<uintptr_t>(a.box_b)) % 16 == 0;
+  const auto kernel =
+      a.nb == 3 ? (!dma ? k_qso_draw<3, kQsoVpt, false, false>
+                   : nt ? k_qso_draw<3, kQsoVpt, true, true>
+                        : k_qso_draw<3, kQsoVpt, false, true>)
+                : (!dma ? k_qso_draw<1, kQsoVpt, false, false>
+                   : nt ? k_qso_draw<1, kQsoVpt, true, true>
+                        : k_qso_draw<1, kQsoVpt, false, true>);
   LYA_TIMED("qso_draw", st,
             hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kQsoBlock), 0, st, a));
   return hipGetLastError();
