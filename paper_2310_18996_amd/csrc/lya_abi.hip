@@ -163,6 +163,19 @@ LnCarve carve_lognormal(int64_t m, int32_t n_r) {
 
 double bias_qso(double z) { return 3.7 * pow((1.0 + z) / 3.33, 1.7); }
 
+// Comoving distance of z = 50: the z(chi) table rises up to there, also where its
+// Newton steps no longer settle further out.  Simpson in ln(1 + z), 256 intervals.
+double rising_distance(double om) {
+  constexpr int kN = 256;
+  const double h = log(51.0) / kN;
+  double acc = 0.0;
+  for (int i = 0; i <= kN; ++i) {
+    const double x = exp(h * i);
+    acc += (i == 0 || i == kN ? 1.0 : (i & 1) ? 4.0 : 2.0) * x / sqrt(om * (x * x * x) + (1.0 - om));
+  }
+  return lya::kCOverH0 * h / 3.0 * acc;
+}
+
 // b_0^2 of the quasar box at z_box: (b_q(z_box) G(z_ref) (1 + z_ref)/(1 + z_box))^2.
 double qso_b2(double z_box, double z_ref, double g_ref) {
   const double b = bias_qso(z_box) * g_ref * (1.0 + z_ref) / (1.0 + z_box);
@@ -818,6 +831,7 @@ int lya_draw_quasars(const lya_box* box, const lya_qso_spec* spec, const lya_cos
   for (int ax = 0; ax < 3; ++ax) a.o[ax] = spec->observer[ax];
   a.oz = static_cast<float>(spec->observer[2]);
   a.tab = reinterpret_cast<const float4*>(w + c.tab);
+  a.t_rise = static_cast<float>(rising_distance(cosmo->omega_m) / lya::kZTabH);
   a.n_nbar = spec->n_nbar;
   a.nbar_z = spec->nbar_z;
   a.nbar = spec->nbar;

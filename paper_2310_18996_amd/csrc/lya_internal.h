@@ -353,6 +353,7 @@ struct QsoDrawArgs {
   float zb[3];            // z_i, and tiles of 64 x 8 voxels per wave (set at the launch)
   int tiles;
   const float4* tab;      // {z, c_1, c_2, c_3} per kZTabH of comoving distance
+  float t_rise;           // table steps up to which z rises with distance
   int n_nbar;
   const double* nbar_z;
   const double* nbar;

@@ -368,6 +368,9 @@ __device__ __forceinline__ float2 qso_ends(const QsoDrawArgs& a, float r2xy, int
   const float per_h = 1.0f / static_cast<float>(kZTabH);
   const float t_lo = __builtin_amdgcn_sqrtf(r2xy + r_lo) * per_h * (1.0f - 4e-6f);
   const float t_hi = __builtin_amdgcn_sqrtf(r2xy + r_hi) * per_h * (1.0f + 4e-6f);
+  // from where the table may fall or hold no number (towards the horizon) nothing
+  // bounds the voxels between its nodes: they are all kept
+  if (!(t_hi < a.t_rise)) return make_float2(__builtin_nanf(""), __builtin_nanf(""));
   return make_float2(a.tab[min(static_cast<int>(t_lo), kZTabN - 2)].x,
                      a.tab[min(static_cast<int>(t_hi), kZTabN - 2) + 1].x);
 }
