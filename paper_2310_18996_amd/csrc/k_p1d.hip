@@ -37,15 +37,22 @@ __global__ void __launch_bounds__(kPdNT, 3) k_p1d(P1dArgs a) {
   __shared__ float2 sbuf[kPdWaves][kHalfBuf];
   __shared__ float2 stw[tidx(kPdTw)];
   __shared__ float sfm[kMaxZBins];
-  __shared__ unsigned short smt[kLenClasses * mode_row(kMaxKBins)];
+  __shared__ uint32_t smt2[kLenClasses * mode_row(kMaxKBins) / 2];
+  const unsigned short* smt = reinterpret_cast<const unsigned short*>(smt2);
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int nk = a.n_kbins, row = mode_row(nk), lg = bin_split(nk);
+  // the first modes, on their way while the other tables come
+  static_assert(kLenClasses % 2 == 0 && kLenClasses * mode_row(kMaxKBins) / 2 <= 2 * kPdNT, "two words per thread");
+  const uint32_t* modes = reinterpret_cast<const uint32_t*>(a.modes);
+  const int words = kLenClasses * row / 2;
+  const uint32_t w0 = tid < words ? modes[tid] : 0u, w1 = tid + kPdNT < words ? modes[tid + kPdNT] : 0u;
   load_twiddles<kPdTw>(stw, a.tw2048, tid, kPdNT);
   for (int b = tid; b < a.n_fbins; b += kPdNT) {
     const double c = static_cast<double>(a.fcount[b]);
     sfm[b] = c > 0.0 ? static_cast<float>(a.fsum[b] / c) : 1.0f;
   }
-  const int nk = a.n_kbins, row = mode_row(nk), lg = bin_split(nk);
-  for (int i = tid; i < kLenClasses * row; i += kPdNT) smt[i] = a.modes[i];
+  if (tid < words) smt2[tid] = w0;
+  if (tid + kPdNT < words) smt2[tid + kPdNT] = w1;
   __syncthreads();
   const LdsTw tw{stw};
   float2* buf = sbuf[wv];

@@ -6,8 +6,8 @@
 // from the class counts and the table of first modes.  (A block per bin over
 // [bin][line] rows took 58 us for 50,000 lines and 32 bins, and each line's 32
 // sums went to as many cache lines.)  Below 256 lines R is 1, and the two stages are
-// one launch (the 1D power of one line and 1, 22, 64 bins: 17.3, 18.3, 20.8 us with two
-// and the table of first modes in both kernels, 15.8, 16.3, 17.0 us with one).
+// one launch (the 1D power of one line and 1, 22, 64 bins: 17.2, 18.2, 20.0 us with two
+// and the table of first modes in both kernels, 15.4, 15.2, 15.1 us with one).
 #pragma once
 
 #include "lya_internal.h"

@@ -98,25 +98,24 @@ __device__ __forceinline__ void mode_table(T* __restrict__ out, const double* __
                                            int part, int tid, int nt) {
   constexpr int nc = kLenClasses / kModeBlocks;
   static_assert(kLenClasses % kModeBlocks == 0, "whole rows per part");
-  __shared__ unsigned short tab[kLenClasses * mode_row(kMaxKBins)];
+  __shared__ int lo[nc], hi[nc];
   const int row = mode_row(nk), c0 = part * nc;
+  if (tid < nc) {
+    lo[tid] = kHalfMax + 1;
+    hi[tid] = 0;
+  }
+  __syncthreads();
   for (int i = tid; i < nc * (nk + 1); i += nt) {
-    const int c = c0 + i / (nk + 1), b = i % (nk + 1);
-    tab[c * row + b] = static_cast<unsigned short>(c > 0 ? first_mode(k_edges[b], 1 << c, dv) : 1);
+    const int c = i / (nk + 1), b = i % (nk + 1), m = c0 + c > 0 ? first_mode(k_edges[b], 1 << (c0 + c), dv) : 1;
+    out[(c0 + c) * row + b] = static_cast<T>(m);
+    atomicMin(&lo[c], m);   // (one thread per row over the finished row took longer than the modes)
+    atomicMax(&hi[c], m);
   }
   __syncthreads();
-  for (int c = c0 + tid; c < c0 + nc; c += nt) {
-    unsigned short lo = tab[c * row], hi = lo;
-    for (int b = 1; b <= nk; ++b) {
-      const unsigned short m = tab[c * row + b];
-      lo = m < lo ? m : lo;
-      hi = m > hi ? m : hi;
-    }
-    tab[c * row + nk + 1] = lo;
-    tab[c * row + nk + 2] = hi;
+  if (tid < nc) {
+    out[(c0 + tid) * row + nk + 1] = static_cast<T>(lo[tid]);
+    out[(c0 + tid) * row + nk + 2] = static_cast<T>(hi[tid]);
   }
-  __syncthreads();
-  for (int i = c0 * row + tid; i < (c0 + nc) * row; i += nt) out[i] = tab[i];
 }
 
 // |X_m|^2 scale of a transformed line for the modes lo <= m < hi (1 <= m <= M),
