@@ -51,12 +51,14 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch from rocprofv3 FETCH_SIZE and WRITE_SIZE (KiB per
 # dispatch) on the 2048^3 + 1M-skewer workload, scaled by what the same
 # counters read for a plain 4 GiB device copy (FETCH_SIZE x 2, WRITE_SIZE x 1);
-# profiles/box2048_skewers1M_hbm_traffic.md.  Keyed by (kernel, FFT variant)
+# profiles/box2048_skewers1M_hbm_traffic.md and, for the quasar draw of the
+# quasar leg, profiles/quasars2048_kernel_stats_hbm_traffic.md.  Keyed by (kernel, FFT variant)
 # for the strided passes and by (chunk, blocks per CU, unroll) for the skewer
 # kernel; valid only for the kernels as they were when the counters were taken
 # (a changed kernel must drop its entry) and reported only for that workload.
-TRAFFIC = {("fft_x", 9): 137490967113, ("fft_y", 8): 140316083069,
-           ("fft_z_gen", "2buf"): 71343721648, ("fft_x2", None): 137466313366, ("fft_y2", None): 137819123443}
+TRAFFIC = {("fft_x", 9): 137490967113, ("fft_x", 15): 137442534380, ("fft_y", 8): 138196343843,
+           ("fft_z_gen", "2buf"): 71343721648, ("fft_x2", None): 137466313366, ("fft_y2", None): 137819123443,
+           ("skewers", (4, 4, 1)): 15062803807, ("qso_draw", None): 137444557543}
 TRAFFIC_CONFIG = "big"
 
 
