@@ -32,7 +32,8 @@ constexpr int kPdTw = kTw2048 * 3 / 4;
 // per pixel over all edges was five dependent LDS reads).  The arithmetic of each
 // power is as in a radix-4 transform of one line.  35M pixels of 50,000 lines:
 // 305 us with FP64 bin searches per line and two blocks per CU, 214 us;
-// 128 us with the queue on 16 cache lines.
+// 128 us with the queue on 16 cache lines, 124 us with the table from the launch before
+// (read per line from memory instead of the block's copy: 131 us).
 __global__ void __launch_bounds__(kPdNT, 3) k_p1d(P1dArgs a) {
   __shared__ float2 sbuf[kPdWaves][kHalfBuf];
   __shared__ float2 stw[tidx(kPdTw)];

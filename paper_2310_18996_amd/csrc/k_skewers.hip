@@ -163,7 +163,7 @@ __device__ __forceinline__ void gauss7_at(const SkewerArgs& a, const int64_t (&p
 // two waves per SIMD nothing else hides them), with a plane's address in
 // scalar registers.
 // 35M pixels of 50,000 lines in a 512^3 box: 3.11 ms when each pixel read its
-// 343 voxels from LDS, 1.91 ms now (1.59 ms without delta_S; the same from a 64^3
+// 343 voxels from LDS, 1.78 ms now (the same from a 64^3
 // box: bound by vector issue and the latencies two waves per SIMD leave open.
 // Reading a plane ahead took 2.26 against 2.07 ms under the profiler: spills).
 constexpr int kGaussRows = 84;                            // z runs of 16 in a wave's slice (42 of 32)
@@ -520,14 +520,15 @@ struct BinWalk {
 // reads its cell's four columns.  The arithmetic is the same to the bit.
 // Cells are numbered by the boundaries crossed since the wave's first pixel, all
 // axes together; a number that no pixel has stays unused.  Lines with steps that
-// may cross more than 15 boundaries in 64 pixels (above a fifth of a cell along an
-// axis) gather pixel by pixel.
+// may cross more than 15 boundaries in 64 pixels (steps above about a fifth of a cell
+// summed over the axes: 0.206 along one, 0.079 along each of three) gather pixel by
+// pixel.
 // What bounded the gathers: the address unit (20 cycles each, 70% busy) and that
 // every step waited for the stores of the step before (loads and stores complete
 // in order).  1.1e9 pixels of 1M lines in a 2048^3 box without delta_S and FGPA
-// 6.7 -> 5.6 ms, with both and bins 11.9 -> 10.6 ms (now two thirds vector issue);
-// 35M wide-angle pixels in 512^3 (four BF16 boxes) 592 -> 481 us, (FP32) 788 -> 696
-// us.  The columns alone, without the order of loads and stores, took 13.1 ms.
+// 6.7 -> 5.6 ms, with both and bins 11.9 -> 10.6 ms (0.77 vector
+// instructions per CU cycle); 35M wide-angle pixels in 512^3 (four BF16 boxes) 592 -> 481
+// us (vector unit 72% busy), (FP32) 788 -> 643 us.  The columns alone, without the order of loads and stores, took 13.1 ms.
 constexpr int kCells = 16;
 __device__ __forceinline__ bool cells_fit(int64_t sx, int64_t sy, int64_t sz) {
   // 63 steps cross at most floor(63 |s|) + 1 boundaries of an axis

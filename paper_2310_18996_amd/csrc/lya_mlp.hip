@@ -309,7 +309,7 @@ __global__ void __launch_bounds__(256) k_adam(AdamArgs a, const float* __restric
 // for 0.4 GFLOP; now 32 us, bound by the chain of six dependent layers in
 // k_emu_rows.
 // No row of the batch needs another until the weight gradients, so
-// k_emu_rows takes 16 rows through the forward pass, the loss and the backward
+// k_emu_rows takes 4, 8 or 16 rows (row_shape) through the forward pass, the loss and the backward
 // pass to the inputs of every layer, and k_emu_grads then forms all weight and
 // bias gradients (and, in training, Adam's update of each parameter, which only
 // it touches).  The products, their order of summation and their roundings are
