@@ -62,12 +62,6 @@ __device__ __forceinline__ float2 ld_field(const SkewerArgs& a, size_t i) {
   else return a.field[i];
 }
 
-template <bool B16>
-__device__ __forceinline__ float2 ld_wide(const SkewerArgs& a, int k, size_t i) {
-  if constexpr (B16) return unpack_bf16x2(a.wide_bf16[k][i]);
-  else return a.wide[k][i];
-}
-
 // Interpolation modes of the skewer kernel.
 enum { kSkTri = 0, kSkWide = 1, kSkGauss = 2 };
 
@@ -657,9 +651,9 @@ struct LineNoise {
   int ps_fixed_amp;
 };
 
-// (the Gaussian mode's LDS leaves two waves per SIMD; four FP32 boxes need 145 registers)
+// (the Gaussian mode's LDS leaves two waves per SIMD)
 template <int U, int MODE, bool B16>
-__global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : MODE == kSkWide && !B16 ? 3 : U == 1 ? 4 : 1) k_skewers(SkewerArgs a) {
+__global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : U == 1 ? 4 : 1) k_skewers(SkewerArgs a) {
   __shared__ float2 sbuf[kSkWaves][kHalfBuf];
   __shared__ __align__(8) float sgauss[MODE == kSkGauss ? kSkWaves : 1][MODE == kSkGauss ? kGaussWords : 1];
   constexpr bool kCellWalk = U == 1 && MODE != kSkGauss;
@@ -924,7 +918,7 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : MODE == kSkWide 
               else gauss7_at<B16>(a, p3, N, NN, dl[0], el[0]);
             }
           } else {
-          float2 c[U][8];
+          float2 c[U][MODE == kSkWide ? 4 : 8];   // columns or corners
           float t3[U][3];
 #pragma unroll
           for (int u = 0; u < U; ++u) {
@@ -940,39 +934,37 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : MODE == kSkWide 
             t3[u][0] = static_cast<float>(static_cast<uint32_t>(px)) * 2.3283064365386963e-10f;
             t3[u][1] = static_cast<float>(static_cast<uint32_t>(py)) * 2.3283064365386963e-10f;
             t3[u][2] = static_cast<float>(static_cast<uint32_t>(pz)) * 2.3283064365386963e-10f;
-            if (MODE == kSkWide) {
+            if constexpr (MODE == kSkWide) {
+              // Lines come here whose steps are too long for the cell walk.  The four
+              // columns, z taken, box by box: most of a voxel's cache line is a
+              // neighbouring corner's, and with the four boxes in turn at each corner
+              // the 64 lanes' lines left the L1 in between (1.2e8 FP32 pixels in
+              // directions all over, 0.3 and 1 cells a step: 12.0 and 31.5 ms by two
+              // corners, all four boxes each; 8.9 and 26.7 so; BF16 10.7 and 29.9, 8.1
+              // and 24.5).  Three waves per SIMD, without FP32's spills, take 8.6 and 24.8,
+              // but short lines there are 2-5% slower than on four.
               // plane offsets in 64 bits, offsets within a plane (< n^2) in 32
               const size_t x0 = static_cast<size_t>(ix) * NN, x1 = static_cast<size_t>(jx) * NN;
               const uint32_t y0 = iy * static_cast<uint32_t>(N), y1 = jy * static_cast<uint32_t>(N);
-              const size_t ci[8] = {x0 + (y0 + iz), x0 + (y0 + jz), x0 + (y1 + iz), x0 + (y1 + jz),
-                                    x1 + (y0 + iz), x1 + (y0 + jz), x1 + (y1 + iz), x1 + (y1 + jz)};
-              // the gathers of G corners box by box, then eta_par = u_p u_q eta^pq per
-              // corner.  Lines come here whose steps are too long for the cell walk, and
-              // most of a corner's cache line is then a neighbouring corner's: with the
-              // four boxes in turn at each corner their 64 lanes' lines left the L1 in
-              // between (100M FP32 pixels in directions all over, 0.3 and 1 cells a step:
-              // 12.0 and 31.5 ms by two corners, 11.4 and 30.7 ms by eight; box by box
-              // 8.6 and 24.8).  BF16 takes four corners, what four waves per SIMD leave
-              // (8.8 and 26.9 ms; all eight on three waves 8.1 and 25.5, but then the
-              // cell walk is slower: 416 against 404 us for 30M pixels at 0.09 cells a
-              // step; FP32 on three waves 563 against 571 us, its walk spilled on four)
-              constexpr int G = B16 ? 4 : 8;
+              const size_t col[4] = {x0 + y0, x0 + y1, x1 + y0, x1 + y1};
+              typename GaussCell<B16>::type w[4][4][2];
 #pragma unroll
-              for (int h = 0; h < 8; h += G) {
-                float2 w0[G], w1[G], w2[G], w3[G];
+              for (int f = 0; f < 4; ++f) {
+                const typename GaussCell<B16>::type* b;
+                if constexpr (B16) b = f == 0 ? a.field_bf16 : a.wide_bf16[f - 1];
+                else b = f == 0 ? a.field : a.wide[f - 1];
 #pragma unroll
-                for (int k = 0; k < G; ++k) w0[k] = ld_field<B16>(a, ci[h + k]);
-#pragma unroll
-                for (int k = 0; k < G; ++k) w1[k] = ld_wide<B16>(a, 0, ci[h + k]);
-#pragma unroll
-                for (int k = 0; k < G; ++k) w2[k] = ld_wide<B16>(a, 1, ci[h + k]);
-#pragma unroll
-                for (int k = 0; k < G; ++k) w3[k] = ld_wide<B16>(a, 2, ci[h + k]);
-#pragma unroll
-                for (int k = 0; k < G; ++k) {
-                  c[u][h + k] = make_float2(w0[k].x, ww.eta(w0[k], w1[k], w2[k], w3[k]));
+                for (int k = 0; k < 4; ++k) {
+                  w[f][k][0] = b[col[k] + iz];
+                  w[f][k][1] = b[col[k] + jz];
                 }
-                if constexpr (G < 8) __builtin_amdgcn_sched_barrier(0);
+              }
+#pragma unroll
+              for (int k = 0; k < 4; ++k) {
+                const float2 v0 = gauss_cell(w[0][k][0]), v1 = gauss_cell(w[0][k][1]);
+                const float e0 = ww.eta(v0, gauss_cell(w[1][k][0]), gauss_cell(w[2][k][0]), gauss_cell(w[3][k][0]));
+                const float e1 = ww.eta(v1, gauss_cell(w[1][k][1]), gauss_cell(w[2][k][1]), gauss_cell(w[3][k][1]));
+                c[u][k] = make_float2(v0.x + t3[u][2] * (v1.x - v0.x), e0 + t3[u][2] * (e1 - e0));
               }
             } else {
               // byte addresses: each x plane's start as one 32 x 32 -> 64-bit
@@ -999,10 +991,17 @@ __global__ void __launch_bounds__(kSkNT, MODE == kSkGauss ? 2 : MODE == kSkWide 
 #pragma unroll
           for (int u = 0; u < U; ++u) {
             const float tx = t3[u][0], ty = t3[u][1], tz = t3[u][2];
-            dl[u] = trilerp(tx, ty, tz, c[u][0].x, c[u][1].x, c[u][2].x, c[u][3].x, c[u][4].x, c[u][5].x,
-                            c[u][6].x, c[u][7].x);
-            el[u] = trilerp(tx, ty, tz, c[u][0].y, c[u][1].y, c[u][2].y, c[u][3].y, c[u][4].y, c[u][5].y,
-                            c[u][6].y, c[u][7].y);
+            if constexpr (MODE == kSkWide) {
+              const float cd[4] = {c[u][0].x, c[u][1].x, c[u][2].x, c[u][3].x};
+              const float ce[4] = {c[u][0].y, c[u][1].y, c[u][2].y, c[u][3].y};
+              dl[u] = bilerp(tx, ty, cd);
+              el[u] = bilerp(tx, ty, ce);
+            } else {
+              dl[u] = trilerp(tx, ty, tz, c[u][0].x, c[u][1].x, c[u][2].x, c[u][3].x, c[u][4].x, c[u][5].x,
+                              c[u][6].x, c[u][7].x);
+              el[u] = trilerp(tx, ty, tz, c[u][0].y, c[u][1].y, c[u][2].y, c[u][3].y, c[u][4].y, c[u][5].y,
+                              c[u][6].y, c[u][7].y);
+            }
           }
           }
 #pragma unroll
