@@ -536,8 +536,12 @@ __device__ __forceinline__ bool cells_fit(int64_t sx, int64_t sy, int64_t sz) {
 // cells, are right modulo the box, but their cells are no longer in the order that
 // the cell walk and the 7^3 windows count them in.
 __device__ __forceinline__ bool no_wrap(int64_t ox, int64_t oy, int64_t oz) {
-  constexpr int64_t kHalf = int64_t(1) << 62;
-  return ox >= -kHalf && ox < kHalf && oy >= -kHalf && oy < kHalf && oz >= -kHalf && oz < kHalf;
+  // (from -2^62 up to 2^62 the two highest bits are alike)
+  const auto top = [](int64_t v) {
+    const uint32_t h = static_cast<uint32_t>(static_cast<uint64_t>(v) >> 32);
+    return h ^ (h << 1);
+  };
+  return static_cast<int32_t>(top(ox) | top(oy) | top(oz)) >= 0;
 }
 __device__ __forceinline__ uint32_t abs_diff(uint32_t a, uint32_t uniform) {
   uint32_t r;
